@@ -227,7 +227,8 @@ int letkf_set_state(letkf_handle* h, const double* X, uint64_t frame, void* stre
 /* Per-domain intermediates of the last analysis (needs LETKF_FLAG_DEBUG):
  * C_out [m x m] (C = Y'^T diag(r) Y', no (m-1)/rho I), lam_out [m]
  * (ascending eigenvalues of A), T_out [m x m] (W + wbar 1^T), sweeps_out
- * (Jacobi sweeps used), cycles_out [5] (shader-clock cycles spent by the
+ * (Jacobi sweeps used; m > 128: matrix products of the polynomial stages that
+ * form A^(-1/2)), cycles_out [5] (shader-clock cycles spent by the
  * domain's workgroup in: gather + C/b, Cholesky, Jacobi, wbar/W/T, update).
  * Any output may be NULL.  Waits for the stream. */
 int letkf_debug_domain(letkf_handle* h, int32_t domain, double* C_out, double* lam_out,
@@ -250,7 +251,8 @@ int letkf_debug_placement(letkf_handle* h, int32_t domain, uint32_t* hw_id_out, 
  * refinement, T}.  Waits for the stream. */
 int letkf_debug_substeps(letkf_handle* h, int32_t domain, double* cycles_out, void* stream);
 
-/* Number of domains whose eigensolver hit the sweep cap in the last analysis
+/* Number of domains of the last analysis whose eigensolver hit the sweep cap, or
+ * (m > 128) whose condition number passed the polynomial stages' range of 1e14
  * (0 when all converged); waits for the stream. */
 int letkf_unconverged_domains(letkf_handle* h, int32_t* count, void* stream);
 
@@ -324,7 +326,8 @@ int letkf_autotune(letkf_handle* h, int32_t reps, letkf_tuning* out, void* strea
  * LETKF_EINVAL for out-of-range fields. */
 int letkf_set_tuning(letkf_handle* h, const letkf_tuning* t, void* stream);
 
-/* Totals since create (or set_state): Jacobi sweeps over all domain solves,
+/* Totals since create (or set_state): Jacobi sweeps (m > 128: matrix products of
+ * the polynomial stages) over all domain solves,
  * and the number of domain solves.  Waits for the stream. */
 int letkf_sweep_stats(letkf_handle* h, uint64_t* sweeps, uint64_t* domain_solves, void* stream);
 

@@ -45,7 +45,7 @@ def kernel_hash() -> str:
     change to the host runtime leaves the kernels' memory traffic as it was."""
     h = hashlib.sha256()
     h.update(" ".join(f for f in FLAGS if not f.startswith(("/", "-I"))).encode())
-    for f in ("kernels.hip", "desc.hpp", "launch.hpp"):
+    for f in ("kernels.hip", "desc.hpp", "isqrt_plan.hpp", "launch.hpp"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(f.encode() + b"\0" + fh.read())
     return h.hexdigest()[:16]

@@ -62,10 +62,10 @@ struct InstDesc {
   const double* pist_coef;   // [terms]: its coefficient (1, or 1 - k_j for the domain's own row)
   double* pist_r;            // [n_dom][2][m] overlap mismatch of each domain, instant, member
   double* pist_c;            // [n_dom][2][m] pistons added before the merge
-  double* bigA;              // m > 128: [n_dom][256][256] A (row-major), then T
-  double* bigB;              // m > 128: [n_dom][256][256] L, then B = L J, then U (column-major)
-  double* bigv;              // m > 128: [n_dom][5][256] b, wbar, lambda, spare
-  int32_t* bigf;             // m > 128: [n_dom][4] converged, rounds that rotated, sweeps, spare
+  double* bigA;              // m > 128: [n_dom][256][256] A
+  double* bigW;              // m > 128: [n_dom][5][256][256] M, M^2, P and two Z of the stages (column-major)
+  double* bigv;              // m > 128: [n_dom][5][256] b, wbar, spare, partial sums of |A^2|_F^2, spare
+  int32_t* bigf;             // m > 128: [n_dom][4] debug Jacobi: converged, rounds that rotated, sweeps; table row of the stages
   uint32_t* dom_sweeps;      // [n_dom] Jacobi sweeps of each domain, summed over every analysis
   double* Ascr;              // FP64, m <= 128: [n_dom][m(m+1)/2] each domain's A (lower triangle packed by rows), for refining wbar
   double* dbg;               // [n_dom][2*m*m + m] C, lambda, T (NULL unless debug)

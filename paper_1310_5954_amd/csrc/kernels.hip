@@ -15,6 +15,7 @@
 #include <mutex>
 
 #include "desc.hpp"
+#include "isqrt_plan.hpp"
 #include "launch.hpp"
 
 namespace letkf {
@@ -330,6 +331,7 @@ __global__ __launch_bounds__(64) void k_advance(const InstDesc* __restrict__ tab
 // dominate W.
 // ----------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // The thread index as a value the compiler may not move: every phase of the
@@ -2148,39 +2150,44 @@ __global__ __launch_bounds__(256) void k_analysis(const InstDesc* __restrict__ t
 }
 
 // ----------------------------------------------------------------------------
-// a4-a8 for ensembles of 129..256 members (padded to 256, FP64).  A domain's
-// 256 x 256 matrices (512 KB each) do not fit in LDS, so its analysis is a
-// sequence of launches over scratch in the instance workspace (A, B and a few
-// vectors per domain, which stay in L2 between launches):
-//   k_big_gram    A = (m-1)/rho I + Y'^T diag(r) Y' by 64 x 64 tiles on FP64
-//                 MFMA, b = Y'^T diag(r) d; clears the domain's Jacobi flags
-//   k_big_chol    A = L L^T, right-looking by panels, one workgroup per domain
-//   k_big_round   one round of the blocked one-sided Jacobi (below)
-//   k_big_sweep   end of a sweep: a domain is done when no round rotated
-//   k_big_eig     lambda, U, wbar (one refinement step through the exact A)
-//   k_big_T       T = U diag(sqrt((m-1)/lambda)) U^T + wbar 1^T, by tiles
-//   k_big_update  Z = xbar 1^T + X' T, by 64 x 64 tiles
-// The Jacobi is the one-sided method of the m <= 128 kernel on the columns of
-// L (L J = U Sigma), visited by blocks: the columns form NB blocks of 16 (NB
-// even; columns past m are unit vectors that never rotate).  A sweep is NB - 1
-// rounds of a round-robin tournament between the blocks (circle method, block
-// 0 fixed); in a round every pair of blocks is one workgroup that holds its 32
-// columns in LDS and rotates the 256 pairs between them in 16 steps of 16
-// disjoint pairs (the first round also the pairs inside each block), so every
-// pair of columns is visited once per sweep.  Launch boundaries order the
-// rounds; a converged domain's later launches return at once.
+// a4-a8 for ensembles of 129..256 members (padded to a multiple of 16, leading
+// dimension 256, FP64).  A domain's matrices (512 KB each) do not fit in LDS, so
+// its analysis is a sequence of launches over scratch in the instance workspace
+// (which stays in L2 between launches), one wavefront group per 16 x 16 tile:
+//   k_big_gram    A = (m-1)/rho I + Y'^T diag(r) Y' by tiles, b = Y'^T diag(r) d
+//   k_big_mul     the matrix products of the polynomial stages of A^(-1/2)
+//                 (isqrt_plan.hpp), one launch per product
+//   k_big_slow    the stages past the launched ones, for condition bounds that
+//                 need more than kBigStages of them (an empty launch otherwise)
+//   k_big_wbar    wbar = Z (Z b), refined once with A
+//   k_big_update  Z_l = xbar 1^T + X' (sqrt(m-1) Z + wbar 1^T)
+// W = [(m-1) A^-1]^(1/2) needs no eigenvectors: A's smallest eigenvalue is at
+// least (m-1)/rho, so with the upper bound beta = |A^2|_F^(1/2) its spectrum's
+// interval is known, and Z = A^(-1/2) comes from minimax polynomial stages
+//   P = q(M),  Z <- P Z,  M <- P (P M),   M_0 = A, Z_0 = I,
+// the first stage's coefficients carrying the scaling by beta.  The products
+// are polynomials in A taken from the left, never mirrored: their rounding
+// stays commuting with A to first order (a CPU replay matches Cholesky + SVD
+// at every condition number up to 1e15; forcing symmetry costs a factor 10).
+// Every stage has degree 4 (the table's rows of that form), so that the launch
+// sequence is the same for every condition number; the launches of stages a
+// domain does not need return at once.  On the 32 x 32 pupil (m = 197, one
+// domain) the blocked Jacobi this replaced took 3.42 of the analysis's 3.98 ms,
+// in 312 dependent launches.
 // ----------------------------------------------------------------------------
 constexpr int kBigM = 256;
 constexpr int kBigLd = kBigM + 8;     // LDS column stride in k_big_round
 constexpr int kBigMaxSweeps = 24;
+constexpr int kBigStages = 7;
 
 struct BigDom {
   const InstDesc* I;
   int l, est_off, e, obs_off, s;
   double* A;
-  double* B;
+  double* W;   // 5 matrices: M, M^2 (then P M), P, Z of even and of odd stages
   double* v;
   int32_t* f;
+  __device__ double* mat(int k) const { return W + (size_t)k * kBigM * kBigM; }
 };
 
 __device__ __forceinline__ BigDom big_dom(const InstDesc* __restrict__ tab, const ClassBatch& cb, int item) {
@@ -2193,7 +2200,7 @@ __device__ __forceinline__ BigDom big_dom(const InstDesc* __restrict__ tab, cons
   d.obs_off = d.I->dom[4 * d.l + 2];
   d.s = d.I->dom[4 * d.l + 3];
   d.A = d.I->bigA + (size_t)d.l * kBigM * kBigM;
-  d.B = d.I->bigB + (size_t)d.l * kBigM * kBigM;
+  d.W = d.I->bigW + (size_t)d.l * 5 * kBigM * kBigM;
   d.v = d.I->bigv + (size_t)d.l * 5 * kBigM;
   d.f = d.I->bigf + 4 * d.l;
   return d;
@@ -2204,137 +2211,411 @@ __device__ __forceinline__ double* big_dbg(const BigDom& D) {
   return D.I->dbg ? D.I->dbg + (size_t)D.l * (2 * m * m + m + kDbgTail) : nullptr;
 }
 
-// 1024 threads: member j = t % 256 of observation quarter t / 256, summed in LDS.
-// grid (10, items): the upper tiles (ti <= tj) of the 4 x 4 grid of 64 x 64
-// tiles of C = Y'^T diag(r) Y', on FP64 MFMA: wavefront w owns the 32 x 32
-// quadrant (w / 2, w % 2) of the tile, 2 x 2 MFMA tiles of 16 x 16, over
-// chunks of 32 observations staged in LDS (Ya: Y' rows of the tile's rows,
-// Yb: r Y' of its columns).  The diagonal tiles also form their 64 entries of
-// b = Y'^T diag(r) d, and tile 0 clears the domain's Jacobi flags.
-__global__ __launch_bounds__(256) void k_big_gram(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                                  int cls) {
-  __shared__ double Ya[32][64], Yb[32][64], rd[32], bred[4][64];
-  const ClassBatch& cb = hdr->cls[cls];
-  if ((int)blockIdx.y >= cb.dom_off[cb.n]) return;
-  int t = blockIdx.x, ti = 0;
-  while (t >= 4 - ti) { t -= 4 - ti; ++ti; }
-  const int tj = ti + t, i0 = 64 * ti, j0 = 64 * tj;
-  const bool diag = ti == tj;
-  const BigDom D = big_dom(tab, cb, blockIdx.y);
-  const InstDesc& I = *D.I;
-  const int m = I.m, tid = threadIdx.x, w = tid / 64, lane = tid % 64, nobs = 2 * D.s;
-  if (blockIdx.x == 0 && tid == 0) {
-    D.f[0] = 0;
-    D.f[1] = 0;
-    D.f[2] = 0;
-  }
-  const double* Yp = (const double*)I.Yp;
-  const int qr = 32 * (w / 2), qc = 32 * (w % 2);  // the wavefront's quadrant
-  f64x4 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  double bpart = 0.0;  // diagonal tiles: b for row i0 + lane, observations w, w + 4, ...
-  // Thread tid stages observations tid / 64 + 4 e (e < 8) of every chunk, row
-  // entry c = tid % 64.  The next chunk's values are loaded into registers
-  // before this chunk's products, and their row indices one chunk earlier
-  // still, so the loads' latency overlaps the MFMAs instead of preceding them.
-  const int c = tid % 64;
-  int prow[8];
-  double pr[8], pa[8], pb[8], pd[8];
-  auto fetch_idx = [&](int q0n) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int q = q0n + tid / 64 + 4 * e;
-      prow[e] = -1;
-      pr[e] = 0.0;
-      if (q < nobs) {
-        const int o = 2 * D.obs_off + q;
-        prow[e] = I.obs_row[o];
-        pr[e] = I.obs_r[o];
-      }
-    }
-  };
-  auto fetch_val = [&]() {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      pa[e] = pb[e] = pd[e] = 0.0;
-      if (prow[e] >= 0) {
-        const size_t row = (size_t)prow[e] * m;
-        if (i0 + c < m) pa[e] = Yp[row + i0 + c];
-        if (j0 + c < m) pb[e] = pr[e] * Yp[row + j0 + c];
-        if (diag && c == 0) pd[e] = pr[e] * I.d[prow[e]];
-      }
-    }
-  };
-  fetch_idx(0);
-  fetch_val();
-  fetch_idx(32);
-  for (int q0 = 0; q0 < nobs; q0 += 32) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      Ya[tid / 64 + 4 * e][c] = pa[e];
-      Yb[tid / 64 + 4 * e][c] = pb[e];
-      if (c == 0) rd[tid / 64 + 4 * e] = pd[e];
-    }
-    __syncthreads();
-    if (q0 + 32 < nobs) {
-      fetch_val();
-      fetch_idx(q0 + 64);
-    }
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const int k = 4 * ks + lane / 16;
-      double av[2], bv[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        av[a] = Ya[k][qr + 16 * a + lane % 16];
-        bv[a] = Yb[k][qc + 16 * a + lane % 16];
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-    }
-    if (diag)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) bpart = fma(Ya[w + 4 * e][lane], rd[w + 4 * e], bpart);
-    __syncthreads();
-  }
-  if (diag) {
-    bred[w][lane] = bpart;
-    __syncthreads();
-    if (tid < 64) {
-      const int i = i0 + tid;
-      D.v[i] = i < m ? (bred[0][tid] + bred[1][tid]) + (bred[2][tid] + bred[3][tid]) : 0.0;
-    }
-  }
-  double* dbg = big_dbg(D);
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = i0 + qr + 16 * a + lane / 16 + 4 * v, j = j0 + qc + 16 * b + lane % 16;
-        if (i > j) continue;  // one writer per symmetric pair (deterministic)
-        const double c = acc[a][b][v];
-        double x;
-        if (i < m && j < m) {
-          x = c + (i == j ? I.a_diag : 0.0);
-          if (dbg) {
-            dbg[(size_t)i * m + j] = c;
-            dbg[(size_t)j * m + i] = c;
-          }
-        } else {
-          x = i == j ? 1.0 : 0.0;  // padded members: identity
-        }
-        D.A[(size_t)i * kBigM + j] = x;
-        D.A[(size_t)j * kBigM + i] = x;
-      }
+// The sum of v over a 256-thread workgroup, on every thread.
+__device__ __forceinline__ double block_sum256(double v, double* red) {
+  v = group_sum<16>(v);
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
+  __syncthreads();
+  const double t = (red[0] + red[1]) + (red[2] + red[3]);
+  __syncthreads();
+  return t;
 }
 
+// grid (upper tiles ti <= tj, items), 8 wavefronts: one 16 x 16 tile of C per
+// workgroup, the observations in blocks of 16 dealt over the wavefronts (block
+// b to wavefront b mod 8), four k-steps of v_mfma_f64_16x16x4f64 each, and
+// their partial tiles summed in LDS.  91 workgroups at m = 197, against the ten
+// 64 x 64 tiles of the former split, whose 51 chunks in sequence were a latency
+// chain (306 us on the global 32 x 32 domain).  A diagonal tile also forms its
+// 16 entries of b.
+constexpr int kGramWaves = 8, kGramObs = 1024;
+__global__ __launch_bounds__(64 * kGramWaves) void k_big_gram(const InstDesc* __restrict__ tab,
+                                                              const BatchHdr* __restrict__ hdr, int cls) {
+  __shared__ int rowT[kGramObs];
+  __shared__ double rT[kGramObs], rdT[kGramObs];
+  __shared__ double red[kGramWaves][16 * 17], bred[kGramWaves][16];
+  const ClassBatch& cb = hdr->cls[cls];
+  if ((int)blockIdx.y >= cb.dom_off[cb.n]) return;
+  const BigDom D = big_dom(tab, cb, blockIdx.y);
+  const InstDesc& I = *D.I;
+  const int m = I.m, nt = (m + 15) / 16;
+  int t = blockIdx.x, ti = 0;
+  while (ti < nt && t >= nt - ti) { t -= nt - ti; ++ti; }
+  if (ti >= nt) return;
+  const int tj = ti + t, i0 = 16 * ti, j0 = 16 * tj;
+  const bool diag = ti == tj;
+  const int tid = threadIdx.x, w = tid / 64, lane = tid % 64, g = lane / 16, i = lane % 16, nobs = 2 * D.s;
+  const double* Yp = (const double*)I.Yp;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  double bpart = 0.0;
+  const bool ia = i0 + i < m, ja = j0 + i < m;
+  for (int g0 = 0; g0 < nobs; g0 += kGramObs) {
+    const int gn = min(kGramObs, nobs - g0), gr = (gn + 15) & ~15;
+    if (g0) __syncthreads();
+    for (int q = tid; q < gr; q += 64 * kGramWaves) {
+      int row = 0;
+      double r = 0.0, rd = 0.0;
+      if (q < gn) {
+        row = gload(I.obs_row + 2 * D.obs_off + g0 + q);
+        r = gload(I.obs_r + 2 * D.obs_off + g0 + q);
+        rd = r * gload(I.d + row);
+      }
+      rowT[q] = row;
+      rT[q] = r;
+      rdT[q] = rd;
+    }
+    __syncthreads();
+    // observation 16 b + 4 g + h in k-step h; a block past the table has weight zero
+#pragma unroll 4
+    for (int b = w; b < gr / 16; b += kGramWaves) {
+      double ya[4], yb[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const double* y = Yp + (size_t)rowT[16 * b + 4 * g + h] * m;
+        ya[h] = ia ? gload(y + i0 + i) : 0.0;
+        yb[h] = diag ? ya[h] : ja ? gload(y + j0 + i) : 0.0;
+      }
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        if (diag) bpart = fma(rdT[16 * b + 4 * g + h], ya[h], bpart);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ya[h], rT[16 * b + 4 * g + h] * yb[h], acc, 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[w][i * 17 + g + 4 * v] = acc[v];
+  bpart += __shfl_xor(bpart, 16, 64);
+  bpart += __shfl_xor(bpart, 32, 64);
+  if (lane < 16) bred[w][i] = bpart;
+  __syncthreads();
+  double* dbg = big_dbg(D);
+  if (tid < 256) {
+    const int r = tid % 16, c = tid / 16;
+    double x = 0.0;
+#pragma unroll
+    for (int k = 0; k < kGramWaves; ++k) x += red[k][c * 17 + r];
+    const int gi = i0 + r, gj = j0 + c;
+    if (!diag || r <= c) {  // one writer per symmetric pair
+      double a;
+      if (gi < m && gj < m) {
+        a = x + (gi == gj ? I.a_diag : 0.0);
+        if (dbg) {
+          dbg[(size_t)gi * m + gj] = x;
+          dbg[(size_t)gj * m + gi] = x;
+        }
+      } else {
+        a = gi == gj ? I.a_diag : 0.0;  // padded members: the spectrum's lower bound
+      }
+      D.A[(size_t)gj * kBigM + gi] = a;
+      D.A[(size_t)gi * kBigM + gj] = a;
+    }
+  }
+  if (diag && tid < 16) {
+    double x = 0.0;
+#pragma unroll
+    for (int k = 0; k < kGramWaves; ++k) x += bred[k][tid];
+    D.v[i0 + tid] = i0 + tid < m ? x : 0.0;
+  }
+}
+
+// Tile (tr, tc) of L X (c2 X2 != nullptr: of L (c1 X + c2 X2)), column-major
+// matrices of leading dimension 256, by a 256-thread workgroup: wavefront w
+// takes the 16-row blocks w, w + 4, ... of the contraction, all its operand
+// loads first (the loads' latency, not the 13 to 16 products of a wavefront,
+// is what a tile takes), and the four partial tiles are summed in LDS.  Thread
+// t returns element (t % 16, t / 16) of the tile.
+__device__ __forceinline__ double big_tile(const double* L, const double* X, const double* X2, double c1, double c2,
+                                           int tr, int tc, int nt, double (&red)[4][16 * 17]) {
+  const int tid = threadIdx.x, w = tid / 64, lane = tid % 64, g = lane / 16, i = lane % 16;
+  double a[16];
+  f64x2 x[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int b = w + 4 * k;
+    const bool in = b < nt;
+    const double* Xc = X + (size_t)(16 * tc + i) * kBigM + 16 * (in ? b : 0) + 4 * g;
+    const double* La = L + (size_t)(16 * (in ? b : 0) + 4 * g) * kBigM + 16 * tr + i;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) a[4 * k + h] = gload(La + h * kBigM);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) x[2 * k + h] = gload((const f64x2*)Xc + h);
+    if (X2) {
+      const double* X2c = X2 + (size_t)(16 * tc + i) * kBigM + 16 * (in ? b : 0) + 4 * g;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) x[2 * k + h] = c1 * x[2 * k + h] + c2 * gload((const f64x2*)X2c + h);
+    }
+    if (!in)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) x[2 * k + h] = f64x2{0.0, 0.0};
+  }
+  __builtin_amdgcn_sched_barrier(0);  // every load issued before the first product waits
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k], x[k / 2][k % 2], acc, 0, 0, 0);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[w][i * 17 + g + 4 * v] = acc[v];
+  __syncthreads();
+  const int o = tid / 16 * 17 + tid % 16;
+  const double t = (red[0][o] + red[1][o]) + (red[2][o] + red[3][o]);
+  __syncthreads();
+  return t;
+}
+
+// Table row of a domain by its condition bound: the rows whose stages all have
+// degree 4.  Rows past kBigStages stages run in k_big_slow.
+__device__ __forceinline__ int big_row(double kappa) {
+  constexpr int rows[] = {25, 37, 48, 59, 71, 83, 95};
+  const double x = kappa > 1.0 ? 2.0 * log2(kappa) + 0.01 : 0.01;
+  for (int k = 0; k < 6; ++k)
+    if (x <= rows[k]) return rows[k];
+  return rows[6];
+}
+
+// Tile (tr, tc) of product `kind` of stage s (table row R, condition scaling
+// 1 / beta in the first stage):
+//   0: M^2    1: P = M^2 (q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I
+//   2: Z <- P Z    3: P M    4: M <- P (P M), minus I ahead of the last stage
+// Returns the thread's element.
+__device__ __forceinline__ double big_product(const BigDom& D, int kind, int s, const IsqrtRow& R, double beta, int tr,
+                                              int tc, int nt, double (&red)[4][16 * 17]) {
+  const double* M = s == 0 ? D.A : D.mat(0);
+  double* M2 = D.mat(1);
+  double* P = D.mat(2);
+  double* Zo = D.mat(3 + s % 2);
+  const int r = 16 * tr + threadIdx.x % 16, c = 16 * tc + threadIdx.x / 16;
+  const size_t at = (size_t)c * kBigM + r;
+  if (kind == 0) {
+    const double t = big_tile(M, M, nullptr, 0.0, 0.0, tr, tc, nt, red);
+    M2[at] = t;
+    return t;
+  }
+  if (kind == 1) {
+    double q[5], scale = s == 0 ? 1.0 / sqrt(beta) : 1.0;
+    const double step = s == 0 ? 1.0 / beta : 1.0;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      q[k] = R.c[s][k] * scale;
+      scale *= step;
+    }
+    double t = big_tile(M2, M, M2, q[3], q[4], tr, tc, nt, red);
+    t += q[2] * M2[at] + q[1] * M[at] + (r == c ? q[0] : 0.0);
+    P[at] = t;
+    if (s == 0) Zo[at] = t;
+    return t;
+  }
+  if (kind == 2) {
+    const double t = big_tile(P, D.mat(3 + (s + 1) % 2), nullptr, 0.0, 0.0, tr, tc, nt, red);
+    Zo[at] = t;
+    return t;
+  }
+  if (kind == 3) {
+    const double t = big_tile(P, M, nullptr, 0.0, 0.0, tr, tc, nt, red);
+    M2[at] = t;
+    return t;
+  }
+  const double t = big_tile(P, M2, nullptr, 0.0, 0.0, tr, tc, nt, red) - (s + 2 == R.n && r == c ? 1.0 : 0.0);
+  D.mat(0)[at] = t;
+  return t;
+}
+
+// grid (16 nt, ...): tile (x / 16, x % 16); KIND 0, 1, 4: that product; KIND 2:
+// products 2 and 3, by blockIdx.z.  f[3]: the domain's table row, written by the
+// first stage's KIND 1 from the tiles' partial sums of |A^2|_F^2 (KIND 0).
+template <int KIND>
+__global__ __launch_bounds__(256) void k_big_mul(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
+                                                 int cls, int s) {
+  __shared__ double red[4][16 * 17];
+  __shared__ double bs[4];
+  const ClassBatch& cb = hdr->cls[cls];
+  if ((int)blockIdx.y >= cb.dom_off[cb.n]) return;
+  const BigDom D = big_dom(tab, cb, blockIdx.y);
+  const int nt = (D.I->m + 15) / 16, tr = blockIdx.x / 16, tc = blockIdx.x % 16, tid = threadIdx.x;
+  if (tr >= nt || tc >= nt) return;
+  double beta = 1.0;
+  int row = 0;
+  if (KIND != 0 || s > 0) {
+    if (KIND == 1 && s == 0) {
+      // every workgroup sums the same partials in the same order
+      const double part = tid / 16 < nt && tid % 16 < nt ? D.v[3 * kBigM + tid] : 0.0;
+      beta = sqrt(sqrt(block_sum256(part, bs)));
+      const double kappa = beta / D.I->a_diag;
+      row = big_row(kappa);
+      if (blockIdx.x == 0 && tid == 0) {
+        D.f[3] = row;
+        if (!(kappa <= 0x1.0p47)) gatomic_add(&D.I->st->unconverged, 1);
+      }
+    } else {
+      row = D.f[3];
+    }
+    const int n = kIsqrtPlan[row].n;
+    if (s >= n || s >= kBigStages) return;
+    if ((KIND == 4 || (KIND == 2 && blockIdx.z == 1)) && s + 1 == n) return;
+  }
+  const int kind = KIND == 2 ? (s == 0 ? 3 : 2 + (int)blockIdx.z) : KIND;
+  const double t = big_product(D, kind, s, kIsqrtPlan[row], beta, tr, tc, nt, red);
+  if (KIND == 0 && s == 0) {
+    const double sum = block_sum256(t * t, bs);
+    if (tid == 0) D.v[3 * kBigM + blockIdx.x] = sum;
+  }
+}
+
+// grid (items): the stages past kBigStages, one workgroup per domain (seconds of
+// a millisecond each: condition bounds above 7e8, where FP64 leaves 1e-8 of W).
+__global__ __launch_bounds__(256) void k_big_slow(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
+                                                  int cls) {
+  __shared__ double red[4][16 * 17];
+  const ClassBatch& cb = hdr->cls[cls];
+  if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
+  const BigDom D = big_dom(tab, cb, blockIdx.x);
+  const IsqrtRow& R = kIsqrtPlan[D.f[3]];
+  const int nt = (D.I->m + 15) / 16;
+  for (int s = kBigStages; s < R.n; ++s)
+    for (int kind = 0; kind < 5; ++kind) {
+      if (kind >= 3 && s + 1 == R.n) break;
+      for (int t = 0; t < nt * nt; ++t) big_product(D, kind, s, R, 1.0, t / nt, t % nt, nt, red);
+      __syncthreads();
+    }
+}
+
+// grid (items), 1024 threads: wbar = Z (Z b) and one refinement step with A; the
+// columns of Z (and of A) dealt over four thread groups, rows over a group.
+__global__ __launch_bounds__(1024) void k_big_wbar(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
+                                                   int cls) {
+  __shared__ double x[kBigM], part[4][kBigM];
+  const ClassBatch& cb = hdr->cls[cls];
+  if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
+  const BigDom D = big_dom(tab, cb, blockIdx.x);
+  const InstDesc& I = *D.I;
+  const int m = I.m, mp = (m + 15) & ~15, tid = threadIdx.x, r = tid % kBigM, q = tid / kBigM;
+  const int n = kIsqrtPlan[D.f[3]].n;
+  const double* Z = D.mat(3 + (n - 1) % 2);
+  auto product = [&](const double* B) {  // x <- B x; returns row r on every group
+    double t0 = 0.0, t1 = 0.0;
+    if (r < mp) {
+      const int c1 = (q + 1) * (mp / 4);
+      int c = q * (mp / 4);
+#pragma unroll 8
+      for (; c + 1 < c1; c += 2) {
+        t0 = fma(gload(B + (size_t)c * kBigM + r), x[c], t0);
+        t1 = fma(gload(B + (size_t)(c + 1) * kBigM + r), x[c + 1], t1);
+      }
+    }
+    part[q][r] = t0 + t1;
+    __syncthreads();
+    const double t = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
+    if (q == 0) x[r] = t;
+    __syncthreads();
+    return t;
+  };
+  if (q == 0) x[r] = r < mp ? D.v[r] : 0.0;
+  __syncthreads();
+  product(Z);
+  const double w0 = product(Z);
+  const double aw = product(D.A);
+  if (q == 0) x[r] = r < m ? D.v[r] - aw : 0.0;
+  __syncthreads();
+  product(Z);
+  const double w1 = product(Z);
+  if (q == 0) D.v[kBigM + r] = r < m ? w0 + w1 : 0.0;
+  if (double* dbg = big_dbg(D)) {
+    if (q == 0) x[r] = r < m ? w0 + w1 : 0.0;
+    __syncthreads();
+    const double sc = sqrt((double)(m - 1));
+    for (int k = q; k < m; k += 4)
+      if (r < m) dbg[(size_t)m * m + m + (size_t)k * m + r] = fma(sc, Z[(size_t)r * kBigM + k], x[k]);
+  }
+  if (tid == 0) {
+    const int products = kIsqrtPlan[D.f[3]].products;
+    if (I.dbg_sweeps) I.dbg_sweeps[D.l] = products;
+    gatomic_add(&I.st->sweeps, (unsigned long long)products);
+    gatomic_add(&I.st->solves, 1ull);
+  }
+}
+
+// grid (16-row tiles of the domain's state rows, groups of four column tiles,
+// items): Z_l = xbar + sqrt(m-1) X' Z + X' wbar.  The 16 rows X' are staged
+// once in LDS, each wavefront forms one 16 x 16 output tile on FP64 MFMA with
+// the columns of Z straight from L2 (32 contiguous bytes a lane).  440 workgroups
+// on the global 32 x 32 domain; the VALU form over 64 x 64 tiles took 66 us.
+__global__ __launch_bounds__(256) void k_big_update(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
+                                                    int cls) {
+  constexpr int LDX = kBigM + 1;
+  __shared__ double Xs[16 * LDX], xb[16], xw[16];
+  const ClassBatch& cb = hdr->cls[cls];
+  if ((int)blockIdx.z >= cb.dom_off[cb.n]) return;
+  const BigDom D = big_dom(tab, cb, blockIdx.z);
+  const InstDesc& I = *D.I;
+  const int m = I.m, nt = (m + 15) / 16, rows = 2 * D.e, tid = threadIdx.x, w = tid / 64, lane = tid % 64;
+  const int q0 = 16 * blockIdx.x, tc = 4 * blockIdx.y + w;
+  if (q0 >= rows || 4 * (int)blockIdx.y >= nt) return;
+  const int cur = I.st->cur, n = kIsqrtPlan[D.f[3]].n;
+  const double* Z = D.mat(3 + (n - 1) % 2);
+  const double* wbar = D.v + kBigM;
+  const double* ens = (const double*)I.ens;
+  const size_t slot = (size_t)I.n_act * m;
+  {
+    // 16 threads a row: its values into registers, their mean, then X' to LDS
+    const int rr = tid / 16, part = tid % 16, q = q0 + rr;
+    double x[16], sum = 0.0, dot = 0.0;
+    const bool on = q < rows;
+    const double* row = ens + (size_t)((q < D.e ? cur : cur ^ 1)) * slot +
+                        (size_t)(on ? I.est_act[D.est_off + (q < D.e ? q : q - D.e)] : 0) * m;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int j = part + 16 * k;
+      x[k] = on && j < m ? gload(row + j) : 0.0;
+      sum += x[k];
+    }
+    const double mean = group_sum<16>(sum) / (double)m;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int j = part + 16 * k;
+      const double xp = j < m ? x[k] - mean : 0.0;
+      Xs[rr * LDX + j] = xp;
+      dot = fma(xp, j < m ? gload(wbar + j) : 0.0, dot);
+    }
+    dot = group_sum<16>(dot);
+    if (part == 0) {
+      xb[rr] = mean;
+      xw[rr] = dot;
+    }
+  }
+  __syncthreads();
+  if (tc >= nt) return;
+  const int g = lane / 16, i = lane % 16, col = 16 * tc + i;
+  const double* Zc = Z + (size_t)col * kBigM + 4 * g;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int b = 0; b < nt; ++b) {
+    const f64x2 z0 = gload((const f64x2*)(Zc + 16 * b)), z1 = gload((const f64x2*)(Zc + 16 * b) + 1);
+    const double* xr = Xs + i * LDX + 16 * b + 4 * g;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[0], z0.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[1], z0.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[2], z1.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[3], z1.y, acc, 0, 0, 0);
+  }
+  const double sc = sqrt((double)(m - 1));
+  double* out = (double*)I.Z + (size_t)2 * D.est_off * m;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int rr = g + 4 * v;
+    if (q0 + rr < rows && col < m) gstore(out + (size_t)(q0 + rr) * m + col, xb[rr] + (xw[rr] + sc * acc[v]));
+  }
+}
+
+// ---- debug instances, m > 128: the eigenvalues of each domain's A ------------
+// As for m <= 128, when a debug record is read: Cholesky, then the one-sided
+// Jacobi by blocks (L J = U Sigma).  The columns form NB blocks of 16 (NB even;
+// columns past m are unit vectors that never rotate).  A sweep is NB - 1 rounds
+// of a round-robin tournament between the blocks (circle method, block 0
+// fixed); in a round every pair of blocks is one workgroup that holds its 32
+// columns in LDS and rotates the 256 pairs between them in 16 steps of 16
+// disjoint pairs (the first round also the pairs inside each block), so every
+// pair of columns is visited once per sweep.  Launch boundaries order the
+// rounds; a converged domain's later launches return at once.
 // A = L L^T into B (column-major, leading dimension kBigM; the upper triangle
 // zero, padded members the identity), right-looking by panels of 16 columns
 // as the m <= 128 kernel: wavefront 0 factors the panel in registers (rows
@@ -2355,8 +2636,9 @@ __global__ __launch_bounds__(64 * kBigCholWaves) void k_big_chol(const InstDesc*
     double v;
     if (c < m) v = (r >= c && r < m) ? D.A[(size_t)c * kBigM + r] : 0.0;  // A symmetric
     else v = r == c ? 1.0 : 0.0;
-    D.B[idx] = v;
+    D.W[idx] = v;
   }
+  if (tid < 3) D.f[tid] = 0;
   __syncthreads();
   for (int c0 = 0; c0 < mp; c0 += 16) {
     if (w == 0) {
@@ -2366,7 +2648,7 @@ __global__ __launch_bounds__(64 * kBigCholWaves) void k_big_chol(const InstDesc*
         const int r = c0 + lane + 64 * s;
         const bool on = r < mp;
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) a[s][jj] = on ? D.B[(size_t)(c0 + jj) * kBigM + r] : 0.0;
+        for (int jj = 0; jj < 16; ++jj) a[s][jj] = on ? D.W[(size_t)(c0 + jj) * kBigM + r] : 0.0;
       }
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
@@ -2391,7 +2673,7 @@ __global__ __launch_bounds__(64 * kBigCholWaves) void k_big_chol(const InstDesc*
         if (r < mp)
 #pragma unroll
           for (int jj = 0; jj < 16; ++jj) {
-            D.B[(size_t)(c0 + jj) * kBigM + r] = a[s][jj];
+            D.W[(size_t)(c0 + jj) * kBigM + r] = a[s][jj];
             pnl[jj][r] = a[s][jj];
           }
       }
@@ -2405,14 +2687,14 @@ __global__ __launch_bounds__(64 * kBigCholWaves) void k_big_chol(const InstDesc*
         const int rb = c0 + 16 * (R + 1), cb = c0 + 16 * (Cc + 1);
         f64x4 acc;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] = D.B[(size_t)(cb + lane % 16) * kBigM + rb + lane / 16 + 4 * v];
+        for (int v = 0; v < 4; ++v) acc[v] = D.W[(size_t)(cb + lane % 16) * kBigM + rb + lane / 16 + 4 * v];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
           const int k = 4 * ks + lane / 16;
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pnl[k][rb + lane % 16], -pnl[k][cb + lane % 16], acc, 0, 0, 0);
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) D.B[(size_t)(cb + lane % 16) * kBigM + rb + lane / 16 + 4 * v] = acc[v];
+        for (int v = 0; v < 4; ++v) D.W[(size_t)(cb + lane % 16) * kBigM + rb + lane / 16 + 4 * v] = acc[v];
       }
     __syncthreads();
   }
@@ -2434,7 +2716,7 @@ __global__ __launch_bounds__(256) void k_big_round(const InstDesc* __restrict__ 
   for (int idx = tid; idx < 32 * kBigM; idx += 256) {
     const int k = idx / kBigM, r = idx % kBigM;
     const int c = 16 * (k < 16 ? a : b) + (k & 15);
-    col[k * kBigLd + r] = D.B[(size_t)c * kBigM + r];
+    col[k * kBigLd + r] = D.W[(size_t)c * kBigM + r];
   }
   __syncthreads();
   {
@@ -2547,7 +2829,7 @@ __global__ __launch_bounds__(256) void k_big_round(const InstDesc* __restrict__ 
     for (int idx = tid; idx < 32 * kBigM; idx += 256) {
       const int k = idx / kBigM, r = idx % kBigM;
       const int c = 16 * (k < 16 ? a : b) + (k & 15);
-      D.B[(size_t)c * kBigM + r] = col[k * kBigLd + r];
+      D.W[(size_t)c * kBigM + r] = col[k * kBigLd + r];
     }
     if (tid == 0) atomicAdd(&D.f[1], 1);
   }
@@ -2565,195 +2847,22 @@ __global__ __launch_bounds__(64) void k_big_sweep(const InstDesc* __restrict__ t
     D.f[0] = 1;
   } else if (D.f[2] >= kBigMaxSweeps) {
     D.f[0] = 2;
-    atomicAdd(&D.I->st->unconverged, 1);
   }
   D.f[1] = 0;
 }
 
-// Thread c: lambda_c and U_c = B_c / sigma_c; then wbar = U Lambda^-1 U^T b
-// and one refinement step wbar += U Lambda^-1 U^T (b - A wbar) with the exact A.
-__global__ __launch_bounds__(256) void k_big_eig(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                                 int cls) {
-  __shared__ double bs[kBigM], zs[kBigM], wsh[kBigM];
+// Thread c: lambda_c, the squared norm of column c of L J.
+__global__ __launch_bounds__(256) void k_big_lambda(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
+                                                    int cls) {
   const ClassBatch& cb = hdr->cls[cls];
   if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
   const BigDom D = big_dom(tab, cb, blockIdx.x);
-  const InstDesc& I = *D.I;
-  const int m = I.m, c = threadIdx.x;
-  double* Bc = D.B + (size_t)c * kBigM;
-  double lc = 1.0;
-  if (c < m) {
-    double ss = 0.0;
-    for (int r = 0; r < m; ++r) ss = fma(Bc[r], Bc[r], ss);
-    lc = ss;
-    const double inv = 1.0 / sqrt(ss);
-    for (int r = 0; r < m; ++r) Bc[r] *= inv;
-  }
-  D.v[2 * kBigM + c] = lc;
-  bs[c] = D.v[c];
-  __syncthreads();
-  auto project = [&](const double* rhs) {  // zs = Lambda^-1 U^T rhs
-    double z = 0.0;
-    if (c < m)
-      for (int r = 0; r < m; ++r) z = fma(Bc[r], rhs[r], z);
-    zs[c] = c < m ? z / lc : 0.0;
-    __syncthreads();
-  };
-  auto expand = [&](int r) {  // (U zs)[r]
-    double w = 0.0;
-    if (r < m)
-      for (int k = 0; k < m; ++k) w = fma(D.B[(size_t)k * kBigM + r], zs[k], w);
-    return w;
-  };
-  project(bs);
-  const int r = threadIdx.x;
-  wsh[r] = r < m ? expand(r) : 0.0;
-  __syncthreads();
-  double res = 0.0;
-  if (r < m) {
-    double t = 0.0;
-    for (int j = 0; j < m; ++j) t = fma(D.A[(size_t)j * kBigM + r], wsh[j], t);
-    res = bs[r] - t;
-  }
-  __syncthreads();
-  bs[r] = res;
-  __syncthreads();
-  project(bs);
-  D.v[kBigM + r] = r < m ? wsh[r] + expand(r) : 0.0;
+  const int m = D.I->m, c = threadIdx.x;
   double* dbg = big_dbg(D);
-  if (dbg && c < m) dbg[(size_t)m * m + c] = lc;
-  if (threadIdx.x == 0) {
-    const int sweeps = D.f[2];
-    if (I.dbg_sweeps) I.dbg_sweeps[D.l] = sweeps;
-    atomicAdd(&I.st->sweeps, (unsigned long long)sweeps);
-    atomicAdd(&I.st->solves, 1ull);
-  }
-}
-
-// grid (16, items): 64 x 64 tile (blockIdx.x / 4, blockIdx.x % 4) of T, written
-// over A (row-major); U columns staged 32 at a time.
-__global__ __launch_bounds__(256) void k_big_T(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                               int cls) {
-  __shared__ double Ua[32][64], Ub[32][64];
-  __shared__ double sc[kBigM];
-  const ClassBatch& cb = hdr->cls[cls];
-  if ((int)blockIdx.y >= cb.dom_off[cb.n]) return;
-  const BigDom D = big_dom(tab, cb, blockIdx.y);
-  const int m = D.I->m, tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int i0 = 64 * (blockIdx.x / 4), j0 = 64 * (blockIdx.x % 4);
-  if (i0 >= m || j0 >= m) return;
-  sc[tid] = tid < m ? sqrt((double)(m - 1) / D.v[2 * kBigM + tid]) : 0.0;
-  __syncthreads();
-  double acc[4][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = 0.0;
-  for (int c0 = 0; c0 < m; c0 += 32) {
-    for (int idx = tid; idx < 32 * 64; idx += 256) {
-      const int cc = idx / 64, q = idx % 64, c = c0 + cc;
-      const double* Uc = D.B + (size_t)c * kBigM;
-      Ua[cc][q] = (c < m && i0 + q < m) ? Uc[i0 + q] * sc[c] : 0.0;
-      Ub[cc][q] = (c < m && j0 + q < m) ? Uc[j0 + q] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int cc = 0; cc < 32; ++cc) {
-      double a[4], b[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) a[x] = Ua[cc][ty + 16 * x];
-#pragma unroll
-      for (int y = 0; y < 4; ++y) b[y] = Ub[cc][tx + 16 * y];
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = fma(a[x], b[y], acc[x][y]);
-    }
-    __syncthreads();
-  }
-  double* dbg = big_dbg(D);
-  const double* wbar = D.v + kBigM;
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int i = i0 + ty + 16 * x, j = j0 + tx + 16 * y;
-      if (i < m && j < m) {
-        const double tv = acc[x][y] + wbar[i];
-        D.A[(size_t)i * kBigM + j] = tv;
-        if (dbg) dbg[(size_t)m * m + m + (size_t)i * m + j] = tv;
-      }
-    }
-}
-
-// grid (row tiles, member tiles, items): Z rows q0..q0+63 of the domain (both
-// instants), members j0..j0+63; X' staged 32 members at a time.
-__global__ __launch_bounds__(256) void k_big_update(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                                    int cls) {
-  __shared__ double Xs[64][33], Ts[32][64], xb[64];
-  const ClassBatch& cb = hdr->cls[cls];
-  if ((int)blockIdx.z >= cb.dom_off[cb.n]) return;
-  const BigDom D = big_dom(tab, cb, blockIdx.z);
-  const InstDesc& I = *D.I;
-  const int m = I.m, rows = 2 * D.e, tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int q0 = 64 * blockIdx.x, j0 = 64 * blockIdx.y;
-  if (q0 >= rows || j0 >= m) return;
-  const int cur = I.st->cur;
-  const double* ens = (const double*)I.ens;
-  const size_t slot = (size_t)I.n_act * m;
-  auto row_ptr = [&](int q) {  // ensemble row of the domain's state row q
-    const int inst = q < D.e ? cur : (cur ^ 1);
-    const int act = I.est_act[D.est_off + (q < D.e ? q : q - D.e)];
-    return ens + (size_t)inst * slot + (size_t)act * m;
-  };
-  {
-    const int rr = tid / 4, part = tid % 4, q = q0 + rr;
-    double sum = 0.0;
-    if (q < rows) {
-      const double* x = row_ptr(q);
-      for (int j = part; j < m; j += 4) sum += x[j];
-    }
-    sum = group_sum<4>(sum);
-    if (part == 0) xb[rr] = sum / (double)m;
-  }
-  __syncthreads();
-  double acc[4][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = 0.0;
-  for (int k0 = 0; k0 < m; k0 += 32) {
-    for (int idx = tid; idx < 64 * 32; idx += 256) {
-      const int rr = idx / 32, kk = idx % 32, q = q0 + rr, k = k0 + kk;
-      Xs[rr][kk] = (q < rows && k < m) ? row_ptr(q)[k] - xb[rr] : 0.0;
-    }
-    for (int idx = tid; idx < 32 * 64; idx += 256) {
-      const int kk = idx / 64, cc = idx % 64, k = k0 + kk, j = j0 + cc;
-      Ts[kk][cc] = (k < m && j < m) ? D.A[(size_t)k * kBigM + j] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < 32; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) a[x] = Xs[ty + 16 * x][kk];
-#pragma unroll
-      for (int y = 0; y < 4; ++y) b[y] = Ts[kk][tx + 16 * y];
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = fma(a[x], b[y], acc[x][y]);
-    }
-    __syncthreads();
-  }
-  double* Z = (double*)I.Z + (size_t)2 * D.est_off * m;
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int rr = ty + 16 * x, q = q0 + rr, j = j0 + tx + 16 * y;
-      if (q < rows && j < m) Z[(size_t)q * m + j] = xb[rr] + acc[x][y];
-    }
+  if (!dbg || c >= m) return;
+  double ss = 0.0;
+  for (int r = 0; r < m; ++r) ss = fma(D.W[(size_t)c * kBigM + r], D.W[(size_t)c * kBigM + r], ss);
+  dbg[(size_t)m * m + c] = ss;
 }
 
 // ----------------------------------------------------------------------------
@@ -2903,18 +3012,28 @@ void launch_rows(int cls, int mode, int rows, const InstDesc* tab, BatchHdr* hdr
 
 void launch_big_analysis(int items, int rows_max, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s) {
   if (items <= 0) return;
+  const int cls = kBigClass, nt = (m_max + 15) / 16;
+  hipLaunchKernelGGL(k_big_gram, dim3(nt * (nt + 1) / 2, items), dim3(64 * kGramWaves), 0, s, tab, hdr, cls);
+  for (int st = 0; st < kBigStages; ++st) {
+    hipLaunchKernelGGL(k_big_mul<0>, dim3(16 * nt, items), dim3(256), 0, s, tab, hdr, cls, st);
+    hipLaunchKernelGGL(k_big_mul<1>, dim3(16 * nt, items), dim3(256), 0, s, tab, hdr, cls, st);
+    hipLaunchKernelGGL(k_big_mul<2>, dim3(16 * nt, items, st == 0 ? 1 : 2), dim3(256), 0, s, tab, hdr, cls, st);
+    hipLaunchKernelGGL(k_big_mul<4>, dim3(16 * nt, items), dim3(256), 0, s, tab, hdr, cls, st);
+  }
+  hipLaunchKernelGGL(k_big_slow, dim3(items), dim3(256), 0, s, tab, hdr, cls);
+  hipLaunchKernelGGL(k_big_wbar, dim3(items), dim3(1024), 0, s, tab, hdr, cls);
+  hipLaunchKernelGGL(k_big_update, dim3((rows_max + 15) / 16, (nt + 3) / 4, items), dim3(256), 0, s, tab, hdr, cls);
+}
+
+void launch_big_lambda(int items, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s) {
   const int cls = kBigClass, nb = 2 * ((m_max + 31) / 32);
-  hipLaunchKernelGGL(k_big_gram, dim3(10, items), dim3(256), 0, s, tab, hdr, cls);
   hipLaunchKernelGGL(k_big_chol, dim3(items), dim3(64 * kBigCholWaves), 0, s, tab, hdr, cls);
   for (int sw = 0; sw < kBigMaxSweeps; ++sw) {
     for (int r = 0; r < nb - 1; ++r)
       hipLaunchKernelGGL(k_big_round, dim3(nb / 2, items), dim3(256), 0, s, tab, hdr, cls, nb, r);
     hipLaunchKernelGGL(k_big_sweep, dim3((items + 63) / 64), dim3(64), 0, s, tab, hdr, cls);
   }
-  hipLaunchKernelGGL(k_big_eig, dim3(items), dim3(256), 0, s, tab, hdr, cls);
-  hipLaunchKernelGGL(k_big_T, dim3(16, items), dim3(256), 0, s, tab, hdr, cls);
-  hipLaunchKernelGGL(k_big_update, dim3((rows_max + 63) / 64, (m_max + 63) / 64, items), dim3(256), 0, s, tab, hdr,
-                     cls);
+  hipLaunchKernelGGL(k_big_lambda, dim3(items), dim3(256), 0, s, tab, hdr, cls);
 }
 
 void launch_analysis(int cls, int grid, const InstDesc* tab, BatchHdr* hdr, hipStream_t s, int fair) {

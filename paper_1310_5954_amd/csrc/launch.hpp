@@ -52,5 +52,8 @@ void launch_noalloc_setup(const InstDesc* src, const BatchHdr* src_hdr, unsigned
 // the domains' scratch (rows_max: most state rows of a domain, m_max: most
 // members of an instance in the batch).
 void launch_big_analysis(int items, int rows_max, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
+// Eigenvalues of every domain of a debug instance of that class, from the A its
+// last analysis left (over the scratch of the stages).
+void launch_big_lambda(int items, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
 
 }  // namespace letkf

@@ -172,11 +172,11 @@ Layout make_layout(const Problem& P) {
   } else {
     L.pist_r = L.pist_c = 0;
   }
-  L.bigA = L.bigB = L.bigv = L.bigf = 0;
+  L.bigA = L.bigW = L.bigv = L.bigf = 0;
   if (padded_members(P.m) > 128) {
     const size_t mm = 256 * 256;
     L.bigA = take((size_t)P.n_dom * mm * 8);
-    L.bigB = take((size_t)P.n_dom * mm * 8);
+    L.bigW = take((size_t)P.n_dom * 5 * mm * 8);
     L.bigv = take((size_t)P.n_dom * 5 * 256 * 8);
     L.bigf = take((size_t)P.n_dom * 4 * 4);
   }
@@ -435,7 +435,7 @@ int upload_instance(const Problem& P, const Layout& L, char* ws, const double* X
   }
   if (L.bigA) {
     D.bigA = (double*)(ws + L.bigA);
-    D.bigB = (double*)(ws + L.bigB);
+    D.bigW = (double*)(ws + L.bigW);
     D.bigv = (double*)(ws + L.bigv);
     D.bigf = (int32_t*)(ws + L.bigf);
   }
@@ -1051,6 +1051,7 @@ int letkf_debug_domain(letkf_handle* h, int32_t domain, double* C_out, double* l
   const size_t m = h->P.m, per = 2 * m * m + m + kDbgTail;
   std::vector<double> buf(per);
   int32_t sw = 0;
+  if (lam_out && h->cls == letkf::kBigClass) letkf::launch_big_lambda(h->P.n_dom, h->P.m, dev_desc(h), dev_hdr(h), s);
   LETKF_HIP(hipMemcpyAsync(buf.data(), h->ws + h->L.dbg + domain * per * 8, per * 8, hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipMemcpyAsync(&sw, h->ws + h->L.dbg_sweeps + domain * 4, 4, hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipStreamSynchronize(s));
