@@ -79,18 +79,22 @@ def unique_bytes(case, esize: int) -> int:
     return int(p * m * esize + n * m * esize + 16 * p + zrows * m * esize)
 
 
-def analysis_flops(m: int, dmap, sweeps_total: int, solves: int, frames: int) -> float:
+def analysis_flops(m: int, dmap, sweeps_total: int, solves: int, frames: int, poly: bool = False) -> float:
     """Algorithmic FP64 flops of the domain-analysis kernel over `frames`
     launches.  Per domain with p_l slopes and n_l state rows:
       C (symmetric) m(m+1) p_l, r-scaling m p_l, b 2 m p_l,
       Jacobi per sweep: column norms 2m^2 + one dot per pair 2m * m(m-1)/2,
       rotations 6m per pair * m(m-1)/2 in every sweep but the last (check) one,
-      lambda/U 3m^2, wbar 4m^2, W 2m^3, update 2 n_l m^2 + 2 n_l m."""
+      lambda/U 3m^2, wbar 4m^2, W 2m^3, update 2 n_l m^2 + 2 n_l m.
+    poly: the FP64 and FP32 paths, whose A^(-1/2) takes sweeps_total matrix
+    products of 2m^3 instead."""
     e = np.diff(dmap.est_ptr).astype(float)
     s = np.diff(dmap.obs_ptr).astype(float)
     p_l, n_l = 2 * s, 2 * e
     L = dmap.n_domains
-    fixed = np.sum(m * (m + 1) * p_l + 3 * m * p_l + 2 * n_l * m * m + 2 * n_l * m) + L * (2 * m ** 3 + 7 * m * m)
+    fixed = np.sum(m * (m + 1) * p_l + 3 * m * p_l + 2 * n_l * m * m + 2 * n_l * m) + L * ((0 if poly else 2 * m ** 3) + 7 * m * m)
+    if poly:
+        return frames * fixed + sweeps_total * 2 * m ** 3
     dots = 2 * m * m + m * m * (m - 1)
     rots = 3 * m * m * (m - 1)
     return frames * fixed + sweeps_total * dots + (sweeps_total - solves) * rots
@@ -824,7 +828,7 @@ def main() -> int:
         """Algorithmic FP64-dominated work of one analysis launch over its
         HIP-event duration; HBM traffic from the committed counter summary."""
         ana_ms = run["kernel_ms"][1]
-        flops = analysis_flops(case.m, case.dmap, run["sweeps"], run["solves"], K) / K
+        flops = analysis_flops(case.m, case.dmap, run["sweeps"], run["solves"], K, path_name != "bf16") / K
         achieved = flops / (ana_ms * 1e-3) / 1e12
         es = 8 if path_name == "fp64" else 4
         traffic = measured_traffic(TRAFFIC_FILES[path_name], kernel_hash(), run["tuning"]) if args.workload == 84 else None
@@ -856,7 +860,7 @@ def main() -> int:
     print(f"[bench] plain fp64, graph replay: {graph['fps']:.1f} frames/s p50 {graph['p50_us']:.0f} us "
           f"p99 {graph['p99_us']:.0f} us", file=sys.stderr, flush=True)
     rf64 = roofline_of(plain, "fp64")
-    rf64["kernel"] = f"k_analysis<FP64, m={case.m}> (vector FP64: Cholesky + one-sided Jacobi dominate)"
+    rf64["kernel"] = f"k_analysis_poly<FP64, m={case.m}> (FP64 MFMA: the polynomial stages of A^(-1/2) dominate)"
     plain_out = dict(frames_per_s=round(plain["fps"], 2), p50_us=round(plain["p50_us"], 1),
                      p99_us=round(plain["p99_us"], 1), latency_frames=NL,
                      kernel_ms=dict(slopes=round(plain["kernel_ms"][0], 4), analysis=round(plain["kernel_ms"][1], 4),

@@ -76,16 +76,21 @@ extern "C" {
 #define LETKF_ESTATE   (-6)  /* call not valid in the handle's state (e.g. no debug buffers) */
 
 /* ---- precision paths --------------------------------------------------
- * The eigensolve (Cholesky, one-sided Jacobi rotations), wbar and W are FP64
- * on every path (the rotations unless LETKF_FLAG_FP32_ROTATIONS is given);
- * the paths differ in the storage of the ensemble and slopes
- * and in the two dense contractions, C = Y'^T diag(r) Y' and X' T.
- * LETKF_FP64: ensemble, slopes and both contractions in FP64 (C on FP64
- *             MFMA for m <= 64, FP64 FMA above); Jacobi tolerance 32 M eps.
+ * W = [(m-1) A^-1]^(1/2) and wbar are FP64 on every path; the paths differ in
+ * the storage of the ensemble and slopes and in the two dense contractions,
+ * C = Y'^T diag(r) Y' and X' T.
+ * On LETKF_FP64, and LETKF_FP32 with m <= 64, A^(-1/2) comes from minimax
+ * polynomial stages (matrix products on FP64 MFMA) chosen by a bound of A's
+ * condition number, exact to rounding.  LETKF_BF16, LETKF_FP32 with m > 64 and
+ * instances with m <= 128 and obs_instant 1 solve the eigenproblem (Cholesky,
+ * one-sided Jacobi rotations in FP64 unless LETKF_FLAG_FP32_ROTATIONS is given)
+ * to a path's tolerance.
+ * LETKF_FP64: ensemble, slopes and both contractions in FP64 (FP64 MFMA; the
+ *             Jacobi's C on FP64 FMA for m > 64, its tolerance 32 M eps).
  * LETKF_FP32: FP32 ensemble and slopes; C on FP32 MFMA (v_mfma_f32_16x16x4f32),
  *             each 4-observation k-step's FP32 product added into an FP64
- *             accumulator; X' T on FP32 MFMA with FP32 accumulation; Jacobi
- *             tolerance 1e-6 and two refinement steps of wbar.
+ *             accumulator; X' T on FP32 MFMA with FP32 accumulation (Jacobi
+ *             tolerance 1e-6 and two refinement steps of wbar).
  * LETKF_BF16: FP32 ensemble and slopes; C on BF16 MFMA from split operands
  *             (sqrt(r) Y' = hi + lo, both BF16; hi hi^T + hi lo^T + lo hi^T)
  *             with FP32 accumulation; X' T on BF16 MFMA with BF16 X' and a
@@ -227,9 +232,10 @@ int letkf_set_state(letkf_handle* h, const double* X, uint64_t frame, void* stre
 /* Per-domain intermediates of the last analysis (needs LETKF_FLAG_DEBUG):
  * C_out [m x m] (C = Y'^T diag(r) Y', no (m-1)/rho I), lam_out [m]
  * (ascending eigenvalues of A), T_out [m x m] (W + wbar 1^T), sweeps_out
- * (Jacobi sweeps used; m > 128: matrix products of the polynomial stages that
- * form A^(-1/2)), cycles_out [5] (shader-clock cycles spent by the
- * domain's workgroup in: gather + C/b, Cholesky, Jacobi, wbar/W/T, update).
+ * (Jacobi sweeps used; matrix products, where A^(-1/2) comes from polynomial
+ * stages), cycles_out [5] (shader-clock cycles spent by the domain's workgroup
+ * in: gather + C/b, Cholesky, Jacobi, wbar/W/T, update; the second and third
+ * are A^2 with its norm and the stages on those paths).
  * Any output may be NULL.  Waits for the stream. */
 int letkf_debug_domain(letkf_handle* h, int32_t domain, double* C_out, double* lam_out,
                        double* T_out, int32_t* sweeps_out, double* cycles_out, void* stream);
@@ -247,13 +253,13 @@ int letkf_debug_placement(letkf_handle* h, int32_t domain, uint32_t* hw_id_out, 
 
 /* Shader-clock cycles of the sub-steps of the wbar/W/T phase of a domain in
  * the last analysis (needs LETKF_FLAG_DEBUG; m <= 128): cycles_out [4] =
- * {lambda and U from the columns of L J, wbar = U Lambda^-1 U^T b, its
+ * {lambda and U from the columns of L J (A^(-1/2) to LDS), wbar, its
  * refinement, T}.  Waits for the stream. */
 int letkf_debug_substeps(letkf_handle* h, int32_t domain, double* cycles_out, void* stream);
 
 /* Number of domains of the last analysis whose eigensolver hit the sweep cap, or
- * (m > 128) whose condition number passed the polynomial stages' range of 1e14
- * (0 when all converged); waits for the stream. */
+ * whose condition number passed the polynomial stages' range (4e15, 1e14 for
+ * m > 128; 0 when all converged); waits for the stream. */
 int letkf_unconverged_domains(letkf_handle* h, int32_t* count, void* stream);
 
 /* The means the last plain-path frame wrote (host [n_act] each, either may
@@ -326,8 +332,8 @@ int letkf_autotune(letkf_handle* h, int32_t reps, letkf_tuning* out, void* strea
  * LETKF_EINVAL for out-of-range fields. */
 int letkf_set_tuning(letkf_handle* h, const letkf_tuning* t, void* stream);
 
-/* Totals since create (or set_state): Jacobi sweeps (m > 128: matrix products of
- * the polynomial stages) over all domain solves,
+/* Totals since create (or set_state): Jacobi sweeps (or the matrix products of
+ * the polynomial stages, as in letkf_debug_domain) over all domain solves,
  * and the number of domain solves.  Waits for the stream. */
 int letkf_sweep_stats(letkf_handle* h, uint64_t* sweeps, uint64_t* domain_solves, void* stream);
 

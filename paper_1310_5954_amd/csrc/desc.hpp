@@ -13,6 +13,8 @@
 namespace letkf {
 
 constexpr int kMaxBatch = 64;   // frames per batch
+constexpr int kParkDoubles = 128 * 112;  // 64 < m <= 128, poly: a parking slot (isqrt_stages)
+constexpr int kParkSlots = 256; // most workgroups of such an analysis launch, and parking slots of an instance
 // classes 0..15: 4 padded sizes (16, 32, 64, 128) x 4 arithmetic variants
 // (index variant x 4 + size): FP64, FP32, BF16, and BF16 with the Jacobi
 // rotations in FP32 (LETKF_FLAG_FP32_ROTATIONS); class 16: 129..256 members,
@@ -23,9 +25,9 @@ constexpr int kBigClass = 4 * kVariants;
 
 struct InstState {           // mutated on the device by the forecast kernel
   int32_t cur;               // ring slot holding phi_k (the other holds phi_{k-1})
-  int32_t unconverged;       // domains that hit the Jacobi sweep cap in the last analysis
+  int32_t unconverged;       // domains of the last analysis that hit the Jacobi sweep cap or passed the stages' condition range
   uint64_t frame;            // forecasts done so far (Philox counter word 2..3)
-  unsigned long long sweeps; // Jacobi sweeps summed over every domain solve
+  unsigned long long sweeps; // Jacobi sweeps (poly: matrix products of the stages) summed over every domain solve
   unsigned long long solves; // domain solves
 };
 
@@ -33,7 +35,7 @@ struct InstDesc {
   int32_t n_act, n_sub, m, n_dom;
   int32_t prec, flags, zrows, nnz;
   int32_t obs_inst;          // ring slot offset of the observed instant: 0 = phi_k, 1 = phi_{k-1}
-  int32_t pad0;
+  int32_t poly;              // 1: k_analysis_poly analyses the instance, 0: k_analysis (uses_poly)
   double sigma_v;
   double a_diag;             // (m-1)/rho
   uint64_t seed;
@@ -66,8 +68,9 @@ struct InstDesc {
   double* bigW;              // m > 128: [n_dom][5][256][256] M, M^2, P and two Z of the stages (column-major)
   double* bigv;              // m > 128: [n_dom][5][256] b, wbar, spare, partial sums of |A^2|_F^2, spare
   int32_t* bigf;             // m > 128: [n_dom][4] debug Jacobi: converged, rounds that rotated, sweeps; table row of the stages
-  uint32_t* dom_sweeps;      // [n_dom] Jacobi sweeps of each domain, summed over every analysis
+  uint32_t* dom_sweeps;      // [n_dom] Jacobi sweeps (poly: products) of each domain, summed over every analysis
   double* Ascr;              // FP64, m <= 128: [n_dom][m(m+1)/2] each domain's A (lower triangle packed by rows), for refining wbar
+  double* park;              // poly, 64 < m <= 128: [min(n_dom, kParkSlots)][kParkDoubles] a workgroup's Z between its stages
   double* dbg;               // [n_dom][2*m*m + m] C, lambda, T (NULL unless debug)
   int32_t* dbg_sweeps;       // [n_dom]
   InstState* st;
@@ -83,7 +86,7 @@ struct ClassBatch {
   int32_t slope_off[kMaxBatch + 1];
   int32_t dom_off[kMaxBatch + 1];
   uint32_t next;                  // analysis work counter: items claimed past the first grid (k_slopes zeroes it)
-  uint32_t pad;
+  uint32_t next_poly;             // the same for k_analysis_poly
 };
 
 struct BatchHdr {
@@ -110,6 +113,23 @@ constexpr int kDbgTail = 16;
 // path with FP32 rotations (fp32_rot: LETKF_FLAG_FP32_ROTATIONS, validated to
 // come with LETKF_BF16).
 inline int variant_of(int prec, bool fp32_rot) { return fp32_rot ? 3 : prec; }
+
+// Which analysis kernel serves an instance (m <= 128): A^(-1/2) by polynomial
+// stages (k_analysis_poly) or through the Jacobi eigensolver (k_analysis).  The
+// stages agree with the eigensolver to rounding and take 0.47 of its launch time
+// in FP64 at 84 x 84, m = 64 (134 against 286 us), so they serve every instance
+// whose trajectory a change of rounding leaves alone.  Three kinds do not.  The
+// BF16 paths round X' to BF16 every frame, so that two solvers agreeing to 1e-7
+// flip different roundings and stand 1e-3 apart after four to eight frames.  On
+// the FP32 path the rounding of C, amplified by kappa(A), does the same at a
+// smaller scale: 1e-6 to 1e-5 after 16 frames for m <= 64, but 4e-5 after two for
+// m > 64.  A filter that observes the previous instant (H = [0 D]) is unstable
+// on window maps (a CPU replay of 33 x 33 grows a perturbation 7 times a frame).
+// Those keep the solver, and so the trajectories, they have had.
+inline bool uses_poly(int prec, int m, int obs_instant) {
+  return obs_instant == 0 && (prec == 0 || (prec == 1 && m <= 64));
+}
+constexpr int kKindJacobi = 1, kKindPoly = 2;  // kinds of instances in a launch
 
 inline int class_of(int padded_m, int prec, bool fp32_rot) {
   if (padded_m > 128) return kBigClass;  // validated to be FP64

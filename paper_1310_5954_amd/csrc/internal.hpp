@@ -29,7 +29,7 @@ struct Layout {
   size_t a1, a2, rowptr, col, val, dom, order, est, obs_row, obs_r, obs_sr, mptr, mrow, mw, mdom, pist_op;
   size_t pist_r, pist_c, pist_ptr, pist_row, pist_coef;
   size_t bigA, bigW, bigv, bigf;   // m > 128 only
-  size_t dom_sweeps, Ascr, dbg, dbg_sweeps;
+  size_t dom_sweeps, Ascr, park, dbg, dbg_sweeps;
   size_t static_begin, static_end;  // [a1, end of tables) uploaded at create
   size_t total;
 };
@@ -106,6 +106,7 @@ struct letkf_handle {
   int device = 0;
   int mpad = 16;
   int cls = 0;
+  int kinds() const { return desc.poly ? letkf::kKindPoly : letkf::kKindJacobi; }
   double* h_y = nullptr;       // pinned staging
   double* h_out = nullptr;     // pinned staging of the output means
   hipEvent_t y_free = nullptr; // last H2D of h_y completed

@@ -5,8 +5,10 @@
 //   k_rows      a1/a2/a8-merge: weighted merge of the per-domain analysis
 //               rows into the ensemble, optionally fused with the AR forecast
 //               (Philox4x32-10 + Box-Muller model noise) and the output means.
-//   k_analysis  a4-a8: one workgroup per domain: gather, C and b, FP64
-//               one-sided Jacobi eigensolver in LDS, wbar, W, T, update.
+//   k_analysis_poly  a4-a8: one workgroup per domain: gather, C and b, A^(-1/2)
+//               by polynomial stages on the FP64 matrix cores, wbar, T, update.
+//   k_analysis  the same with an FP64 one-sided Jacobi eigensolver in LDS, for
+//               the instances the stages do not serve (InstDesc::poly).
 //
 // All kernels walk the entries of one batch class (same padded ensemble size
 // and storage precision) so that frames of several instances share a launch.
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(256) void k_slopes(const InstDesc* __restrict__ tab
   ClassBatch& cb = hdr->cls[cls];
   if (blockIdx.x == 0) {
     if ((int)threadIdx.x < cb.n) tab[cb.inst[threadIdx.x]].st->unconverged = 0;
-    if (threadIdx.x == 0) cb.next = 0;  // the analysis launch that follows claims items from zero
+    if (threadIdx.x == 0) cb.next = cb.next_poly = 0;  // the analysis launch that follows claims items from zero
   }
   const int j = threadIdx.x % MP;
   const int total = cb.slope_off[cb.n];
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(64) void k_advance(const InstDesc* __restrict__ tab
 // ----------------------------------------------------------------------------
 // a4-a8: per-domain analysis, one 256-thread workgroup (4 wavefronts) per domain.
 //
-// P selects the contraction path: 0 = FP64 vector FMA, 1 = FP32 MFMA
+// P selects the contraction path: 0 = FP64, 1 = FP32 MFMA
 // (v_mfma_f32_16x16x4f32), 2 = BF16 MFMA (v_mfma_f32_16x16x32_bf16) with FP32
 // accumulation, 3 = the BF16 path with its Jacobi rotations in FP32 (an
 // opt-in variant, LETKF_FLAG_FP32_ROTATIONS).  The eigensolve, wbar and W are
@@ -332,6 +334,7 @@ __global__ __launch_bounds__(64) void k_advance(const InstDesc* __restrict__ tab
 // ----------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // The thread index as a value the compiler may not move: every phase of the
@@ -345,8 +348,32 @@ __device__ __forceinline__ int phase_tid() {
   return t;
 }
 
-template <int M> struct AnaCfg {
-  static constexpr int NT = 256;
+// What the gathers and updates take from a configuration of M padded members and
+// NT_ threads.
+template <int M_, int NT_> struct StageCfg {
+  static constexpr int M = M_, NT = NT_, NW = NT / 64;
+  // the products that form C: the wavefronts as a WR x WC grid, each with
+  // TR x TC tiles of 16 x 16 (one wavefront only at M = 16)
+  static constexpr int TILES = M / 16;
+  static constexpr int WC = TILES >= 2 ? 2 : 1, WR = TILES >= 2 ? NW / 2 : 1;
+  static constexpr int TR = TILES / WR, TC = TILES / WC;
+  static constexpr int KCD = 16, LDKD = KCD + 1;   // FP64: observations per chunk; an odd row stride puts the 16 rows of an operand load in 16 bank pairs
+  static constexpr int KCF = M <= 64 ? 32 : 16;    // FP32: observations per staged chunk
+  // row stride (floats) of the transposed chunk: 2 mod 32, so that the 16 rows
+  // and 2 k-offsets of a 32-lane operand load fall in 32 different banks
+  static constexpr int LDKF = KCF + 2;
+  static constexpr int KCB = 32;                   // BF16: observations per chunk (one k-step)
+  static constexpr int LDKB = KCB + 8;             // row stride (bf16) of the transposed chunk
+  static constexpr int KR = M <= 64 ? 32 : 16;     // update: state rows per chunk (16-row tiles)
+};
+
+// k_analysis: 256 threads.
+template <int M> struct AnaCfg : StageCfg<M, 256> {
+  using StageCfg<M, 256>::NT;
+  using StageCfg<M, 256>::KCF;
+  using StageCfg<M, 256>::LDKF;
+  using StageCfg<M, 256>::LDKB;
+  using StageCfg<M, 256>::KR;
   static constexpr int KC = 16;                    // FP64 path: rows per staged chunk (keeps m = 64 at 3 workgroups/CU)
   static constexpr int TM = M / 16;                // FP64 path: TM x TM outputs per thread
   static constexpr int TPP = (2 * NT / M) < M ? (2 * NT / M) : M;  // threads per Jacobi pair
@@ -357,14 +384,6 @@ template <int M> struct AnaCfg {
   static constexpr int ACTIVE = (M / 2) * TPP;
   static constexpr int RPT = M / TPP;              // rows per thread in a Jacobi step
   static constexpr int MAX_SWEEPS = 40;
-  // MFMA paths
-  static constexpr int KCF = M <= 64 ? 32 : 16;    // FP32: observations per staged chunk
-  // row stride (floats) of the transposed chunk: 2 mod 32, so that the 16 rows
-  // and 2 k-offsets of a 32-lane operand load fall in 32 different banks
-  static constexpr int LDKF = KCF + 2;
-  static constexpr int KCB = 32;                   // BF16: observations per chunk (one k-step)
-  static constexpr int LDKB = KCB + 8;             // row stride (bf16) of the transposed chunk
-  static constexpr int KR = M <= 64 ? 32 : 16;     // update: state rows per chunk (16-row tiles)
   static constexpr size_t STAGE_BYTES = [] {
     size_t a = (size_t)KC * M * 8, b = (size_t)M * LDKF * 4, c = (size_t)M * LDKB * 2 * 2, d = (size_t)KR * M * 4;
     size_t x = a > b ? a : b;
@@ -375,6 +394,8 @@ template <int M> struct AnaCfg {
 
 template <int M> struct AnaSmem {
   using C = AnaCfg<M>;
+  static constexpr int LDA = C::LDB;                  // the gathers' stride of A
+  static __device__ double pad(double) { return 1.0; }  // diagonal of A past m
   double Bm[M * C::LDB];                              // A, then U, then T (row-major)
   alignas(16) unsigned char stage[C::STAGE_BYTES];    // chunk staging (phase-dependent type)
   double rc[32], dc[32];
@@ -385,124 +406,90 @@ template <int M> struct AnaSmem {
   __device__ double* red() { return (double*)stage; }  // NT partial sums, aliases the staging area
 };
 
+// k_analysis_poly: a wavefront per 16 columns of the M x M matrices, at least four.
+template <int M> struct PolyCfg : StageCfg<M, M <= 64 ? 256 : 512> {
+  using B = StageCfg<M, M <= 64 ? 256 : 512>;
+  static constexpr int LDB = M + (M <= 64 ? 8 : 4);  // column stride of Z and T in LDS
+  static constexpr int LDA = M + 2;                  // of A and the stages' left factors
+  static constexpr int KEEP = M <= 32 ? M / 16 : M == 64 ? 2 : 1;  // tiles of Z that stay in registers (isqrt_stages)
+  static constexpr size_t STAGE_BYTES = [] {
+    size_t x = 0;
+    for (size_t v : {(size_t)M * B::LDKD * 8, (size_t)M * B::LDKF * 4, (size_t)16 * (M + 1) * 8, (size_t)B::KR * (M + 1) * 4,
+                     (size_t)B::NT * 8, M == 64 ? (size_t)B::NT * 8 * 4 * 2 - (size_t)M * (LDB - LDA) * 8 : 0})  // parked Z, behind A
+      x = v > x ? v : x;
+    return (x + 15) & ~size_t(15);
+  }();
+};
+template <int M> struct PolySmem {
+  using C = PolyCfg<M>;
+  static constexpr int LDA = C::LDA;
+  // past m the diagonal of A is its smallest eigenvalue, which leaves the spectrum's bounds alone
+  static __device__ double pad(double a_diag) { return a_diag; }
+  alignas(16) double Bm[M * C::LDB];                  // A, the stages' left factors, Z, then T (row-major)
+  alignas(16) unsigned char stage[C::STAGE_BYTES];    // chunk staging (phase-dependent type)
+  double rc[32], dc[32];
+  double bvec[M], zv[M], wbar[M], pcol[M];
+  __device__ double* red() { return (double*)stage; }  // NT partial sums, aliases the staging area
+};
+
 // The entry (i, j) of A = (m-1)/rho I + C into LDS at (i, j) only: for the FP64
 // gather, whose 16 tiles cover both halves and compute C_ij and C_ji with the
 // same products summed in the same order (bitwise equal), so every entry is
 // written once and along rows (the mirrored write went down a column, an 8-way
 // bank conflict).
-template <int M>
-__device__ __forceinline__ void put_A_own(AnaSmem<M>& sm, int i, int j, int m, double c, double a_diag, double* dbg) {
+template <typename SM>
+__device__ __forceinline__ void put_A_own(SM& sm, int i, int j, int m, double c, double a_diag, double* dbg) {
   double v = c;
-  if (i >= m || j >= m) v = (i == j) ? 1.0 : 0.0;
+  if (i >= m || j >= m) v = (i == j) ? SM::pad(a_diag) : 0.0;
   else {
     if (dbg) dbg[i * m + j] = c;
     if (i == j) v += a_diag;
   }
-  sm.Bm[i * AnaCfg<M>::LDB + j] = v;
+  sm.Bm[i * SM::LDA + j] = v;
 }
 
 // Writes the entry (i, j) of A = (m-1)/rho I + C into LDS (symmetrically: only
-// the producer of i <= j writes, to both halves), padded members -> identity.
-template <int M>
-__device__ __forceinline__ void put_A(AnaSmem<M>& sm, int i, int j, int m, double c, double a_diag, double* dbg) {
+// the producer of i <= j writes, to both halves), padded members -> SM::pad on
+// the diagonal.
+template <typename SM>
+__device__ __forceinline__ void put_A(SM& sm, int i, int j, int m, double c, double a_diag, double* dbg) {
   if (i > j) return;
   double v = c;
-  if (i >= m || j >= m) v = (i == j) ? 1.0 : 0.0;
+  if (i >= m || j >= m) v = (i == j) ? SM::pad(a_diag) : 0.0;
   else {
     if (dbg) { dbg[i * m + j] = c; dbg[j * m + i] = c; }
     if (i == j) v += a_diag;
   }
-  sm.Bm[j * AnaCfg<M>::LDB + i] = v;
-  sm.Bm[i * AnaCfg<M>::LDB + j] = v;
+  sm.Bm[j * SM::LDA + i] = v;
+  sm.Bm[i * SM::LDA + j] = v;
 }
 
-// ---- a4/a5 on the FP64 path: C = Y'^T diag(r) Y', b = Y'^T diag(r) d -------
-template <int M>
-__device__ void gather_C_fp64(AnaSmem<M>& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
-  using C = AnaCfg<M>;
-  constexpr int NT = C::NT, KC = C::KC, TM = C::TM;
-  double* Xc = (double*)sm.stage;
-  const int m = I.m, tid = phase_tid(), ti = tid / 16, tj = tid % 16;
-  double acc[TM][TM];
-#pragma unroll
-  for (int x = 0; x < TM; ++x)
-#pragma unroll
-    for (int y = 0; y < TM; ++y) acc[x][y] = 0.0;
-  double bacc = 0.0;
-  const double* Yp = (const double*)I.Yp;
-  const int nobs = 2 * s;
-  for (int q0 = 0; q0 < nobs; q0 += KC) {
-    const int kc = min(KC, nobs - q0);
-    for (int idx = tid; idx < KC * M; idx += NT) {
-      const int qq = idx / M, j = idx % M;
-      double v = 0.0;
-      if (qq < kc && j < m) v = Yp[(size_t)I.obs_row[2 * obs_off + q0 + qq] * m + j];
-      Xc[idx] = v;
-    }
-    if (tid < KC) {
-      double r = 0.0, dd = 0.0;
-      if (tid < kc) {
-        r = I.obs_r[2 * obs_off + q0 + tid];
-        dd = I.d[I.obs_row[2 * obs_off + q0 + tid]];
-      }
-      sm.rc[tid] = r;
-      sm.dc[tid] = dd;
-    }
-    __syncthreads();
-    for (int qq = 0; qq < kc; ++qq) {
-      const double r = sm.rc[qq];
-      double yi[TM], yj[TM];
-#pragma unroll
-      for (int x = 0; x < TM; ++x) {
-        yi[x] = r * Xc[qq * M + ti + 16 * x];
-        yj[x] = Xc[qq * M + tj + 16 * x];
-      }
-#pragma unroll
-      for (int x = 0; x < TM; ++x)
-#pragma unroll
-        for (int y = 0; y < TM; ++y) acc[x][y] += yi[x] * yj[y];
-    }
-    if (tid < M)
-      for (int qq = 0; qq < kc; ++qq) bacc += sm.rc[qq] * sm.dc[qq] * Xc[qq * M + tid];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int x = 0; x < TM; ++x)
-#pragma unroll
-    for (int y = 0; y < TM; ++y) put_A<M>(sm, ti + 16 * x, tj + 16 * y, m, acc[x][y], I.a_diag, dbg);
-  if (tid < M) sm.bvec[tid] = tid < m ? bacc : 0.0;
-  __syncthreads();
-}
-
-// ---- a4/a5 on the FP64 path with FP64 MFMA (M <= 64) -------------------------
+// ---- a4/a5 on the FP64 path: C = Y'^T diag(r) Y', b = Y'^T diag(r) d --------
 // As on the MFMA paths below, a chunk of KCH observations is staged transposed
-// as At[j][k] = sqrt(r_k) Y'[k][j] (FP64), and wave w owns a WT x WT block of
+// as At[j][k] = sqrt(r_k) Y'[k][j] (FP64), and wave w owns a TR x TC block of
 // 16 x 16 tiles of C, accumulated by v_mfma_f64_16x16x4f64 in FP64 registers.
 // A single wavefront per SIMD issues a VALU instruction only every ~8.5
 // cycles, so the matrix core reaches the FP64 rate that the FMA loop cannot.
-// (M = 128 would need 64 accumulators per lane and keeps the FMA loop.)
 // Lane layout of v_mfma_f64_16x16x4f64 (measured on gfx950): A[i][k] in lane
 // i + 16 k, B[k][j] in lane j + 16 k, and result register v of lane l holds
 // D[l / 16 + 4 v][l % 16] (rows interleaved, unlike the FP32 16x16x4 form).
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <int M>
-__device__ void gather_C_fp64_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
-  using C = AnaCfg<M>;
-  constexpr int NT = C::NT, KCH = 16, LDK = KCH + 1;  // LDK odd: the 16 rows of an operand load in 16 bank pairs
-  constexpr int TILES = M / 16;
-  constexpr int WT = TILES >= 2 ? TILES / 2 : 1;
-  static_assert(M <= 64 && (size_t)M * LDK * 8 <= C::STAGE_BYTES, "staging");
+template <typename SM>
+__device__ __forceinline__ void gather_C_fp64_mfma(SM& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
+  using C = typename SM::C;
+  constexpr int M = C::M;
+  constexpr int NT = C::NT, KCH = C::KCD, LDK = C::LDKD;
+  constexpr int TILES = C::TILES, TR = C::TR, TC = C::TC;
   double* At = (double*)sm.stage;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
   const bool wave_on = TILES >= 2 || w == 0;
-  const int tr0 = TILES >= 2 ? (w / 2) * WT : 0;
-  const int tc0 = TILES >= 2 ? (w % 2) * WT : 0;
-  f64x4 acc[WT][WT];
+  const int tr0 = TILES >= 2 ? (w / 2) * TR : 0;
+  const int tc0 = TILES >= 2 ? (w % 2) * TC : 0;
+  f64x4 acc[TR][TC];
 #pragma unroll
-  for (int a = 0; a < WT; ++a)
+  for (int a = 0; a < TR; ++a)
 #pragma unroll
-    for (int b = 0; b < WT; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int b = 0; b < TC; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
   double bpart = 0.0;
   const double* Yp = (const double*)I.Yp;
   const int nobs = 2 * s;
@@ -512,7 +499,7 @@ __device__ void gather_C_fp64_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_of
   // issues only the loads of Y' rows, three chunks of them in flight: with the
   // index, r and d loads in the loop, each chunk's loads waited on the
   // previous chunk's and a chunk spent ~5k cycles for ~1k of products.
-  constexpr int SEG = (M * C::LDB * 8 / 20) / KCH * KCH;
+  constexpr int SEG = (M * SM::LDA * 8 / 20) / KCH * KCH;
   static_assert(SEG >= KCH && SEG % 2 == 0 && (size_t)SEG * (4 + 8 + 8) <= sizeof(sm.Bm), "observation table");
   int* rowT = reinterpret_cast<int*>(sm.Bm);
   double* sT = sm.Bm + SEG / 2;
@@ -564,16 +551,15 @@ __device__ void gather_C_fp64_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_of
       if (wave_on) {
 #pragma unroll
         for (int ks = 0; ks < KCH / 4; ++ks) {
-          double av[WT], bv[WT];
+          double av[TR], bv[TC];
 #pragma unroll
-          for (int a = 0; a < WT; ++a) {
-            av[a] = At[((tr0 + a) * 16 + lane % 16) * LDK + ks * 4 + lane / 16];
-            bv[a] = At[((tc0 + a) * 16 + lane % 16) * LDK + ks * 4 + lane / 16];
-          }
+          for (int a = 0; a < TR; ++a) av[a] = At[((tr0 + a) * 16 + lane % 16) * LDK + ks * 4 + lane / 16];
 #pragma unroll
-          for (int a = 0; a < WT; ++a)
+          for (int b = 0; b < TC; ++b) bv[b] = At[((tc0 + b) * 16 + lane % 16) * LDK + ks * 4 + lane / 16];
 #pragma unroll
-            for (int b = 0; b < WT; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+          for (int a = 0; a < TR; ++a)
+#pragma unroll
+            for (int b = 0; b < TC; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
         }
       }
       __syncthreads();
@@ -589,12 +575,12 @@ __device__ void gather_C_fp64_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_of
   }
   if (wave_on) {
 #pragma unroll
-    for (int a = 0; a < WT; ++a)
+    for (int a = 0; a < TR; ++a)
 #pragma unroll
-      for (int b = 0; b < WT; ++b)
+      for (int b = 0; b < TC; ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          put_A_own<M>(sm, (tr0 + a) * 16 + lane / 16 + 4 * v, (tc0 + b) * 16 + lane % 16, m, acc[a][b][v], I.a_diag, dbg);
+          put_A_own(sm, (tr0 + a) * 16 + lane / 16 + 4 * v, (tc0 + b) * 16 + lane % 16, m, acc[a][b][v], I.a_diag, dbg);
   }
   // b: threads sharing j = tid % M hold partial sums
   sm.red()[tid] = bpart;
@@ -607,37 +593,30 @@ __device__ void gather_C_fp64_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_of
   __syncthreads();
 }
 
-// ---- a4/a5 on the MFMA paths ------------------------------------------------
+// ---- a4/a5 on the FP32 path -------------------------------------------------
 // The chunk of observations is staged transposed, At[j][k] = sqrt(r_k) Y'[k][j],
 // so that C = At At^T is one MFMA product per 16 x 16 tile.  Wave w owns a
-// WT x WT block of tiles.  b is accumulated in FP64 from the FP32 slopes.
-template <int P, int M>
-__device__ void gather_C_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
-  using C = AnaCfg<M>;
+// TR x TC block of tiles.  b is accumulated in FP64 from the FP32 slopes.
+template <typename SM>
+__device__ __forceinline__ void gather_C_fp32(SM& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
+  using C = typename SM::C;
+  constexpr int M = C::M;
   constexpr int NT = C::NT;
-  constexpr int KCH = P == 1 ? C::KCF : C::KCB;
-  constexpr int TILES = M / 16;
-  constexpr int WT = TILES >= 2 ? TILES / 2 : 1;
+  constexpr int KCH = C::KCF;
+  constexpr int TILES = C::TILES, TR = C::TR, TC = C::TC;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
   const bool wave_on = TILES >= 2 || w == 0;
-  const int tr0 = TILES >= 2 ? (w / 2) * WT : 0;
-  const int tc0 = TILES >= 2 ? (w % 2) * WT : 0;
-  f32x4 acc[WT][WT];
-#pragma unroll
-  for (int a = 0; a < WT; ++a)
-#pragma unroll
-    for (int b = 0; b < WT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int tr0 = TILES >= 2 ? (w / 2) * TR : 0;
+  const int tc0 = TILES >= 2 ? (w % 2) * TC : 0;
   double bpart = 0.0;
   const float* Yp = (const float*)I.Yp;
   const int nobs = 2 * s;
-  // FP32 path: every k-step's product (4 observations) comes out of the MFMA
+  // Every k-step's product (4 observations) comes out of the MFMA
   // on its own and is added into an FP64 accumulator in LDS (Bm, row-major,
   // each entry owned by one lane).  A single FP32 accumulator over all p_l
   // observations carries ~sqrt(p_l / 4) 2^-24 of |C|, which the inverse square
   // root amplifies by up to kappa(A) / 2 (~1e4 on the ELT workloads).
-  constexpr int LDB = C::LDB;
-  if constexpr (P == 1)
-    for (int idx = tid; idx < M * LDB; idx += NT) sm.Bm[idx] = 0.0;
+  for (int idx = tid; idx < M * SM::LDA; idx += NT) sm.Bm[idx] = 0.0;
   // Thread (kk0 = tid / M, j = tid % M) stages observations kk0 + e NT / M of
   // every chunk for member j; the next chunk's rows are loaded into registers
   // before the current chunk's MFMAs, so their latency overlaps the products.
@@ -650,36 +629,21 @@ __device__ void gather_C_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_off, in
   const double* obs_sr = I.obs_sr + 2 * obs_off;
   const double* dvec = I.d;
   auto fetch = [&](int q0) {
-    if constexpr (M <= 64) {
-      // global loads (see gload), the row indices first, then what depends on them
-      int row[EPT];
+    // global loads (see gload), the row indices first, then what depends on them
+    int row[EPT];
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int q = q0 + kk0 + e * (NT / M);
-        row[e] = (q < nobs && j < m) ? gload(obs_row + q) : -1;
-        sv[e] = q < nobs ? gload(obs_sr + q) : 0.0;
-      }
+    for (int e = 0; e < EPT; ++e) {
+      const int q = q0 + kk0 + e * (NT / M);
+      row[e] = (q < nobs && j < m) ? gload(obs_row + q) : -1;
+      sv[e] = q < nobs ? gload(obs_sr + q) : 0.0;
+    }
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        yv[e] = 0.f;
-        dv[e] = 0.0;
-        if (row[e] >= 0) {
-          dv[e] = gload(dvec + row[e]);
-          yv[e] = gload(Yp + (size_t)row[e] * m + j);
-        }
-      }
-    } else {  // M = 128: the indices of every value at once would not fit in the registers
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int q = q0 + kk0 + e * (NT / M);
-        yv[e] = 0.f;
-        sv[e] = dv[e] = 0.0;
-        if (q < nobs && j < m) {
-          const int row = gload(obs_row + q);
-          sv[e] = gload(obs_sr + q);
-          dv[e] = gload(dvec + row);
-          yv[e] = gload(Yp + (size_t)row * m + j);
-        }
+    for (int e = 0; e < EPT; ++e) {
+      yv[e] = 0.f;
+      dv[e] = 0.0;
+      if (row[e] >= 0) {
+        dv[e] = gload(dvec + row[e]);
+        yv[e] = gload(Yp + (size_t)row[e] * m + j);
       }
     }
   };
@@ -691,59 +655,27 @@ __device__ void gather_C_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_off, in
       const double y = (double)yv[e];
       const double sy = sv[e] * y;
       bpart += (sv[e] * dv[e]) * sy;  // r d y with r = sqrt(r)^2
-      if constexpr (P == 1) ((float*)sm.stage)[j * C::LDKF + kk] = (float)sy;
-      else {
-        // split BF16: x = hi + lo with hi = bf16(x), lo = bf16(x - hi)
-        const float xf = (float)sy;
-        const __bf16 hi = (__bf16)xf;
-        ((__bf16*)sm.stage)[j * C::LDKB + kk] = hi;
-        ((__bf16*)sm.stage)[M * C::LDKB + j * C::LDKB + kk] = (__bf16)(xf - (float)hi);
-      }
+      ((float*)sm.stage)[j * C::LDKF + kk] = (float)sy;
     }
     __syncthreads();
     if (q0 + KCH < nobs) fetch(q0 + KCH);
     if (wave_on) {
-      if constexpr (P == 1) {
-        const float* At = (const float*)sm.stage;
+      const float* At = (const float*)sm.stage;
 #pragma unroll
-        for (int ks = 0; ks < KCH / 4; ++ks) {
-          float av[WT], bv[WT];
+      for (int ks = 0; ks < KCH / 4; ++ks) {
+        float av[TR], bv[TC];
 #pragma unroll
-          for (int a = 0; a < WT; ++a) {
-            av[a] = At[((tr0 + a) * 16 + lane % 16) * C::LDKF + ks * 4 + lane / 16];
-            bv[a] = At[((tc0 + a) * 16 + lane % 16) * C::LDKF + ks * 4 + lane / 16];
-          }
+        for (int a = 0; a < TR; ++a) av[a] = At[((tr0 + a) * 16 + lane % 16) * C::LDKF + ks * 4 + lane / 16];
 #pragma unroll
-          for (int a = 0; a < WT; ++a)
+        for (int b = 0; b < TC; ++b) bv[b] = At[((tc0 + b) * 16 + lane % 16) * C::LDKF + ks * 4 + lane / 16];
 #pragma unroll
-            for (int b = 0; b < WT; ++b) {
-              const f32x4 part = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-              double* cr = sm.Bm + ((tr0 + a) * 16 + 4 * (lane / 16)) * LDB + (tc0 + b) * 16 + lane % 16;
+        for (int a = 0; a < TR; ++a)
 #pragma unroll
-              for (int v = 0; v < 4; ++v) cr[v * LDB] += (double)part[v];
-            }
-        }
-      } else {
-        // C += hi hi^T + hi lo^T + lo hi^T (the lo lo^T term is below FP32 rounding)
-        const __bf16* Ah = (const __bf16*)sm.stage;
-        const __bf16* Al = Ah + M * C::LDKB;
-        bf16x8 ah[WT], al[WT], bh[WT], bl[WT];
+          for (int b = 0; b < TC; ++b) {
+            const f32x4 part = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            double* cr = sm.Bm + ((tr0 + a) * 16 + 4 * (lane / 16)) * SM::LDA + (tc0 + b) * 16 + lane % 16;
 #pragma unroll
-        for (int a = 0; a < WT; ++a) {
-          const int ra = ((tr0 + a) * 16 + lane % 16) * C::LDKB + 8 * (lane / 16);
-          const int rb = ((tc0 + a) * 16 + lane % 16) * C::LDKB + 8 * (lane / 16);
-          ah[a] = *(const bf16x8*)(Ah + ra);
-          al[a] = *(const bf16x8*)(Al + ra);
-          bh[a] = *(const bf16x8*)(Ah + rb);
-          bl[a] = *(const bf16x8*)(Al + rb);
-        }
-#pragma unroll
-        for (int a = 0; a < WT; ++a)
-#pragma unroll
-          for (int b = 0; b < WT; ++b) {
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
+            for (int v = 0; v < 4; ++v) cr[v * SM::LDA] += (double)part[v];
           }
       }
     }
@@ -751,17 +683,17 @@ __device__ void gather_C_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_off, in
   }
   if (wave_on) {
 #pragma unroll
-    for (int a = 0; a < WT; ++a)
+    for (int a = 0; a < TR; ++a)
 #pragma unroll
-      for (int b = 0; b < WT; ++b)
+      for (int b = 0; b < TC; ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int i = (tr0 + a) * 16 + 4 * (lane / 16) + v, j = (tc0 + b) * 16 + lane % 16;
-          // FP32 path: put_A of (i <= j) overwrites only (i, j), which this lane
+          // put_A of (i <= j) overwrites only (i, j), which this lane
           // owns, and (j, i), whose owner does not use its value; so every value
           // that is used is read before anything overwrites it.
-          const double c = P == 1 ? sm.Bm[i * LDB + j] : (double)acc[a][b][v];
-          put_A<M>(sm, i, j, m, c, I.a_diag, dbg);
+          const double c = sm.Bm[i * SM::LDA + j];
+          put_A(sm, i, j, m, c, I.a_diag, dbg);
         }
   }
   // b: threads sharing j = tid % M hold partial sums
@@ -775,32 +707,32 @@ __device__ void gather_C_mfma(AnaSmem<M>& sm, const InstDesc& I, int obs_off, in
   __syncthreads();
 }
 
-// The BF16 paths at M <= 64: the same products as gather_C_mfma, with the
+// ---- a4/a5 on the BF16 paths -------------------------------------------------
+// Split operands (hi + lo, three products) on v_mfma_f32_16x16x32_bf16, with the
 // observation table staged in LDS first (as in the FP64 gather: row of Y',
 // sqrt(r), sqrt(r) d, in the space A takes afterwards), so that the chunk
 // loop issues only the FP32 loads of Y' rows, three chunks in flight.  With
 // the index, r and d loads in the loop a chunk of 32 observations spent
 // ~6.6k cycles for a few hundred cycles of products.
-template <int P, int M>
-__device__ void gather_C_bf16_tab(AnaSmem<M>& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
-  using C = AnaCfg<M>;
-  static_assert(P >= 2 && M <= 64, "BF16 paths, M <= 64");
+template <typename SM>
+__device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
+  using C = typename SM::C;
+  constexpr int M = C::M;
   constexpr int NT = C::NT, KCH = C::KCB, LDKB = C::LDKB;
-  constexpr int TILES = M / 16;
-  constexpr int WT = TILES >= 2 ? TILES / 2 : 1;
+  constexpr int TILES = C::TILES, TR = C::TR, TC = C::TC;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
   const bool wave_on = TILES >= 2 || w == 0;
-  const int tr0 = TILES >= 2 ? (w / 2) * WT : 0;
-  const int tc0 = TILES >= 2 ? (w % 2) * WT : 0;
-  f32x4 acc[WT][WT];
+  const int tr0 = TILES >= 2 ? (w / 2) * TR : 0;
+  const int tc0 = TILES >= 2 ? (w % 2) * TC : 0;
+  f32x4 acc[TR][TC];
 #pragma unroll
-  for (int a = 0; a < WT; ++a)
+  for (int a = 0; a < TR; ++a)
 #pragma unroll
-    for (int b = 0; b < WT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < TC; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
   double bpart = 0.0;
   const float* Yp = (const float*)I.Yp;
   const int nobs = 2 * s;
-  constexpr int SEG = (M * C::LDB * 8 / 20) / KCH * KCH;
+  constexpr int SEG = (M * SM::LDA * 8 / 20) / KCH * KCH;
   static_assert(SEG >= KCH && SEG % 2 == 0 && (size_t)SEG * (4 + 8 + 8) <= sizeof(sm.Bm), "observation table");
   int* rowT = reinterpret_cast<int*>(sm.Bm);
   double* sT = sm.Bm + SEG / 2;
@@ -857,20 +789,23 @@ __device__ void gather_C_bf16_tab(AnaSmem<M>& sm, const InstDesc& I, int obs_off
       if (q0 + 2 * KCH < gn) fetch(next, q0 + 2 * KCH);
       if (wave_on) {
         // C += hi hi^T + hi lo^T + lo hi^T (the lo lo^T term is below FP32 rounding)
-        bf16x8 ah[WT], al[WT], bh[WT], bl[WT];
+        bf16x8 ah[TR], al[TR], bh[TC], bl[TC];
 #pragma unroll
-        for (int a = 0; a < WT; ++a) {
+        for (int a = 0; a < TR; ++a) {
           const int ra = ((tr0 + a) * 16 + lane % 16) * LDKB + 8 * (lane / 16);
-          const int rb = ((tc0 + a) * 16 + lane % 16) * LDKB + 8 * (lane / 16);
           ah[a] = *(const bf16x8*)(Ah + ra);
           al[a] = *(const bf16x8*)(Al + ra);
-          bh[a] = *(const bf16x8*)(Ah + rb);
-          bl[a] = *(const bf16x8*)(Al + rb);
         }
 #pragma unroll
-        for (int a = 0; a < WT; ++a)
+        for (int b = 0; b < TC; ++b) {
+          const int rb = ((tc0 + b) * 16 + lane % 16) * LDKB + 8 * (lane / 16);
+          bh[b] = *(const bf16x8*)(Ah + rb);
+          bl[b] = *(const bf16x8*)(Al + rb);
+        }
 #pragma unroll
-          for (int b = 0; b < WT; ++b) {
+        for (int a = 0; a < TR; ++a)
+#pragma unroll
+          for (int b = 0; b < TC; ++b) {
             acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
             acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
             acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
@@ -889,13 +824,13 @@ __device__ void gather_C_bf16_tab(AnaSmem<M>& sm, const InstDesc& I, int obs_off
   }
   if (wave_on) {
 #pragma unroll
-    for (int a = 0; a < WT; ++a)
+    for (int a = 0; a < TR; ++a)
 #pragma unroll
-      for (int b = 0; b < WT; ++b)
+      for (int b = 0; b < TC; ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int i = (tr0 + a) * 16 + 4 * (lane / 16) + v, jj = (tc0 + b) * 16 + lane % 16;
-          put_A<M>(sm, i, jj, m, (double)acc[a][b][v], I.a_diag, dbg);
+          put_A(sm, i, jj, m, (double)acc[a][b][v], I.a_diag, dbg);
         }
   }
   // b: threads sharing j = tid % M hold partial sums
@@ -906,6 +841,65 @@ __device__ void gather_C_bf16_tab(AnaSmem<M>& sm, const InstDesc& I, int obs_off
     for (int q = tid; q < NT; q += M) t += sm.red()[q];
     sm.bvec[tid] = tid < m ? t : 0.0;
   }
+  __syncthreads();
+}
+
+// ---- the same on vector FMA, k_analysis at M = 128 (64 accumulators a lane of
+// 256 threads) ---------------------------------------------------------------
+template <int M>
+__device__ __forceinline__ void gather_C_fp64(AnaSmem<M>& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
+  using C = AnaCfg<M>;
+  constexpr int NT = C::NT, KC = C::KC, TM = C::TM;
+  double* Xc = (double*)sm.stage;
+  const int m = I.m, tid = phase_tid(), ti = tid / 16, tj = tid % 16;
+  double acc[TM][TM];
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TM; ++y) acc[x][y] = 0.0;
+  double bacc = 0.0;
+  const double* Yp = (const double*)I.Yp;
+  const int nobs = 2 * s;
+  for (int q0 = 0; q0 < nobs; q0 += KC) {
+    const int kc = min(KC, nobs - q0);
+    for (int idx = tid; idx < KC * M; idx += NT) {
+      const int qq = idx / M, j = idx % M;
+      double v = 0.0;
+      if (qq < kc && j < m) v = Yp[(size_t)I.obs_row[2 * obs_off + q0 + qq] * m + j];
+      Xc[idx] = v;
+    }
+    if (tid < KC) {
+      double r = 0.0, dd = 0.0;
+      if (tid < kc) {
+        r = I.obs_r[2 * obs_off + q0 + tid];
+        dd = I.d[I.obs_row[2 * obs_off + q0 + tid]];
+      }
+      sm.rc[tid] = r;
+      sm.dc[tid] = dd;
+    }
+    __syncthreads();
+    for (int qq = 0; qq < kc; ++qq) {
+      const double r = sm.rc[qq];
+      double yi[TM], yj[TM];
+#pragma unroll
+      for (int x = 0; x < TM; ++x) {
+        yi[x] = r * Xc[qq * M + ti + 16 * x];
+        yj[x] = Xc[qq * M + tj + 16 * x];
+      }
+#pragma unroll
+      for (int x = 0; x < TM; ++x)
+#pragma unroll
+        for (int y = 0; y < TM; ++y) acc[x][y] += yi[x] * yj[y];
+    }
+    if (tid < M)
+      for (int qq = 0; qq < kc; ++qq) bacc += sm.rc[qq] * sm.dc[qq] * Xc[qq * M + tid];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TM; ++y) put_A(sm, ti + 16 * x, tj + 16 * y, m, acc[x][y], I.a_diag, dbg);
+  if (tid < M) sm.bvec[tid] = tid < m ? bacc : 0.0;
   __syncthreads();
 }
 
@@ -1445,7 +1439,7 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
 // columns at stride M + TPP inside the double storage), rotated, and widened
 // back.  The other paths rotate in FP64.
 template <int P, int M>
-__device__ int jacobi(AnaSmem<M>& sm, int m, bool& converged, bool fair) {
+__device__ __forceinline__ int jacobi(AnaSmem<M>& sm, int m, bool& converged, bool fair) {
   using C = AnaCfg<M>;
   if constexpr (P == 3) {
     // In-place width change by chunks of CC columns (at most 16 values per
@@ -1499,15 +1493,16 @@ __device__ int jacobi(AnaSmem<M>& sm, int m, bool& converged, bool fair) {
   }
 }
 
-// Products with the M x M matrix in LDS (column c at Bm[c * LDB ..]), by
-// TPC = NT / M lanes per output reduced by DPP: lane group o = tid / TPC,
+// Product of the transposed M x M matrix in LDS (column c at Bm[c * LDB ..]) with a
+// vector, by TPC = NT / M lanes per output reduced by DPP: lane group o = tid / TPC,
 // lane part = tid % TPC takes every TPC-th term (two accumulators), and every
 // lane of the group gets the sum.  With the column stride LDB the lanes of a
 // wavefront read distinct banks in both forms.
-// colsum: sum over r of Bm[o LDB + r] v[r]   (U^T v for U in the columns)
-template <int M>
-__device__ __forceinline__ double colsum(const AnaSmem<M>& sm, const double* v, int o, int part) {
-  using C = AnaCfg<M>;
+// sum over r of Bm[o LDB + r] v[r]
+template <typename SM>
+__device__ __forceinline__ double colsum(const SM& sm, const double* v, int o, int part) {
+  using C = typename SM::C;
+  constexpr int M = C::M;
   constexpr int TPC = C::NT / M, PER = M / TPC, LDB = C::LDB;
   double t0 = 0.0, t1 = 0.0;
 #pragma unroll 8
@@ -1540,7 +1535,7 @@ __device__ __forceinline__ double rowsum(const AnaSmem<M>& sm, const double* z, 
 // Cholesky, its lower triangle packed by rows), not through the eigenvectors,
 // and wbar += U Lambda^-1 U^T res.  Uses pcol[0] (residual) and pcol[1].
 template <int M>
-__device__ void refine_wbar(AnaSmem<M>& sm, const double* __restrict__ Ag, int m) {
+__device__ __forceinline__ void refine_wbar(AnaSmem<M>& sm, const double* __restrict__ Ag, int m) {
   constexpr int TPC = AnaCfg<M>::NT / M, PER = M / TPC;
   const int tid = phase_tid(), o = tid / TPC, part = tid % TPC;
   double* res = sm.pcol[0];
@@ -1569,7 +1564,7 @@ __device__ void refine_wbar(AnaSmem<M>& sm, const double* __restrict__ Ag, int m
   }
   __syncthreads();
   {
-    const double t = colsum<M>(sm, res, o, part);
+    const double t = colsum(sm, res, o, part);
     if (part == 0) z[o] = o < m ? t / sm.lam[o] : 0.0;
   }
   __syncthreads();
@@ -1590,14 +1585,14 @@ __device__ void refine_wbar(AnaSmem<M>& sm, const double* __restrict__ Ag, int m
 // factor of order tol kappa(A): two steps at tol 1e-6 and three at 1e-4 leave
 // wbar below 1e-8 and 2e-5 on the 15x15 (m = 100) and 84x84 workloads.
 template <int M>
-__device__ void refine_wbar_lj(AnaSmem<M>& sm, int m) {
+__device__ __forceinline__ void refine_wbar_lj(AnaSmem<M>& sm, int m) {
   constexpr int TPC = AnaCfg<M>::NT / M;
   const int tid = phase_tid(), o = tid / TPC, part = tid % TPC;
   double* z = sm.pcol[0];
   double* res = sm.pcol[1];
   __syncthreads();  // wbar complete
   {
-    const double t = colsum<M>(sm, sm.wbar, o, part);
+    const double t = colsum(sm, sm.wbar, o, part);
     if (part == 0) z[o] = o < m ? sm.lam[o] * t : 0.0;
   }
   __syncthreads();
@@ -1607,7 +1602,7 @@ __device__ void refine_wbar_lj(AnaSmem<M>& sm, int m) {
   }
   __syncthreads();
   {
-    const double t = colsum<M>(sm, res, o, part);
+    const double t = colsum(sm, res, o, part);
     if (part == 0) z[o] = o < m ? t / sm.lam[o] : 0.0;
   }
   __syncthreads();
@@ -1622,7 +1617,7 @@ __device__ void refine_wbar_lj(AnaSmem<M>& sm, int m) {
 // (from the converged columns sigma_i u_i of L J)
 // Leaves T row-major in Bm (T[k][j] at Bm[k*LDB + j], zero outside m x m).
 template <int P, int M>
-__device__ void transform(AnaSmem<M>& sm, const InstDesc& I, int l, double* dbg) {
+__device__ __forceinline__ void transform(AnaSmem<M>& sm, const InstDesc& I, int l, double* dbg) {
   const int m = I.m;
   using C = AnaCfg<M>;
   constexpr int NT = C::NT, LDB = C::LDB, TM = C::TM;
@@ -1653,7 +1648,7 @@ __device__ void transform(AnaSmem<M>& sm, const InstDesc& I, int l, double* dbg)
     // wbar = U Lambda^-1 U^T b
     constexpr int TPC = NT / M;
     const int o = tid / TPC, part = tid % TPC;
-    const double t = colsum<M>(sm, sm.bvec, o, part);
+    const double t = colsum(sm, sm.bvec, o, part);
     if (part == 0) {
       sm.zv[o] = o < m ? t / sm.lam[o] : 0.0;
       sm.nrm[o] = o < m ? sqrt((double)(m - 1) / sm.lam[o]) : 0.0;
@@ -1760,77 +1755,63 @@ __device__ void transform(AnaSmem<M>& sm, const InstDesc& I, int l, double* dbg)
 // KCH - 1: fetch() loads each thread's EPT values into registers (issued
 // before the previous chunk's products, so the loads overlap them), store()
 // writes the zero-padded chunk to LDS and the rows' member means to sm.rc.
-template <int M, int KCH, typename T>
+template <typename C, int KCH, typename T>
 struct RowChunk {
-  static constexpr int NT = AnaCfg<M>::NT, EPT = KCH * M / NT;
+  static constexpr int M = C::M, NT = C::NT, EPT = KCH * M / NT;
   // row stride of the staged chunk: M + 1, so that the 16 rows an MFMA operand
   // load reads for one member (one row per lane) fall in 16 different banks
   // (a stride of M put them all in one: a 16-way conflict on every load)
   static constexpr int LDX = M + 1;
   static_assert(KCH * M % NT == 0, "whole chunks per thread");
   T v[EPT];
-  int act[EPT];  // M <= 64: actuator indices of the chunk fetched next (see fetch)
+  int act[EPT];  // actuator indices of the chunk fetched next (see fetch)
   int qq0, jj;
   __device__ RowChunk() {
     const int tid = phase_tid();
     qq0 = M >= 64 ? __builtin_amdgcn_readfirstlane(tid / M) : tid / M;  // wavefront-uniform for M >= 64
     jj = tid % M;
   }
-  // the actuator indices of chunk q0 (M <= 64; called once for the first chunk,
-  // then by every fetch for the chunk after it)
+  // the actuator indices of chunk q0 (called once for the first chunk, then by
+  // every fetch for the chunk after it)
   __device__ void fetch_act(const InstDesc& I, int est_off, int e, int q0) {
-    if constexpr (M <= 64) {
-      const int m = I.m;
-      const int32_t* est_act = I.est_act + est_off;
+    const int m = I.m;
+    const int32_t* est_act = I.est_act + est_off;
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const int q = q0 + qq0 + u * (NT / M);
-        act[u] = (q < 2 * e && jj < m) ? gload(est_act + (q < e ? q : q - e)) : -1;
-      }
+    for (int u = 0; u < EPT; ++u) {
+      const int q = q0 + qq0 + u * (NT / M);
+      act[u] = (q < 2 * e && jj < m) ? gload(est_act + (q < e ? q : q - e)) : -1;
     }
   }
   __device__ void fetch(const InstDesc& I, int est_off, int e, int cur, int q0) {
     const int m = I.m;
     const T* ens = (const T*)I.ens;
-    const int32_t* est_act = I.est_act + est_off;
     const size_t slot = (size_t)I.n_act * m;
-    if constexpr (M <= 64) {
-      // global loads (see gload); the actuator indices run one chunk ahead
-      // (fetch_act), so a fetch never waits for its own index loads
+    // global loads (see gload); the actuator indices run one chunk ahead
+    // (fetch_act), so a fetch never waits for its own index loads
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const int q = q0 + qq0 + u * (NT / M);
-        v[u] = (T)0;
-        if (act[u] >= 0) {
-          const int inst = q < e ? cur : (cur ^ 1);
-          v[u] = gload(ens + (size_t)inst * slot + (size_t)act[u] * m + jj);
-        }
-      }
-      fetch_act(I, est_off, e, q0 + KCH);
-    } else {  // M = 128: the indices of every value at once would not fit in the registers
-#pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const int q = q0 + qq0 + u * (NT / M);
-        v[u] = (T)0;
-        if (q < 2 * e && jj < m) {
-          const int inst = q < e ? cur : (cur ^ 1);
-          const int act = gload(est_act + (q < e ? q : q - e));
-          v[u] = gload(ens + (size_t)inst * slot + (size_t)act * m + jj);
-        }
+    for (int u = 0; u < EPT; ++u) {
+      const int q = q0 + qq0 + u * (NT / M);
+      v[u] = (T)0;
+      if (act[u] >= 0) {
+        const int inst = q < e ? cur : (cur ^ 1);
+        v[u] = gload(ens + (size_t)inst * slot + (size_t)act[u] * m + jj);
       }
     }
+    fetch_act(I, est_off, e, q0 + KCH);
   }
-  template <typename S>
-  __device__ void store(AnaSmem<M>& sm, S* X, int m) {
+  template <typename SM, typename S>
+  __device__ void store(SM& sm, S* X, int m) {
 #pragma unroll
     for (int u = 0; u < EPT; ++u) X[(qq0 + u * (NT / M)) * LDX + jj] = (S)v[u];
     __syncthreads();
-    constexpr int TPR = NT / KCH;  // threads per row for the means (8 or 16)
+    constexpr int TPR = NT / KCH < 16 ? NT / KCH : 16;  // threads per row for the means
     const int tid = phase_tid(), row = tid / TPR, part = tid % TPR;
-    double sum = 0.0;
-    for (int j = part; j < m; j += TPR) sum += (double)X[row * LDX + j];
-    sum = group_sum<TPR>(sum);
-    if (part == 0) sm.rc[row] = sum / (double)m;
+    if (row < KCH) {
+      double sum = 0.0;
+      for (int j = part; j < m; j += TPR) sum += (double)X[row * LDX + j];
+      sum = group_sum<TPR>(sum);
+      if (part == 0) sm.rc[row] = sum / (double)m;
+    }
     __syncthreads();
   }
 };
@@ -1839,23 +1820,24 @@ struct RowChunk {
 // Chunks of 16 state rows (both instants) are staged with their member means;
 // wave w computes the 16 x 16 output tiles w, w + 4, ... of the chunk with
 // v_mfma_f64_16x16x4f64 (A = X' - xbar from LDS, B = T from Bm).
-template <int M>
-__device__ void update_fp64(AnaSmem<M>& sm, const InstDesc& I, int est_off, int e, int cur) {
-  using C = AnaCfg<M>;
+template <typename SM>
+__device__ __forceinline__ void update_fp64(SM& sm, const InstDesc& I, int est_off, int e, int cur) {
+  using C = typename SM::C;
+  constexpr int M = C::M;
   constexpr int LDB = C::LDB, KR = 16, CB = M / 16;
   static_assert((size_t)KR * (M + 1) * 8 <= C::STAGE_BYTES, "staging");
-  constexpr int LDX = RowChunk<M, KR, double>::LDX;
+  constexpr int LDX = RowChunk<C, KR, double>::LDX;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
   double* Xd = (double*)sm.stage;
   double* Z = (double*)I.Z + (size_t)2 * est_off * m;
-  RowChunk<M, KR, double> rows;
+  RowChunk<C, KR, double> rows;
   rows.fetch_act(I, est_off, e, 0);
   rows.fetch(I, est_off, e, cur, 0);
   for (int q0 = 0; q0 < 2 * e; q0 += KR) {
     const int kc = min(KR, 2 * e - q0);
     rows.store(sm, Xd, m);
     if (q0 + KR < 2 * e) rows.fetch(I, est_off, e, cur, q0 + KR);
-    for (int cb = w; cb < CB; cb += 4) {
+    for (int cb = w; cb < CB; cb += C::NW) {
       const int arow = lane % 16;
       const double xb = sm.rc[arow];
       const int col = cb * 16 + lane % 16;
@@ -1886,23 +1868,24 @@ __device__ void update_fp64(AnaSmem<M>& sm, const InstDesc& I, int est_off, int 
 // ---- a8 on the MFMA paths: Z = xbar 1^T + X' T in 16 x 16 tiles --------------
 // FP32: X' and T in FP32.  BF16: X' in BF16, T split into hi + lo BF16 parts
 // (two MFMAs), so only X' carries the BF16 rounding.
-template <int P, int M>
-__device__ void update_mfma(AnaSmem<M>& sm, const InstDesc& I, int est_off, int e, int cur) {
-  using C = AnaCfg<M>;
+template <int P, typename SM>
+__device__ __forceinline__ void update_mfma(SM& sm, const InstDesc& I, int est_off, int e, int cur) {
+  using C = typename SM::C;
+  constexpr int M = C::M;
   constexpr int LDB = C::LDB, KR = C::KR;
   constexpr int RB = KR / 16, CB = M / 16, NTILE = RB * CB;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
   float* Xf = (float*)sm.stage;
   float* Z = (float*)I.Z + (size_t)2 * est_off * m;
-  RowChunk<M, KR, float> rows;
-  constexpr int LDX = RowChunk<M, KR, float>::LDX;
+  RowChunk<C, KR, float> rows;
+  constexpr int LDX = RowChunk<C, KR, float>::LDX;
   static_assert((size_t)KR * LDX * 4 <= C::STAGE_BYTES, "staging");
   // BF16, M a multiple of 32: T converted once to its hi and lo BF16 parts,
   // transposed (Th[j][k], k contiguous, so that a lane's 8 consecutive k of the
   // B operand are one 16-byte load), in Bm's storage; the staged rows likewise
   // once per chunk to BF16 X' - xbar (zero past m).  Converting inside the
   // products repeated the work for every tile and chunk.
-  constexpr bool PRE = P == 2 && M % 32 == 0 && M <= 64;
+  constexpr bool PRE = P >= 2 && M % 32 == 0 && M * M / C::NT <= 32;
   constexpr int LDT = M + 8;  // bf16 row stride: 16-byte rows, banks spread over a pass
   __bf16* Th = (__bf16*)sm.Bm;
   __bf16* Tl = Th + M * LDT;
@@ -1949,7 +1932,7 @@ __device__ void update_mfma(AnaSmem<M>& sm, const InstDesc& I, int est_off, int 
       __syncthreads();
     }
     if (q0 + KR < 2 * e) rows.fetch(I, est_off, e, cur, q0 + KR);
-    for (int t = w; t < NTILE; t += 4) {
+    for (int t = w; t < NTILE; t += C::NW) {
       const int rb = t / CB, cb = t % CB;
       const int arow = rb * 16 + lane % 16;
       const float xb = (float)sm.rc[arow];
@@ -1981,15 +1964,10 @@ __device__ void update_mfma(AnaSmem<M>& sm, const InstDesc& I, int est_off, int 
             const int k = ks * 32 + 8 * (lane / 16) + u;
             float xa;
             double tv;
-            if constexpr (M <= 64) {
-              // masked by arithmetic, as above; k runs past M only at M = 16 (the index is clamped)
-              const int kc_ = (M % 32 == 0 || k < M) ? k : M - 1;
-              xa = (k < m ? 1.f : 0.f) * (Xf[arow * LDX + kc_] - xb);
-              tv = (M % 32 == 0 || k < M ? 1.0 : 0.0) * sm.Bm[kc_ * LDB + col];
-            } else {  // M = 128: the loads in flight at once would not fit in the registers
-              xa = (k < m) ? Xf[arow * LDX + k] - xb : 0.f;
-              tv = sm.Bm[k * LDB + col];
-            }
+            // masked by arithmetic, as above; k runs past M (the index is clamped)
+            const int kc_ = k < M ? k : M - 1;
+            xa = (k < m ? 1.f : 0.f) * (Xf[arow * LDX + kc_] - xb);
+            tv = (k < M ? 1.0 : 0.0) * sm.Bm[kc_ * LDB + col];
             const __bf16 hi = (__bf16)(float)tv;
             a[u] = (__bf16)xa;
             bh[u] = hi;
@@ -2020,7 +1998,7 @@ __device__ void update_mfma(AnaSmem<M>& sm, const InstDesc& I, int est_off, int 
 // with rows permuted, so T comes out of the transform as T_p and is stored back
 // through perm (T[perm[r]][perm[c]] = T_p[r][c]).
 template <int M>
-__device__ void sort_diag(AnaSmem<M>& sm, int m) {
+__device__ __forceinline__ void sort_diag(AnaSmem<M>& sm, int m) {
   using C = AnaCfg<M>;
   constexpr int NT = C::NT, LDB = C::LDB, PER = M * M / NT;
   static_assert(M * M % NT == 0 && M <= NT && NT % M == 0, "whole rows per thread");
@@ -2053,15 +2031,16 @@ __device__ void sort_diag(AnaSmem<M>& sm, int m) {
 }
 
 template <int P, int M>
-__device__ void analyse_item(AnaSmem<M>& sm, const InstDesc* __restrict__ tab, const ClassBatch& cb, int item, bool fair) {
+__device__ __forceinline__ void analyse_item(AnaSmem<M>& sm, const InstDesc* __restrict__ tab, const ClassBatch& cb, int item, bool fair) {
   using C = AnaCfg<M>;
-  const int eb = find_entry(cb.dom_off, cb.n, item);
+  const int eb = __builtin_amdgcn_readfirstlane(find_entry(cb.dom_off, cb.n, item));
   const InstDesc& I = tab[cb.inst[eb]];
-  const int l = I.order[item - cb.dom_off[eb]];
-  const int est_off = I.dom[4 * l], e = I.dom[4 * l + 1];
-  const int obs_off = I.dom[4 * l + 2], s = I.dom[4 * l + 3];
+  // uniform values, kept in scalar registers
+  const int l = __builtin_amdgcn_readfirstlane(I.order[item - cb.dom_off[eb]]);
+  const int est_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l]), e = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 1]);
+  const int obs_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 2]), s = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 3]);
   const int m = I.m;
-  const int cur = I.st->cur;
+  const int cur = __builtin_amdgcn_readfirstlane(I.st->cur);
   double* dbg = I.dbg ? I.dbg + (size_t)l * (2 * m * m + m + kDbgTail) : nullptr;
   // debug: shader-clock stamps at the phase boundaries (after each phase's barrier)
   auto stamp = [&](int k) {
@@ -2075,10 +2054,10 @@ __device__ void analyse_item(AnaSmem<M>& sm, const InstDesc* __restrict__ tab, c
     dbg[2 * m * m + m + 8] = (double)blockIdx.x;
   }
 
-  if constexpr (P == 0 && M <= 64) gather_C_fp64_mfma<M>(sm, I, obs_off, s, dbg);
+  if constexpr (P == 0 && M <= 64) gather_C_fp64_mfma(sm, I, obs_off, s, dbg);
   else if constexpr (P == 0) gather_C_fp64<M>(sm, I, obs_off, s, dbg);
-  else if constexpr (P >= 2 && M <= 64) gather_C_bf16_tab<P, M>(sm, I, obs_off, s, dbg);
-  else gather_C_mfma<P, M>(sm, I, obs_off, s, dbg);
+  else if constexpr (P >= 2) gather_C_bf16(sm, I, obs_off, s, dbg);
+  else gather_C_fp32(sm, I, obs_off, s, dbg);
   if constexpr (P == 0) {
     __syncthreads();
     if constexpr (M <= 64) sort_diag<M>(sm, m);
@@ -2108,8 +2087,8 @@ __device__ void analyse_item(AnaSmem<M>& sm, const InstDesc* __restrict__ tab, c
     gatomic_add(&I.st->sweeps, (unsigned long long)sweeps);
     gatomic_add(&I.st->solves, 1ull);
   }
-  if constexpr (P == 0) update_fp64<M>(sm, I, est_off, e, cur);
-  else update_mfma<P, M>(sm, I, est_off, e, cur);
+  if constexpr (P == 0) update_fp64(sm, I, est_off, e, cur);
+  else update_mfma<P>(sm, I, est_off, e, cur);
   stamp(5);
 }
 
@@ -2141,11 +2120,496 @@ __global__ __launch_bounds__(256) void k_analysis(const InstDesc* __restrict__ t
   const int total = cb.dom_off[cb.n];
   int item = blockIdx.x;
   while (item < total) {
-    analyse_item<P, M>(sm, tab, cb, item, fair != 0);
+    // FP64 and FP32 batches may hold instances of the other kernel
+    if (P >= 2 || !tab[cb.inst[find_entry(cb.dom_off, cb.n, item)]].poly) analyse_item<P, M>(sm, tab, cb, item, fair != 0);
     if (threadIdx.x == 0) s_next = (int)gridDim.x + (int)atomicAdd(&cb.next, 1u);
     __syncthreads();
-    item = s_next;
+    item = __builtin_amdgcn_readfirstlane(s_next);
     __syncthreads();
+  }
+}
+
+// pcol = b - A wbar, with A itself (Ag: the domain's copy of A = (m-1)/rho I + C,
+// its lower triangle packed by rows), for the refinement step of wbar = A^-1 b
+// on the FP64 path: Z (Z b) carries Z's rounding of order eps kappa, which the
+// step takes out (wbar 1e-10 -> 1e-12 where b lies along the large eigenvalues).
+template <int M>
+__device__ __forceinline__ void residual_wbar(PolySmem<M>& sm, const double* __restrict__ Ag, int m) {
+  constexpr int TPC = PolyCfg<M>::NT / M, PER = M / TPC;
+  const int tid = phase_tid(), o = tid / TPC, part = tid % TPC;
+  // (A wbar)_o: row o of the symmetric A; entry (o, c) is packed at row
+  // max(o, c), column min(o, c).  Padded rows and columns read entry 0 and
+  // are masked by arithmetic (the result is zero past m anyway).
+  double a[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int c = part + TPC * k;
+    const bool in = c < m && o < m;
+    const int hi = c > o ? c : o, lo = c > o ? o : c;
+    a[k] = (in ? 1.0 : 0.0) * gload(Ag + (in ? tri_size(hi) + lo : 0));
+  }
+  double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+  for (int k = 0; k < PER; k += 2) {
+    t0 = fma(a[k], sm.wbar[part + TPC * k], t0);
+    if (k + 1 < PER) t1 = fma(a[k + 1], sm.wbar[part + TPC * (k + 1)], t1);
+  }
+  const double t = group_sum<TPC>(t0 + t1);
+  if (part == 0) sm.pcol[o] = o < m ? sm.bvec[o] - t : 0.0;
+  __syncthreads();
+}
+
+// ---- a6/a7: A^(-1/2) by polynomial stages on the FP64 matrix cores ----------
+// W = [(m-1) A^-1]^(1/2) needs no eigenvectors.  A = (m-1)/rho I + C has its
+// smallest eigenvalue bounded below by (m-1)/rho, so with an upper bound beta
+// the spectrum's interval is known, and Z = A^(-1/2) comes from a few minimax
+// polynomial stages (isqrt_plan.hpp: 17-20 matrix products at the condition
+// numbers 1e4-6e4 of the ELT maps):
+//   P = q(M),  Z <- P Z,  M <- P (P M),   M_0 = A, Z_0 = I.
+// beta = |A^2|_F^(1/2), from the A^2 that the first stage needs anyway (1.05 to
+// 1.4 times the largest eigenvalue there); the first stage's coefficients
+// carry the scaling, so A itself is never rounded again.
+//
+// Layout: wavefront w owns the columns 16 w .. 16 w + 15 of every matrix, in
+// the accumulator registers of v_mfma_f64_16x16x4f64.  Register v of lane l
+// there holds row l / 16 + 4 v of column l % 16, which is exactly the right
+// operand of k-step v, so a product's right factor is never stored: only the
+// left factor goes through LDS (column c at Bm[c LD], one write of M, M^2 or P
+// per product group), and each wavefront reads it whole.  Two row tiles share a
+// 16-byte load: rows 32 p + 2 i and 32 p + 2 i + 1 sit in tiles 2 p and 2 p + 1.
+// LD = M + 2: the 8 lanes of a 16-byte column write then fall in 32 banks.
+// Every factor is used as computed, never mirrored: the products are
+// polynomials in A taken from the left, and their rounding stays commuting with
+// A to first order (forcing symmetry cost a factor 10 in a CPU replay, where
+// this form matches Cholesky + SVD at every condition number of the table:
+// 1e-13 at 1e4, 6e-12 at 1e6, 4e-10 at 6e7).
+template <int M>
+struct IsqrtBlock {
+  static constexpr int T = M / 16, LD = M + 2;
+  // the column a thread holds; row of element (t, v) in lane group g = lane / 16
+  static constexpr __device__ __forceinline__ int column(int tid) { return tid / 64 * 16 + tid % 16; }
+  static constexpr __device__ __forceinline__ int row(int t, int v, int g) {
+    if constexpr (T == 1) return g + 4 * v;
+    else return 32 * (t / 2) + 2 * (g + 4 * v) + (t & 1);
+  }
+  // acc = S X (ADD: acc += S X) for the wavefront's columns; S: column c at S[c * LD]
+  template <bool ADD = false>
+  static __device__ __forceinline__ void mul(const double* S, const f64x4 (&X)[T], f64x4 (&acc)[T], int tid) {
+    constexpr f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+    const int lane = tid % 64, g = lane / 16, i = lane % 16;
+    if constexpr (T == 1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(g + 4 * v) * LD + i], X[0][v], !ADD && v == 0 ? zero : acc[0], 0, 0, 0);
+    } else {
+      // k-step k: rows 32 p + 2 (g + 4 v) + h of X, k = 8 p + 2 v + h; operand
+      // load j = k T / 2 + q serves the two row tiles 2 q, 2 q + 1 of k-step k.
+      // Two loads run ahead of the products; the fence keeps the compiler from
+      // hoisting the others too (registers)
+      constexpr int Q = T / 2, NL = 4 * T * Q;
+      // (an LDS instruction's offset spans 64 KiB: one base per 64 rows, opaque,
+      // or the compiler keeps an address per load)
+      using ldsx2 = __attribute__((address_space(3))) const f64x2;
+      using ldsc = __attribute__((address_space(3))) const char;
+      ldsc* base[(T + 3) / 4];
+#pragma unroll
+      for (int z = 0; z < (T + 3) / 4; ++z) {
+        unsigned o = (unsigned)(uintptr_t)(ldsc*)(const char*)(S + (64 * z + 2 * g) * LD + 2 * i);
+        asm volatile("" : "+v"(o));
+        base[z] = (ldsc*)(uintptr_t)o;
+      }
+      constexpr int AH = T > 4 ? 1 : 2;  // loads ahead
+      f64x2 a[AH + 1];
+      auto load_op = [&](int j) {
+        const int k = j / Q, q = j % Q;
+        a[j % (AH + 1)] = *(ldsx2*)(base[k / 16] + 8 * ((32 * (k / 8 % 2) + 8 * ((k / 2) % 4) + k % 2) * LD + 32 * q));
+      };
+      load_op(0);
+      if constexpr (AH > 1) load_op(1);
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        if (j + AH < NL) load_op(j + AH);
+        const int k = j / Q, q = j % Q;
+        const bool first = !ADD && k == 0;
+        const double x = X[2 * (k / 8) + k % 2][(k / 2) % 4];
+        acc[2 * q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j % (AH + 1)].x, x, first ? zero : acc[2 * q], 0, 0, 0);
+        acc[2 * q + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j % (AH + 1)].y, x, first ? zero : acc[2 * q + 1], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  // the wavefront's columns to / from a matrix with column c at S[c * ld]
+  static __device__ __forceinline__ void store(double* S, int ld, const f64x4 (&X)[T], int tid) {
+    const int c = column(tid), g = tid % 64 / 16;
+    if constexpr (T == 1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) S[c * ld + g + 4 * v] = X[0][v];
+    } else {
+#pragma unroll
+      for (int p = 0; p < T / 2; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          *(f64x2*)(S + c * ld + 32 * p + 2 * (g + 4 * v)) = f64x2{X[2 * p][v], X[2 * p + 1][v]};
+          if constexpr (T > 4) __builtin_amdgcn_sched_barrier(0);  // registers: one pair at a time
+        }
+    }
+  }
+  static __device__ __forceinline__ void load(const double* S, int ld, f64x4 (&X)[T], int tid) {
+    const int c = column(tid), g = tid % 64 / 16;
+    if constexpr (T == 1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) X[0][v] = S[c * ld + g + 4 * v];
+    } else {
+#pragma unroll
+      for (int p = 0; p < T / 2; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const f64x2 x = *(const f64x2*)(S + c * ld + 32 * p + 2 * (g + 4 * v));
+          X[2 * p][v] = x.x;
+          X[2 * p + 1][v] = x.y;
+          if constexpr (T > 4)
+            if (v == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+  }
+};
+
+// Z = A^(-1/2) from A in Bm (stride M + 2): each wavefront ends with its
+// columns of Z in Z.  Returns the matrix products done; in_table: A's condition bound was
+// within the table (past it, or with a NaN in A, the last row runs all the same
+// and the domain counts as unconverged).
+// Four matrices in registers are 128 VGPRs per lane at M = 64 and 256 at
+// M = 128, which leaves too few for the rest: two of Z's four tiles wait in LDS
+// (behind S, up to the end of the staging area) at M = 64, seven of its eight in
+// `park` (a slot of the instance's workspace) at M = 128, while the stage's
+// polynomial is formed.
+template <int M, typename F>
+__device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, double* park, f64x4 (&Z)[M / 16],
+                                            bool& in_table, F&& planned) {
+  using B = IsqrtBlock<M>;
+  using C = PolyCfg<M>;
+  constexpr int T = B::T, NW = C::NW;
+  static_assert(T <= NW && M * B::LD <= M * PolyCfg<M>::LDB, "a column block per wavefront, S inside Bm");
+  // the thread index: at M = 128 afresh at every use, so that nothing derived
+  // from it stays in a register across the stages
+  const int tid0 = phase_tid(), w = __builtin_amdgcn_readfirstlane(tid0 / 64);
+  auto tid = [&]() { return M > 64 ? phase_tid() : tid0; };
+  const bool on = T == NW || w < T;
+  double* S = sm.Bm;
+  f64x4 Mc[T], X[T];
+  double ss = 0.0;
+  if (on) {
+    B::load(S, B::LD, Mc, tid());
+    B::mul(S, Mc, X, tid());  // A^2
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ss = fma(X[t][v], X[t][v], ss);
+  }
+  ss = group_sum<16>(ss);
+  ss += __shfl_xor(ss, 16, 64);
+  ss += __shfl_xor(ss, 32, 64);
+  if (tid0 % 64 == 0) sm.rc[w] = ss;
+  __syncthreads();
+  double fro = 0.0;
+#pragma unroll
+  for (int k = 0; k < (T < NW ? T : NW); ++k) fro += sm.rc[k];
+  const double beta = sqrt(sqrt(fro)), kappa = beta / a_diag;
+  // row r of the table serves kappa <= 2^(r/2); uniform, every thread read the same sums
+  in_table = kappa <= 0.999 * 0x1.0p52;
+  int r = in_table ? 1 + (int)(2.0f * __log2f((float)kappa) + 0.01f) : kIsqrtRows - 1;
+  r = __builtin_amdgcn_readfirstlane(r < 1 ? 1 : r >= kIsqrtRows ? kIsqrtRows - 1 : r);
+  planned();
+  const IsqrtRow& R = kIsqrtPlan[r];
+  const int n = R.n;
+  // Z between the stages: KEEP tiles stay in registers, the others wait outside
+  // (each lane its own values, 16 bytes a lane)
+  constexpr int KEEP = C::KEEP;
+  constexpr int AWAY = 2 * (T - KEEP);  // 16-byte values per lane outside
+  // scalar base + 32-bit lane offset, which the compiler may not turn into one
+  // 64-bit address per value kept across the stages
+  auto lane_offset = [&]() {
+    unsigned o = tid() % 64 * 16;
+    asm volatile("" : "+v"(o));
+    return o;
+  };
+  using gchar = __attribute__((address_space(1))) char;
+  using gx2 = __attribute__((address_space(1))) f64x2;
+  const uint64_t pb = (uint64_t)park;
+  gchar* const away_g = (gchar*)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(pb >> 32)) << 32 |
+                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)pb)) + w * (AWAY * 1024));
+  char* const away = (char*)(sm.Bm + M * B::LD) + w * (AWAY * 1024);
+  auto park_store = [&](const f64x4 (&V)[T]) {
+#pragma unroll
+    for (int t = 0; t < KEEP; ++t) Z[t] = V[t];
+    const unsigned o = lane_offset();
+#pragma unroll
+    for (int k = 0; k < AWAY; ++k) {
+      const f64x2 x = {V[KEEP + k / 2][2 * (k % 2)], V[KEEP + k / 2][2 * (k % 2) + 1]};
+      if constexpr (M > 64) *(gx2*)(away_g + k * 1024 + o) = x;
+      else *(f64x2*)(away + k * 1024 + o) = x;
+    }
+  };
+  auto park_load = [&](f64x4 (&V)[T]) {
+#pragma unroll
+    for (int t = 0; t < KEEP; ++t) V[t] = Z[t];
+    const unsigned o = lane_offset();
+#pragma unroll
+    for (int k = 0; k < AWAY; ++k) {
+      f64x2 x;
+      if constexpr (M > 64) x = *(const gx2*)(away_g + k * 1024 + o);
+      else x = *(const f64x2*)(away + k * 1024 + o);
+      V[KEEP + k / 2][2 * (k % 2)] = x.x;
+      V[KEEP + k / 2][2 * (k % 2) + 1] = x.y;
+    }
+  };
+  // the wavefront's columns of V, plus d I, into S, for all wavefronts to read
+  auto publish = [&](const f64x4 (&V)[T], double d) {
+    __syncthreads();  // every wavefront is done with the old S
+    if (on) {
+      B::store(S, B::LD, V, tid());
+      __asm__ volatile("" ::: "memory");  // a wavefront's LDS operations take effect in order
+      const int t = tid(), c = B::column(t);
+      if (t % 64 < 16 && d != 0.0) S[c * B::LD + c] += d;
+    }
+    __syncthreads();
+  };
+  // P = q(M) into S; Mc: the columns of M (of M - I in the last stage), S: all of
+  // it, X: the columns of its square (unless deg = 1).  Leaves X undefined.
+  auto stage_poly = [&](int s, int deg, double scale, double step) {
+    double q[7];  // in scalar registers
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      q[k] = readlane_f64(R.c[s][k] * scale, 0);
+      scale *= step;
+    }
+    if (deg == 1) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) X[t] = q[1] * Mc[t];
+      publish(X, q[0]);
+    } else if (deg == 2) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) X[t] = q[2] * X[t] + q[1] * Mc[t];
+      publish(X, q[0]);
+    } else {
+      f64x4 Y[T];
+      publish(X, 0.0);
+      // deg 4: M^2 (q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I
+      // deg 6: M^2 (M^2 (q6 M^2 + q5 M) + q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I
+      const bool six = deg == 6;
+      const double h2 = six ? q[6] : q[4], h1 = six ? q[5] : q[3], l2 = six ? q[4] : q[2], l1 = six ? q[3] : q[1];
+#pragma unroll
+      for (int k = 0; k < 4 * T; ++k) {
+        const double m1 = Mc[k / 4][k % 4], m2 = X[k / 4][k % 4];
+        X[k / 4][k % 4] = h2 * m2 + h1 * m1;
+        Y[k / 4][k % 4] = l2 * m2 + l1 * m1;
+        if (k % 2) __builtin_amdgcn_sched_barrier(0);
+      }
+      if (on) B::template mul<true>(S, X, Y, tid());
+      if (six) {
+        if (on) {
+          B::load(S, B::LD, X, tid());
+#pragma unroll
+          for (int t = 0; t < T; ++t) X[t] = q[2] * X[t] + q[1] * Mc[t];
+          B::template mul<true>(S, Y, X, tid());
+        }
+        publish(X, q[0]);
+        return;
+      }
+      publish(Y, q[0]);
+    }
+  };
+  // M <- P (P M) (minus I ahead of the last stage), its columns and S
+  auto stage_next = [&](bool shift) {
+    if (on) {
+      B::mul(S, Mc, X, tid());
+      B::mul(S, X, Mc, tid());
+    }
+    publish(Mc, shift ? -1.0 : 0.0);
+    if (shift && on) B::load(S, B::LD, Mc, tid());
+  };
+  stage_poly(0, R.deg[0], 1.0 / sqrt(beta), 1.0 / beta);  // the powers of A carry 1 / beta each
+  if (on) {
+    B::load(S, B::LD, X, tid());  // Z = P
+    park_store(X);
+  }
+  stage_next(n == 2);
+#pragma unroll 1
+  for (int s = 1;; ++s) {
+    const int deg = R.deg[s];
+    if (deg > 1 && on) B::mul(S, Mc, X, tid());  // M^2
+    stage_poly(s, deg, 1.0, 1.0);
+    f64x4 V[T];
+    if (on) {
+      park_load(V);
+      B::mul(S, V, X, tid());  // Z <- P Z
+    }
+    if (s + 1 == n) break;
+    if (on) park_store(X);
+    stage_next(s + 2 == n);
+  }
+#pragma unroll
+  for (int t = 0; t < T; ++t) Z[t] = X[t];
+  __syncthreads();  // every wavefront is done with S
+  return R.products;
+}
+
+// wbar = A^-1 b = Z (Z b) (with one refinement step through A itself on the
+// FP64 path) and T = sqrt(m-1) Z + wbar 1^T, row-major in Bm (T[k][j] at
+// Bm[k LDB + j], zero outside m x m), from the wavefronts' columns of Z.
+template <int P, int M>
+__device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int l, const f64x4 (&Z)[M / 16], double* dbg) {
+  using B = IsqrtBlock<M>;
+  using C = PolyCfg<M>;
+  constexpr int T = B::T, NW = C::NT / 64, LDB = C::LDB, TPC = C::NT / M;
+  const int m = I.m, tid = phase_tid(), w = tid / 64, g = tid % 64 / 16, c = B::column(tid);
+  const bool on = T == NW || w < T;
+  auto substamp = [&](int k) {
+    if (dbg && threadIdx.x == 0) dbg[2 * m * m + m + 10 + k] = (double)clock64();
+  };
+  if (on) B::store(sm.Bm, LDB, Z, tid);
+  __syncthreads();
+  substamp(0);
+  const int o = tid / TPC, part = tid % TPC;
+  // v <- Z (Z v), Z symmetric; padded entries of v are zero and stay zero
+  auto solve = [&](const double* rhs) {
+    const double t = colsum(sm, rhs, o, part);
+    if (part == 0) sm.zv[o] = t;
+    __syncthreads();
+    return colsum(sm, sm.zv, o, part);
+  };
+  {
+    const double x = solve(sm.bvec);
+    if (part == 0) sm.wbar[o] = x;
+    __syncthreads();
+  }
+  substamp(1);
+  if constexpr (P == 0) {
+    residual_wbar<M>(sm, I.Ascr + (size_t)l * tri_size(m), m);
+    const double x = solve(sm.pcol);
+    if (part == 0) sm.wbar[o] += x;
+    __syncthreads();
+  }
+  substamp(2);
+  if (on) {
+    const double sc = sqrt((double)(m - 1)), wb = sm.wbar[c];
+    f64x4 X[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = B::row(t, v, g);
+        X[t][v] = (r < m && c < m ? 1.0 : 0.0) * fma(sc, Z[t][v], wb);  // T[c][r]
+        if (dbg && r < m && c < m) dbg[m * m + m + c * m + r] = X[t][v];
+      }
+    B::store(sm.Bm, LDB, X, tid);
+  }
+  __syncthreads();
+}
+
+template <int P, int M>
+__device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __restrict__ tab, const ClassBatch& cb, int item) {
+  const int eb = __builtin_amdgcn_readfirstlane(find_entry(cb.dom_off, cb.n, item));
+  const InstDesc& I = tab[cb.inst[eb]];
+  // uniform values, kept in scalar registers
+  const int l = __builtin_amdgcn_readfirstlane(I.order[item - cb.dom_off[eb]]);
+  const int est_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l]), e = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 1]);
+  const int obs_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 2]), s = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 3]);
+  const int m = I.m;
+  const int cur = __builtin_amdgcn_readfirstlane(I.st->cur);
+  double* dbg = I.dbg ? I.dbg + (size_t)l * (2 * m * m + m + kDbgTail) : nullptr;
+  // debug: shader-clock stamps at the phase boundaries (after each phase's barrier)
+  auto stamp = [&](int k) {
+    if (dbg && threadIdx.x == 0) dbg[2 * m * m + m + k] = (double)clock64();
+  };
+  stamp(0);
+  if (dbg && threadIdx.x == 0) {  // debug: where the workgroup runs (HW_ID: SE, SH, CU, SIMD; XCC_ID)
+    dbg[2 * m * m + m + 6] = (double)__builtin_amdgcn_s_getreg(4 | (31 << 11));
+    dbg[2 * m * m + m + 7] = (double)__builtin_amdgcn_s_getreg(20 | (31 << 11));
+    dbg[2 * m * m + m + 8] = (double)blockIdx.x;
+  }
+
+  constexpr int ld = PolySmem<M>::LDA;
+  if constexpr (P == 0) gather_C_fp64_mfma(sm, I, obs_off, s, dbg);
+  else gather_C_fp32(sm, I, obs_off, s, dbg);
+  if constexpr (P == 0) {
+    // the domain's A, kept for the refinement of wbar (the stages overwrite
+    // it): the lower triangle of the m x m matrix, packed by rows (row i at
+    // i (i + 1) / 2), rows spread over the wavefronts and coalesced over lanes
+    double* Ag = I.Ascr + (size_t)l * tri_size(m);
+    const int w = phase_tid() / 64, lane = phase_tid() % 64;
+    for (int i = w; i < m; i += PolyCfg<M>::NT / 64)
+      for (int j = lane; j <= i; j += 64) gstore(Ag + tri_size(i) + j, sm.Bm[i * ld + j]);
+  }
+  stamp(1);
+  {
+    double* park = I.park;  // M > 64: this workgroup's slot (concurrent workgroups never share a slot)
+    static_assert(M <= 64 || kParkDoubles == M * (M - 16 * PolyCfg<M>::KEEP), "parking slots");
+    if (M > 64) park += (size_t)(I.n_dom <= kParkSlots ? l : (int)blockIdx.x) * kParkDoubles;
+    f64x4 Z[M / 16];
+    bool in_table;
+    const int products = isqrt_stages<M>(sm, I.a_diag, park, Z, in_table, [&]() { stamp(2); });
+    stamp(3);
+    if (threadIdx.x == 0) {
+      if (I.dbg_sweeps) I.dbg_sweeps[l] = products;
+      gatomic_add(&I.dom_sweeps[l], (unsigned)products);
+      if (!in_table) gatomic_add(&I.st->unconverged, 1);
+      gatomic_add(&I.st->sweeps, (unsigned long long)products);
+      gatomic_add(&I.st->solves, 1ull);
+    }
+    finish_T<P, M>(sm, I, l, Z, dbg);
+  }
+  stamp(4);
+  if constexpr (P == 0) update_fp64(sm, I, est_off, e, cur);
+  else update_mfma<P>(sm, I, est_off, e, cur);
+  stamp(5);
+}
+
+// Persistent like k_analysis, with a work counter of its own (a batch may hold
+// instances of both kernels).
+template <int P, int M>
+__global__ __launch_bounds__(PolyCfg<M>::NT, M <= 32 ? 4 : M <= 64 ? 3 : 2) void k_analysis_poly(const InstDesc* __restrict__ tab,
+                                                  BatchHdr* __restrict__ hdr, int cls) {
+  __shared__ PolySmem<M> sm;
+  __shared__ int s_next;
+  ClassBatch& cb = hdr->cls[cls];
+  const int total = cb.dom_off[cb.n];
+  int item = blockIdx.x;
+  while (item < total) {
+    if (tab[cb.inst[find_entry(cb.dom_off, cb.n, item)]].poly) analyse_poly<P, M>(sm, tab, cb, item);
+    if (threadIdx.x == 0) s_next = (int)gridDim.x + (int)atomicAdd(&cb.next_poly, 1u);
+    __syncthreads();
+    item = __builtin_amdgcn_readfirstlane(s_next);
+    __syncthreads();
+  }
+}
+
+// ----------------------------------------------------------------------------
+// Debug instances (LETKF_FLAG_DEBUG) of k_analysis_poly: the eigenvalues of a domain's
+// A = (m-1)/rho I + C, from the C that the analysis left in the debug record,
+// by Cholesky and a one-sided Jacobi in LDS, when the record is read
+// (letkf_debug_domain).  No frame runs it.
+// ----------------------------------------------------------------------------
+template <int M>
+__global__ __launch_bounds__(256) void k_lambda(const InstDesc* __restrict__ inst, int l) {
+  using C = AnaCfg<M>;
+  __shared__ AnaSmem<M> sm;
+  const InstDesc& I = *inst;
+  const int m = I.m, tid = phase_tid();
+  double* dbg = I.dbg + (size_t)l * (2 * m * m + m + kDbgTail);
+  for (int idx = tid; idx < M * M; idx += C::NT) {
+    const int c = idx / M, r = idx % M;
+    const double v = c < m && r < m ? gload(dbg + c * m + r) : 0.0;
+    sm.Bm[c * C::LDB + r] = v + (r == c ? I.a_diag : 0.0);
+  }
+  __syncthreads();
+  cholesky<M>(sm);
+  bool converged = false;
+  jacobi<0, M>(sm, m, converged, false);
+  for (int c = tid; c < m; c += C::NT) {
+    double ss = 0.0;
+    for (int r = 0; r < M; ++r) ss = fma(sm.Bm[c * C::LDB + r], sm.Bm[c * C::LDB + r], ss);
+    gstore(dbg + m * m + c, ss);  // columns of L J are sigma_i u_i and lambda_i = sigma_i^2
   }
 }
 
@@ -3036,11 +3500,42 @@ void launch_big_lambda(int items, int m_max, const InstDesc* tab, BatchHdr* hdr,
   hipLaunchKernelGGL(k_big_lambda, dim3(items), dim3(256), 0, s, tab, hdr, cls);
 }
 
-void launch_analysis(int cls, int grid, const InstDesc* tab, BatchHdr* hdr, hipStream_t s, int fair) {
+#define LETKF_POLY_KERNEL(cls, FN)                                  \
+  do {                                                              \
+    const int prec_ = (cls) / 4, sz_ = (cls) % 4;                   \
+    if (prec_ == 0) {                                               \
+      if (sz_ == 0) FN((k_analysis_poly<0, 16>));                   \
+      else if (sz_ == 1) FN((k_analysis_poly<0, 32>));              \
+      else if (sz_ == 2) FN((k_analysis_poly<0, 64>));              \
+      else FN((k_analysis_poly<0, 128>));                           \
+    } else {                                                        \
+      if (sz_ == 0) FN((k_analysis_poly<1, 16>));                   \
+      else if (sz_ == 1) FN((k_analysis_poly<1, 32>));              \
+      else FN((k_analysis_poly<1, 64>));                            \
+    }                                                               \
+  } while (0)
+
+void launch_analysis(int cls, int grid, int kinds, const InstDesc* tab, BatchHdr* hdr, hipStream_t s, int fair) {
   if (grid <= 0 || cls == kBigClass) return;  // the m > 128 class runs launch_big_analysis
+  if (kinds & kKindPoly) {
+    const bool m128 = cls % 4 == 3;
+    const int pgrid = m128 ? min(grid, kParkSlots) : grid;  // a workgroup per parking slot (and one fits a CU)
+#define LETKF_LAUNCH_POLY(K) hipLaunchKernelGGL(K, dim3(pgrid), dim3(m128 ? 512 : 256), 0, s, tab, hdr, cls)
+    LETKF_POLY_KERNEL(cls, LETKF_LAUNCH_POLY);
+#undef LETKF_LAUNCH_POLY
+  }
+  if (!(kinds & kKindJacobi)) return;
 #define LETKF_LAUNCH_ANA(K) hipLaunchKernelGGL(K, dim3(grid), dim3(256), 0, s, tab, hdr, cls, fair)
   LETKF_ANA_KERNEL(cls, LETKF_LAUNCH_ANA);
 #undef LETKF_LAUNCH_ANA
+}
+
+void launch_lambda(int cls, const InstDesc* inst, int domain, hipStream_t s) {
+  const int sz = cls % 4;
+  if (sz == 0) hipLaunchKernelGGL(k_lambda<16>, dim3(1), dim3(256), 0, s, inst, domain);
+  else if (sz == 1) hipLaunchKernelGGL(k_lambda<32>, dim3(1), dim3(256), 0, s, inst, domain);
+  else if (sz == 2) hipLaunchKernelGGL(k_lambda<64>, dim3(1), dim3(256), 0, s, inst, domain);
+  else hipLaunchKernelGGL(k_lambda<128>, dim3(1), dim3(256), 0, s, inst, domain);
 }
 
 int analysis_blocks_per_cu(int cls) {

@@ -18,11 +18,15 @@ void launch_rows(int cls, int mode, int act_rows, const InstDesc* tab, BatchHdr*
 // and the merge.
 void launch_pistons(int cls, int domain_items, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
 // The persistent analysis kernel with `grid` workgroups: they share the
-// class's domain items through its work counter, which the slope kernel
+// class's domain items through its work counter
+// (each kernel those of its own instances; kinds: the kKind* a launch holds), which the slope kernel
 // launched before it zeroes, so any grid >= 1 covers every item.  fair != 0:
 // progress-ordered issue priorities, for launches whose workgroups start
 // together at most two to a CU (analysis_fair_grid).
-void launch_analysis(int cls, int grid, const InstDesc* tab, BatchHdr* hdr, hipStream_t s, int fair = 0);
+void launch_analysis(int cls, int grid, int kinds, const InstDesc* tab, BatchHdr* hdr, hipStream_t s, int fair = 0);
+// Eigenvalues of a domain of a debug instance of k_analysis_poly into its debug
+// record, from the C the last analysis left there.
+void launch_lambda(int cls, const InstDesc* inst, int domain, hipStream_t s);
 // Whether a plain launch of `grid` workgroups on `num_cu` CUs takes the
 // progress-ordered priorities: at most two of its workgroups share a CU.
 inline int analysis_fair_grid(int grid, int num_cu) { return grid <= 2 * num_cu ? 1 : 0; }

@@ -184,6 +184,7 @@ Layout make_layout(const Problem& P) {
   {
     const size_t M = padded_members(P.m);
     L.Ascr = (P.prec == LETKF_FP64 && M <= 128) ? take((size_t)P.n_dom * tri_size(P.m) * 8) : 0;
+    L.park = M == 128 && uses_poly(P.prec, P.m, P.obs_instant) ? take((size_t)std::min(P.n_dom, kParkSlots) * kParkDoubles * 8) : 0;
   }
   if (P.flags & LETKF_FLAG_DEBUG) {
     L.dbg = take((size_t)P.n_dom * (2 * m * m + m + kDbgTail) * 8);
@@ -441,6 +442,8 @@ int upload_instance(const Problem& P, const Layout& L, char* ws, const double* X
   }
   D.dom_sweeps = (uint32_t*)(ws + L.dom_sweeps);
   D.Ascr = L.Ascr ? (double*)(ws + L.Ascr) : nullptr;
+  D.park = L.park ? (double*)(ws + L.park) : nullptr;
+  D.poly = uses_poly(P.prec, P.m, P.obs_instant) ? 1 : 0;
   D.dbg = L.dbg ? (double*)(ws + L.dbg) : nullptr;
   D.dbg_sweeps = L.dbg_sweeps ? (int32_t*)(ws + L.dbg_sweeps) : nullptr;
   D.st = (InstState*)(ws + L.state);
@@ -550,7 +553,7 @@ static void launch_domain_analysis(letkf_handle* h, hipStream_t s) {
   if (h->cls == letkf::kBigClass)
     letkf::launch_big_analysis(h->P.n_dom, h->max_rows, h->P.m, dev_desc(h), dev_hdr(h), s);
   else
-    letkf::launch_analysis(h->cls, h->ana_grid, dev_desc(h), dev_hdr(h), s, letkf::analysis_fair_grid(h->ana_grid, h->num_cu));
+    letkf::launch_analysis(h->cls, h->ana_grid, h->kinds(), dev_desc(h), dev_hdr(h), s, letkf::analysis_fair_grid(h->ana_grid, h->num_cu));
 }
 
 namespace letkf {
@@ -568,7 +571,7 @@ namespace letkf {
 // costliest take the CUs nobody shares).  With more domains than workgroups
 // resident at once (`resident`), the workgroups claim the later domains as
 // they finish: then longest first (decreasing cost) balances the tail.
-// cost[l]: domain l's cost in Jacobi-sweep units.
+// cost[l]: domain l's cost, in any unit.
 std::vector<int32_t> balanced_order(const Problem& P, const std::vector<double>& cost, int num_cu, int resident) {
   const int n = P.n_dom;
   if (n > resident) {
@@ -622,8 +625,9 @@ std::vector<int32_t> balanced_order(const Problem& P, const std::vector<double>&
 int upload_order(letkf_handle* h, int policy, hipStream_t s, std::vector<int32_t>* used) {
   std::vector<int32_t> order;
   if (policy == LETKF_ORDER_BALANCED) {
-    // cost of a domain: its sweeps summed over the analyses so far, plus the
-    // rest of its analysis, about 3.5 sweeps' worth each time
+    // cost of a domain: its sweeps (poly: products) summed over the analyses so
+    // far, plus the rest of its analysis, about 3.5 sweeps' (13 products') worth
+    // each time
     const int n = h->P.n_dom;
     std::vector<uint32_t> sw(n);
     InstState st{};
@@ -632,7 +636,7 @@ int upload_order(letkf_handle* h, int policy, hipStream_t s, std::vector<int32_t
     LETKF_HIP(hipStreamSynchronize(s));
     const double analyses = n > 0 ? (double)st.solves / n : 0.0;
     std::vector<double> cost(n);
-    for (int l = 0; l < n; ++l) cost[l] = sw[l] + 3.5 * analyses;
+    for (int l = 0; l < n; ++l) cost[l] = sw[l] + (h->desc.poly ? 13.0 : 3.5) * analyses;
     int num_cu = 0;
     LETKF_HIP(hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, h->device));
     order = balanced_order(h->P, cost, num_cu, analysis_blocks_per_cu(h->cls) * num_cu);
@@ -684,6 +688,8 @@ int tune_class(int cls, const InstDesc* tab, BatchHdr* hdr, int slope_rows, int 
   if (items <= 0 || insts.empty()) return fail(LETKF_EINVAL, "nothing to tune");
   reps = std::max(1, std::min(reps, 100));
   const int bpc = analysis_blocks_per_cu(cls);
+  int kinds = 0;
+  for (const letkf_handle* h : insts) kinds |= h->kinds();
   std::vector<int> grids;
   for (int k = 1; k <= 2 * bpc; ++k) grids.push_back(std::min(items, (k * num_cu + 1) / 2));
   grids.push_back(std::min(items, 65535));  // one workgroup per item: the hardware dispatcher balances
@@ -711,7 +717,7 @@ int tune_class(int cls, const InstDesc* tab, BatchHdr* hdr, int slope_rows, int 
     for (int r = 0; r <= reps; ++r) {
       launch_slopes(cls, slope_rows, tab, hdr, s);
       LETKF_HIP(hipEventRecord(e0, s));
-      launch_analysis(cls, grid, tab, hdr, s, balanced ? analysis_fair_grid(grid, num_cu) : 0);
+      launch_analysis(cls, grid, kinds, tab, hdr, s, balanced ? analysis_fair_grid(grid, num_cu) : 0);
       LETKF_HIP(hipEventRecord(e1, s));
       LETKF_HIP(hipGetLastError());
       LETKF_HIP(hipEventSynchronize(e1));
@@ -994,7 +1000,7 @@ int letkf_step_noalloc(letkf_handle* h, const double* y_dev, double* pred_dev, v
   const InstDesc* tab = (const InstDesc*)(sp + lay.desc);
   BatchHdr* hdr = (BatchHdr*)(sp + lay.hdr);
   launch_slopes(h->cls, h->P.p(), tab, hdr, s);
-  launch_analysis(h->cls, h->ana_grid, tab, hdr, s, analysis_fair_grid(h->ana_grid, h->num_cu));
+  launch_analysis(h->cls, h->ana_grid, h->kinds(), tab, hdr, s, analysis_fair_grid(h->ana_grid, h->num_cu));
   if (h->P.flags & LETKF_FLAG_PISTONS) launch_pistons(h->cls, h->P.n_dom, tab, hdr, s);
   launch_rows(h->cls, 2, h->P.n_act, tab, hdr, s);
   LETKF_HIP(hipGetLastError());
@@ -1052,6 +1058,7 @@ int letkf_debug_domain(letkf_handle* h, int32_t domain, double* C_out, double* l
   std::vector<double> buf(per);
   int32_t sw = 0;
   if (lam_out && h->cls == letkf::kBigClass) letkf::launch_big_lambda(h->P.n_dom, h->P.m, dev_desc(h), dev_hdr(h), s);
+  else if (lam_out && h->desc.poly) letkf::launch_lambda(h->cls, dev_desc(h), domain, s);
   LETKF_HIP(hipMemcpyAsync(buf.data(), h->ws + h->L.dbg + domain * per * 8, per * 8, hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipMemcpyAsync(&sw, h->ws + h->L.dbg_sweeps + domain * 4, 4, hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipStreamSynchronize(s));

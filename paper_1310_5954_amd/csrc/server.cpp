@@ -75,10 +75,10 @@ struct Batch {
 // power-of-two buckets of slope rows, domain items and actuator rows that
 // size the other grids (their kernels loop over the batch's actual work).
 struct GraphKey {
-  int cls, grid, pistons, rows_s, items, rows_a;
+  int cls, grid, kinds, pistons, rows_s, items, rows_a;
   bool operator<(const GraphKey& o) const {
-    return std::tie(cls, grid, pistons, rows_s, items, rows_a) <
-           std::tie(o.cls, o.grid, o.pistons, o.rows_s, o.items, o.rows_a);
+    return std::tie(cls, grid, kinds, pistons, rows_s, items, rows_a) <
+           std::tie(o.cls, o.grid, o.kinds, o.pistons, o.rows_s, o.items, o.rows_a);
   }
 };
 constexpr size_t kMaxGraphsPerSlot = 32;
@@ -196,7 +196,7 @@ int letkf_server::graph_for(int slot, const GraphKey& k, hipGraphExec_t* out) {
   hipGraph_t g = nullptr;
   LETKF_HIP(hipStreamBeginCapture(capture, hipStreamCaptureModeThreadLocal));
   launch_slopes(k.cls, k.rows_s, table(), dhdr(slot), capture);
-  launch_analysis(k.cls, k.grid, table(), dhdr(slot), capture);
+  launch_analysis(k.cls, k.grid, k.kinds, table(), dhdr(slot), capture);
   if (k.pistons) launch_pistons(k.cls, k.items, table(), dhdr(slot), capture);
   launch_rows(k.cls, 2, k.rows_a, table(), dhdr(slot), capture);
   const hipError_t le = hipGetLastError();
@@ -222,6 +222,7 @@ int letkf_server::launch_batch(Batch& b) {
   H.pmean = dout(s) + kStageDoubles;
   H.check_y = 1;  // device slopes are checked by the slope kernel (bad[] uploaded as zeros)
   size_t ytot = 0, otot = 0;
+  int kinds = 0;
   ClassBatch& cb = H.cls[c];
   for (size_t e = 0; e < b.frames.size(); ++e) {
     letkf_handle* h = b.frames[e].first;
@@ -237,6 +238,7 @@ int letkf_server::launch_batch(Batch& b) {
     }
     b.out_off.push_back((int32_t)otot);
     otot += h->P.n_act;
+    kinds |= h->kinds();
     const int k = cb.n++;
     cb.inst[k] = h->slot;
     cb.ent[k] = (int32_t)e;
@@ -252,14 +254,14 @@ int letkf_server::launch_batch(Batch& b) {
   LETKF_HIP(hipMemcpyAsync(dhdr(s), &H, sizeof(H), hipMemcpyHostToDevice, st));
   if (ytot) LETKF_HIP(hipMemcpyAsync(dy(s), h_y[s], ytot * sizeof(double), hipMemcpyHostToDevice, st));
   if (flags & LETKF_SERVER_GRAPHS) {
-    const GraphKey key{c, grid, b.pistons ? 1 : 0, pow2ceil(rows_s), pow2ceil(items), pow2ceil(rows_a)};
+    const GraphKey key{c, grid, kinds, b.pistons ? 1 : 0, pow2ceil(rows_s), pow2ceil(items), pow2ceil(rows_a)};
     hipGraphExec_t ex = nullptr;
     int rc = graph_for(s, key, &ex);
     if (rc) return rc;
     LETKF_HIP(hipGraphLaunch(ex, st));
   } else {
     launch_slopes(c, rows_s, table(), dhdr(s), st);
-    launch_analysis(c, grid, table(), dhdr(s), st);
+    launch_analysis(c, grid, kinds, table(), dhdr(s), st);
     if (b.pistons) launch_pistons(c, items, table(), dhdr(s), st);
     launch_rows(c, 2, rows_a, table(), dhdr(s), st);
     LETKF_HIP(hipGetLastError());

@@ -1,9 +1,10 @@
 """A^(-1/2) by polynomial stages over the condition numbers and sizes where its
 stages, tiles and padding change: T against the FP64 oracle, every domain."""
+import numpy as np
 import pytest
 
 import oracle
-from paper_1310_5954_amd import FP64, Filter, Problem
+from paper_1310_5954_amd import FP32, FP64, Filter, Problem, Server
 from workload.configs import build_case
 
 from _helpers import rel, sparse_D
@@ -36,3 +37,34 @@ def check_T(m, scale):
 @pytest.mark.parametrize("scale", [1e-6, 1e-2, 1.0, 1e3, 1e8])
 def test_T_over_condition_numbers_large_ensembles(m, scale):
     check_T(m, scale)
+
+
+@pytest.mark.parametrize("m", [2, 15, 16, 17, 32, 33, 63, 64, 65, 127, 128])
+@pytest.mark.parametrize("scale", [1e-6, 1e-2, 1.0, 1e3])
+def test_T_over_condition_numbers(m, scale):
+    check_T(m, scale)
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32])
+@pytest.mark.parametrize("m", [16, 64, 128])
+def test_batch_of_both_solvers_equals_the_plain_path(m, precision):
+    """Instances that observe phi_k and phi_{k-1} share a class but not an
+    analysis kernel; served together they give the plain path's states."""
+    case = build_case(1, m=m)
+    problems = [Problem.from_case(case, obs_instant=o) for o in (0, 1, 0)]
+    plain = []
+    for p in problems:
+        f = Filter(p, case.X0, precision=precision)
+        for k in range(2):
+            f.step(case.slopes(k))
+        plain.append(f.get_state()[0])
+        f.close()
+    srv = Server(sum(p.workspace_size(precision) + (1 << 16) for p in problems) + (64 << 20), max_batch=3)
+    inst = [srv.add(p, case.X0, precision) for p in problems]
+    for k in range(2):
+        for i, x in enumerate(inst):
+            assert srv.submit(x, case.slopes(k), 3 * k + i) == 0
+    srv.drain()
+    for x, want in zip(inst, plain):
+        assert np.array_equal(x.get_state()[0], want)
+    srv.close()
