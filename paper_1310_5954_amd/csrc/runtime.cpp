@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -1012,17 +1013,30 @@ int letkf_get_state(letkf_handle* h, double* X_out, uint64_t* frame_out, void* s
   int rc = access_stream(h, stream, &s);
   if (rc) return rc;
   if (!X_out) return fail(LETKF_EINVAL, "null X_out");
-  const size_t n = 2 * (size_t)h->P.n_act * h->P.m, es = h->P.esize();
-  std::vector<char> buf(n * es);
+  const size_t slot = (size_t)h->P.n_act * h->P.m;
   InstState S;
-  LETKF_HIP(hipMemcpyAsync(buf.data(), h->ws + h->L.ens, buf.size(), hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipMemcpyAsync(&S, h->ws + h->L.state, sizeof(S), hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipStreamSynchronize(s));
-  const size_t slot = (size_t)h->P.n_act * h->P.m;
-  for (int part = 0; part < 2; ++part) {
-    const size_t src = (size_t)(part == 0 ? S.cur : (S.cur ^ 1)) * slot;
-    for (size_t i = 0; i < slot; ++i)
-      X_out[part * slot + i] = es == 8 ? ((double*)buf.data())[src + i] : (double)((float*)buf.data())[src + i];
+  // Straight into the caller's array (FP64), or by chunks that stay in cache
+  // (FP32): a staging vector of the whole ensemble cost its clearing, its page
+  // faults and one more pass over memory (84 x 84, m = 64 FP64: 1.9 ms).
+  const char* ens = h->ws + h->L.ens;
+  if (h->P.esize() == 8) {
+    for (int part = 0; part < 2; ++part)
+      LETKF_HIP(hipMemcpyAsync(X_out + part * slot, ens + (size_t)(S.cur ^ part) * slot * 8, slot * 8,
+                               hipMemcpyDeviceToHost, s));
+    LETKF_HIP(hipStreamSynchronize(s));
+  } else {
+    const size_t chunk = std::min(slot, (size_t)1 << 18);
+    std::unique_ptr<float[]> buf(new float[chunk]);
+    for (int part = 0; part < 2; ++part)
+      for (size_t i = 0; i < slot; i += chunk) {
+        const size_t n = std::min(chunk, slot - i);
+        LETKF_HIP(hipMemcpyAsync(buf.get(), ens + ((size_t)(S.cur ^ part) * slot + i) * 4, n * 4, hipMemcpyDeviceToHost, s));
+        LETKF_HIP(hipStreamSynchronize(s));
+        double* x = X_out + part * slot + i;
+        for (size_t k = 0; k < n; ++k) x[k] = (double)buf[k];
+      }
   }
   if (frame_out) *frame_out = S.frame;
   return LETKF_OK;
