@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "desc.hpp"
 #include "isqrt_plan.hpp"
@@ -411,7 +412,8 @@ template <int M> struct PolyCfg : StageCfg<M, M <= 64 ? 256 : 512> {
   using B = StageCfg<M, M <= 64 ? 256 : 512>;
   static constexpr int LDB = M + (M <= 64 ? 8 : 4);  // column stride of Z and T in LDS
   static constexpr int LDA = M + 2;                  // of A and the stages' left factors
-  static constexpr int KEEP = M <= 32 ? M / 16 : M == 64 ? 2 : 1;  // tiles of Z that stay in registers (isqrt_stages)
+  // tiles of Z, of T, that stay in registers (isqrt_stages)
+  static constexpr int keep(int T) { return T <= 3 ? T : T == 4 ? 2 : T == 5 ? 4 : T == 6 ? 3 : T == 7 ? 0 : 1; }
   static constexpr size_t STAGE_BYTES = [] {
     size_t x = 0;
     for (size_t v : {(size_t)M * B::LDKD * 8, (size_t)M * B::LDKF * 4, (size_t)16 * (M + 1) * 8, (size_t)B::KR * (M + 1) * 4,
@@ -2183,94 +2185,114 @@ __device__ __forceinline__ void residual_wbar(PolySmem<M>& sm, const double* __r
 // A to first order (forcing symmetry cost a factor 10 in a CPU replay, where
 // this form matches Cholesky + SVD at every condition number of the table:
 // 1e-13 at 1e4, 6e-12 at 1e6, 4e-10 at 6e7).
-template <int M>
+// T = ceil(m / 16) tiles take part: at m = 48 a product is 36 MFMAs a wavefront
+// instead of the 64 of the padded M = 64 (an odd last tile has its rows in
+// plain order and loads of its own), at m = 100 seven tiles instead of eight.
+// 40 x 40, m = 48: analysis 82 -> 69 us; 100 x 100, m = 100: 1004 -> 840 us.
+template <int M, int T_>
 struct IsqrtBlock {
-  static constexpr int T = M / 16, LD = M + 2;
+  static constexpr int T = T_, LD = M + 2, Q = T / 2, ODD = T % 2;
   // the column a thread holds; row of element (t, v) in lane group g = lane / 16
-  static constexpr __device__ __forceinline__ int column(int tid) { return tid / 64 * 16 + tid % 16; }
+  static constexpr __device__ __forceinline__ int column(int tid) { return (tid >> 6) * 16 + (tid & 15); }
   static constexpr __device__ __forceinline__ int row(int t, int v, int g) {
-    if constexpr (T == 1) return g + 4 * v;
-    else return 32 * (t / 2) + 2 * (g + 4 * v) + (t & 1);
+    if (ODD && t == T - 1) return 16 * t + g + 4 * v;
+    return 32 * (t / 2) + 2 * (g + 4 * v) + (t & 1);
   }
   // acc = S X (ADD: acc += S X) for the wavefront's columns; S: column c at S[c * LD]
   template <bool ADD = false>
   static __device__ __forceinline__ void mul(const double* S, const f64x4 (&X)[T], f64x4 (&acc)[T], int tid) {
     constexpr f64x4 zero = {0.0, 0.0, 0.0, 0.0};
-    const int lane = tid % 64, g = lane / 16, i = lane % 16;
-    if constexpr (T == 1) {
+    const int g = (tid & 63) >> 4, i = tid & 15;
+    // k-step k < 8 Q: rows 32 p + 2 (g + 4 v) + h of X, k = 8 p + 2 v + h; the
+    // odd last tile's follow, 16 (T - 1) + g + 4 v.  Operand load q < Q of a
+    // k-step serves the two row tiles 2 q, 2 q + 1, load Q the odd last one.
+    // AH loads run ahead of the products; the fence keeps the compiler from
+    // hoisting the others too (registers).  An LDS instruction's offset spans
+    // 64 KiB: one base per 64 columns, opaque, or the compiler keeps an address
+    // per load.
+    constexpr int OPS = Q + ODD, NL = 4 * T * OPS, NB = (2 * Q + 3) / 4;
+    using ldsx2 = __attribute__((address_space(3))) const f64x2;
+    using ldsd = __attribute__((address_space(3))) const double;
+    using ldsc = __attribute__((address_space(3))) const char;
+    auto opaque = [](const double* x) {
+      unsigned o = (unsigned)(uintptr_t)(ldsc*)(const char*)x;
+      asm volatile("" : "+v"(o));
+      return (ldsc*)(uintptr_t)o;
+    };
+    ldsc* pair[NB > 0 ? NB : 1];   // row pairs, paired k
+    ldsc* one[NB > 0 ? NB : 1];    // the odd tile's rows, paired k
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(g + 4 * v) * LD + i], X[0][v], !ADD && v == 0 ? zero : acc[0], 0, 0, 0);
-    } else {
-      // k-step k: rows 32 p + 2 (g + 4 v) + h of X, k = 8 p + 2 v + h; operand
-      // load j = k T / 2 + q serves the two row tiles 2 q, 2 q + 1 of k-step k.
-      // Two loads run ahead of the products; the fence keeps the compiler from
-      // hoisting the others too (registers)
-      constexpr int Q = T / 2, NL = 4 * T * Q;
-      // (an LDS instruction's offset spans 64 KiB: one base per 64 rows, opaque,
-      // or the compiler keeps an address per load)
-      using ldsx2 = __attribute__((address_space(3))) const f64x2;
-      using ldsc = __attribute__((address_space(3))) const char;
-      ldsc* base[(T + 3) / 4];
-#pragma unroll
-      for (int z = 0; z < (T + 3) / 4; ++z) {
-        unsigned o = (unsigned)(uintptr_t)(ldsc*)(const char*)(S + (64 * z + 2 * g) * LD + 2 * i);
-        asm volatile("" : "+v"(o));
-        base[z] = (ldsc*)(uintptr_t)o;
+    for (int z = 0; z < NB; ++z) {
+      pair[z] = opaque(S + (64 * z + 2 * g) * LD + 2 * i);
+      if constexpr (ODD) one[z] = opaque(S + (64 * z + 2 * g) * LD + 16 * (T - 1) + i);
+    }
+    constexpr int AH = T > 4 ? 1 : 2;  // loads ahead
+    f64x2 a[AH + 1];
+    auto load_op = [&](int j) {
+      const int k = j / OPS, q = j % OPS;
+      if (k < 8 * Q) {
+        const int at = 8 * ((32 * (k / 8 % 2) + 8 * ((k / 2) % 4) + k % 2) * LD);
+        if (q < Q) a[j % (AH + 1)] = *(ldsx2*)(pair[k / 16] + at + 8 * 32 * q);
+        else a[j % (AH + 1)].x = *(ldsd*)(one[k / 16] + at);
+      } else {
+        // the odd tile's k: bases formed at their four uses, not kept
+        const double* Sk = S + (16 * (T - 1) + g + 4 * (k - 8 * Q)) * LD;
+        if (q < Q) a[j % (AH + 1)] = *(ldsx2*)(opaque(Sk + 2 * i) + 8 * 32 * q);
+        else a[j % (AH + 1)].x = *(ldsd*)opaque(Sk + 16 * (T - 1) + i);
       }
-      constexpr int AH = T > 4 ? 1 : 2;  // loads ahead
-      f64x2 a[AH + 1];
-      auto load_op = [&](int j) {
-        const int k = j / Q, q = j % Q;
-        a[j % (AH + 1)] = *(ldsx2*)(base[k / 16] + 8 * ((32 * (k / 8 % 2) + 8 * ((k / 2) % 4) + k % 2) * LD + 32 * q));
-      };
-      load_op(0);
-      if constexpr (AH > 1) load_op(1);
+    };
+    if constexpr (AH > 0) load_op(0);
+    if constexpr (AH > 1) load_op(1);
 #pragma unroll
-      for (int j = 0; j < NL; ++j) {
-        if (j + AH < NL) load_op(j + AH);
-        const int k = j / Q, q = j % Q;
-        const bool first = !ADD && k == 0;
-        const double x = X[2 * (k / 8) + k % 2][(k / 2) % 4];
-        acc[2 * q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j % (AH + 1)].x, x, first ? zero : acc[2 * q], 0, 0, 0);
-        acc[2 * q + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j % (AH + 1)].y, x, first ? zero : acc[2 * q + 1], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+    for (int j = 0; j < NL; ++j) {
+      if (j + AH < NL) load_op(j + AH);
+      const int k = j / OPS, q = j % OPS;
+      const bool first = !ADD && k == 0;
+      const double x = k < 8 * Q ? X[2 * (k / 8) + k % 2][(k / 2) % 4] : X[T - 1][k - 8 * Q];
+      const f64x2 av = a[j % (AH + 1)];
+      const int t = q < Q ? 2 * q : T - 1;
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, x, first ? zero : acc[t], 0, 0, 0);
+      if (q < Q) acc[t + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, x, first ? zero : acc[t + 1], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   // the wavefront's columns to / from a matrix with column c at S[c * ld]
   static __device__ __forceinline__ void store(double* S, int ld, const f64x4 (&X)[T], int tid) {
-    const int c = column(tid), g = tid % 64 / 16;
-    if constexpr (T == 1) {
+    const int c = column(tid), g = (tid & 63) >> 4;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) S[c * ld + g + 4 * v] = X[0][v];
-    } else {
+    for (int p = 0; p < Q; ++p)
 #pragma unroll
-      for (int p = 0; p < T / 2; ++p)
+      for (int v = 0; v < 4; ++v) {
+        *(f64x2*)(S + c * ld + 32 * p + 2 * (g + 4 * v)) = f64x2{X[2 * p][v], X[2 * p + 1][v]};
+        if constexpr (T > 4) __builtin_amdgcn_sched_barrier(0);  // registers: one pair at a time
+      }
+    if constexpr (ODD)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          *(f64x2*)(S + c * ld + 32 * p + 2 * (g + 4 * v)) = f64x2{X[2 * p][v], X[2 * p + 1][v]};
-          if constexpr (T > 4) __builtin_amdgcn_sched_barrier(0);  // registers: one pair at a time
-        }
-    }
+      for (int v = 0; v < 4; ++v) S[c * ld + 16 * (T - 1) + g + 4 * v] = X[T - 1][v];
   }
-  static __device__ __forceinline__ void load(const double* S, int ld, f64x4 (&X)[T], int tid) {
-    const int c = column(tid), g = tid % 64 / 16;
-    if constexpr (T == 1) {
+  // X = u S + w Y for the wavefront's columns (w = 0: S itself, Y unread)
+  template <bool AXPY = false>
+  static __device__ __forceinline__ void load(const double* S, int ld, f64x4 (&X)[T], int tid, double u = 1.0, double w = 0.0,
+                                              const f64x4* Y = nullptr) {
+    const int c = column(tid), g = (tid & 63) >> 4;
+    if constexpr (ODD)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) X[0][v] = S[c * ld + g + 4 * v];
-    } else {
+      for (int v = 0; v < 4; ++v) {
+        const double x = S[c * ld + 16 * (T - 1) + g + 4 * v];
+        X[T - 1][v] = AXPY ? u * x + w * Y[T - 1][v] : x;
+        if constexpr (T > 4)
+          if (v % 2) __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
-      for (int p = 0; p < T / 2; ++p)
+    for (int p = 0; p < Q; ++p)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const f64x2 x = *(const f64x2*)(S + c * ld + 32 * p + 2 * (g + 4 * v));
-          X[2 * p][v] = x.x;
-          X[2 * p + 1][v] = x.y;
-          if constexpr (T > 4)
-            if (v == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-    }
+      for (int v = 0; v < 4; ++v) {
+        const f64x2 x = *(const f64x2*)(S + c * ld + 32 * p + 2 * (g + 4 * v));
+        X[2 * p][v] = AXPY ? u * x.x + w * Y[2 * p][v] : x.x;
+        X[2 * p + 1][v] = AXPY ? u * x.y + w * Y[2 * p + 1][v] : x.y;
+        if constexpr (T > 4)
+          if (v % 2) __builtin_amdgcn_sched_barrier(0);
+      }
   }
 };
 
@@ -2283,18 +2305,20 @@ struct IsqrtBlock {
 // (behind S, up to the end of the staging area) at M = 64, seven of its eight in
 // `park` (a slot of the instance's workspace) at M = 128, while the stage's
 // polynomial is formed.
-template <int M, typename F>
-__device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, double* park, f64x4 (&Z)[M / 16],
+template <int M, int T, typename F>
+__device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, double* park, f64x4 (&Z)[T],
                                             bool& in_table, F&& planned) {
-  using B = IsqrtBlock<M>;
+  using B = IsqrtBlock<M, T>;
   using C = PolyCfg<M>;
-  constexpr int T = B::T, NW = C::NW;
+  constexpr int NW = C::NW;
   static_assert(T <= NW && M * B::LD <= M * PolyCfg<M>::LDB, "a column block per wavefront, S inside Bm");
   // the thread index: at M = 128 afresh at every use, so that nothing derived
   // from it stays in a register across the stages
   const int tid0 = phase_tid(), w = __builtin_amdgcn_readfirstlane(tid0 / 64);
   auto tid = [&]() { return M > 64 ? phase_tid() : tid0; };
-  const bool on = T == NW || w < T;
+  // (at T = 7 the eighth wavefront runs along on zero columns: a branch around
+  // its products would cost registers, and the SIMDs hold two wavefronts anyway)
+  const bool on = T == NW || T == 7 || w < T;
   double* S = sm.Bm;
   f64x4 Mc[T], X[T];
   double ss = 0.0;
@@ -2324,12 +2348,12 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
   const int n = R.n;
   // Z between the stages: KEEP tiles stay in registers, the others wait outside
   // (each lane its own values, 16 bytes a lane)
-  constexpr int KEEP = C::KEEP;
+  constexpr int KEEP = C::keep(T);
   constexpr int AWAY = 2 * (T - KEEP);  // 16-byte values per lane outside
   // scalar base + 32-bit lane offset, which the compiler may not turn into one
   // 64-bit address per value kept across the stages
   auto lane_offset = [&]() {
-    unsigned o = tid() % 64 * 16;
+    unsigned o = (tid() & 63) * 16;
     asm volatile("" : "+v"(o));
     return o;
   };
@@ -2370,7 +2394,7 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
       B::store(S, B::LD, V, tid());
       __asm__ volatile("" ::: "memory");  // a wavefront's LDS operations take effect in order
       const int t = tid(), c = B::column(t);
-      if (t % 64 < 16 && d != 0.0) S[c * B::LD + c] += d;
+      if ((t & 63) < 16 && d != 0.0) S[c * B::LD + c] += d;
     }
     __syncthreads();
   };
@@ -2408,9 +2432,7 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
       if (on) B::template mul<true>(S, X, Y, tid());
       if (six) {
         if (on) {
-          B::load(S, B::LD, X, tid());
-#pragma unroll
-          for (int t = 0; t < T; ++t) X[t] = q[2] * X[t] + q[1] * Mc[t];
+          B::template load<true>(S, B::LD, X, tid(), q[2], q[1], Mc);
           B::template mul<true>(S, Y, X, tid());
         }
         publish(X, q[0]);
@@ -2457,17 +2479,23 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
 // wbar = A^-1 b = Z (Z b) (with one refinement step through A itself on the
 // FP64 path) and T = sqrt(m-1) Z + wbar 1^T, row-major in Bm (T[k][j] at
 // Bm[k LDB + j], zero outside m x m), from the wavefronts' columns of Z.
-template <int P, int M>
-__device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int l, const f64x4 (&Z)[M / 16], double* dbg) {
-  using B = IsqrtBlock<M>;
+template <int P, int M, int T>
+__device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int l, const f64x4 (&Z)[T], double* dbg) {
+  using B = IsqrtBlock<M, T>;
   using C = PolyCfg<M>;
-  constexpr int T = B::T, NW = C::NT / 64, LDB = C::LDB, TPC = C::NT / M;
+  constexpr int NW = C::NT / 64, LDB = C::LDB, TPC = C::NT / M;
   const int m = I.m, tid = phase_tid(), w = tid / 64, g = tid % 64 / 16, c = B::column(tid);
-  const bool on = T == NW || w < T;
+  // (at T = 7 the eighth wavefront runs along on zero columns: a branch around
+  // its products would cost registers, and the SIMDs hold two wavefronts anyway)
+  const bool on = T == NW || T == 7 || w < T;
   auto substamp = [&](int k) {
     if (dbg && threadIdx.x == 0) dbg[2 * m * m + m + 10 + k] = (double)clock64();
   };
   if (on) B::store(sm.Bm, LDB, Z, tid);
+  if constexpr (16 * T < M) {  // past the tiles that took part: zero
+    for (int k = tid; k < M * (M - 16 * T); k += C::NT) sm.Bm[k / (M - 16 * T) * LDB + 16 * T + k % (M - 16 * T)] = 0.0;
+    for (int k = tid; k < (M - 16 * T) * 16 * T; k += C::NT) sm.Bm[(16 * T + k / (16 * T)) * LDB + k % (16 * T)] = 0.0;
+  }
   __syncthreads();
   substamp(0);
   const int o = tid / TPC, part = tid % TPC;
@@ -2544,20 +2572,35 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
   stamp(1);
   {
     double* park = I.park;  // M > 64: this workgroup's slot (concurrent workgroups never share a slot)
-    static_assert(M <= 64 || kParkDoubles == M * (M - 16 * PolyCfg<M>::KEEP), "parking slots");
+    static_assert(M <= 64 || (kParkDoubles >= M * 16 * (8 - PolyCfg<M>::keep(8)) && kParkDoubles >= M * 16 * (7 - PolyCfg<M>::keep(7))), "parking slots");
     if (M > 64) park += (size_t)(I.n_dom <= kParkSlots ? l : (int)blockIdx.x) * kParkDoubles;
-    f64x4 Z[M / 16];
-    bool in_table;
-    const int products = isqrt_stages<M>(sm, I.a_diag, park, Z, in_table, [&]() { stamp(2); });
-    stamp(3);
-    if (threadIdx.x == 0) {
-      if (I.dbg_sweeps) I.dbg_sweeps[l] = products;
-      gatomic_add(&I.dom_sweeps[l], (unsigned)products);
-      if (!in_table) gatomic_add(&I.st->unconverged, 1);
-      gatomic_add(&I.st->sweeps, (unsigned long long)products);
-      gatomic_add(&I.st->solves, 1ull);
+    auto solve = [&](auto tiles) {
+      constexpr int T = decltype(tiles)::value;
+      f64x4 Z[T];
+      bool in_table;
+      const int products = isqrt_stages<M, T>(sm, I.a_diag, park, Z, in_table, [&]() { stamp(2); });
+      stamp(3);
+      if (threadIdx.x == 0) {
+        if (I.dbg_sweeps) I.dbg_sweeps[l] = products;
+        gatomic_add(&I.dom_sweeps[l], (unsigned)products);
+        if (!in_table) gatomic_add(&I.st->unconverged, 1);
+        gatomic_add(&I.st->sweeps, (unsigned long long)products);
+        gatomic_add(&I.st->solves, 1ull);
+      }
+      finish_T<P, M, T>(sm, I, l, Z, dbg);
+    };
+    const int t = (m + 15) / 16;
+    if constexpr (M == 64) {
+      if (t <= 3) solve(std::integral_constant<int, 3>{});
+      else solve(std::integral_constant<int, 4>{});
+    } else if constexpr (M == 128) {
+      if (t <= 5) solve(std::integral_constant<int, 5>{});
+      else if (t == 6) solve(std::integral_constant<int, 6>{});
+      else if (t == 7) solve(std::integral_constant<int, 7>{});
+      else solve(std::integral_constant<int, 8>{});
+    } else {
+      solve(std::integral_constant<int, M / 16>{});
     }
-    finish_T<P, M>(sm, I, l, Z, dbg);
   }
   stamp(4);
   if constexpr (P == 0) update_fp64(sm, I, est_off, e, cur);

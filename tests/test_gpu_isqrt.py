@@ -39,7 +39,7 @@ def test_T_over_condition_numbers_large_ensembles(m, scale):
     check_T(m, scale)
 
 
-@pytest.mark.parametrize("m", [2, 15, 16, 17, 32, 33, 63, 64, 65, 127, 128])
+@pytest.mark.parametrize("m", [2, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128])
 @pytest.mark.parametrize("scale", [1e-6, 1e-2, 1.0, 1e3])
 def test_T_over_condition_numbers(m, scale):
     check_T(m, scale)
