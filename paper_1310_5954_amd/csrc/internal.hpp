@@ -119,7 +119,7 @@ struct letkf_handle {
   uint64_t timed_calls = 0;
   // captured frame (LETKF_FLAG_GRAPH)
   hipStream_t graph_stream = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
+  hipGraphExec_t graph_exec[3] = {};  // see capture_frame
   // analysis launch: persistent grid and domain order (letkf_autotune)
   int ana_grid = 0;
   int num_cu = 0;            // CUs of the device (the analysis launch's issue-priority rule)

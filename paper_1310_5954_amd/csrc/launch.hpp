@@ -10,9 +10,19 @@
 
 namespace letkf {
 
-void launch_slopes(int cls, int slope_rows, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
+// y (may be null): the slopes of a batch of one entry, in place of the header's
+// (a device pointer, or pinned host memory)
+void launch_slopes(int cls, int slope_rows, const InstDesc* tab, BatchHdr* hdr, hipStream_t s,
+                   const double* y = nullptr);
+// The means a frame of one instance leaves, `mean` (device, the one the mode
+// writes), stored to pinned host memory as well.
+struct HostMeans {
+  const double* mean = nullptr;
+  double* host = nullptr;
+};
 // mode 0: merge, 1: forecast, 2: merge + forecast
-void launch_rows(int cls, int mode, int act_rows, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
+void launch_rows(int cls, int mode, int act_rows, const InstDesc* tab, BatchHdr* hdr, hipStream_t s,
+                 const HostMeans& out = HostMeans());
 // Differential pistons of the instances created with LETKF_FLAG_PISTONS (the
 // others are skipped): overlap mismatches, then pistons; between the analysis
 // and the merge.

@@ -840,13 +840,21 @@ int letkf_create(const letkf_dims* dims, const letkf_model* model, const letkf_d
   return LETKF_OK;
 }
 
+// The captured frames launch the grid they were captured with.
+static void drop_graphs(letkf_handle* h) {
+  for (hipGraphExec_t& g : h->graph_exec) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
+  }
+}
+
 int letkf_destroy(letkf_handle* h) {
   if (!h) return LETKF_OK;
   if (h->server) return fail(LETKF_ESTATE, "instance belongs to a server: use letkf_server_remove");
   // teardown: errors here cannot be acted on, the host state goes regardless
   if (h->y_free) { (void)hipEventSynchronize(h->y_free); (void)hipEventDestroy(h->y_free); }
   for (hipEvent_t e : h->ev) (void)hipEventDestroy(e);
-  if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
+  drop_graphs(h);
   if (h->graph_stream) (void)hipStreamDestroy(h->graph_stream);
   if (h->h_y) (void)hipHostFree(h->h_y);
   if (h->h_out) (void)hipHostFree(h->h_out);
@@ -854,47 +862,105 @@ int letkf_destroy(letkf_handle* h) {
   return LETKF_OK;
 }
 
-// Stage y into the device y buffer of the handle (plain path).
-static int stage_y(letkf_handle* h, const double* y, int y_on_device, hipStream_t s) {
+// A call that waits for its means hands its host slopes to the slope kernel
+// where they are, in pinned memory, up to this many of them: a single read of
+// each over the bus, hidden behind the row's gathers, in place of a copy
+// command.  About 1600 of them add 1.8 us to k_slopes (12.4 -> 14.2) where the
+// copy cost a frame 4 to 6 us; by 4096 the two are even.
+constexpr int kHostSlopes = 4096;
+
+// Whether the slope kernel can read the caller's device slopes in place:
+// memory of the handle's GPU (anything else a copy command accepts is copied).
+static bool readable_y(const letkf_handle* h, const double* y) {
+  if ((uintptr_t)y % alignof(double)) return false;
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, y) != hipSuccess) {
+    (void)hipGetLastError();  // not memory HIP knows
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == h->device;
+}
+
+// The slopes of a frame (plain path).  *from: where the slope kernel reads
+// them, null for the handle's device y buffer, into which they are then copied.
+// waits: the call returns after the frame's end, so its kernels may read the
+// pinned buffer; inplace: device slopes may be read in the caller's memory.
+static int stage_y(letkf_handle* h, const double* y, int y_on_device, bool waits, bool inplace, const double** from,
+                   hipStream_t s) {
   const size_t bytes = sizeof(double) * h->P.p();
   double* dy = (double*)(h->ws + h->L.y);
+  *from = nullptr;
   if (!y) return fail(LETKF_EINVAL, "null y");
   if (y_on_device) {
+    if (inplace && readable_y(h, y)) {
+      *from = y;
+      return LETKF_OK;
+    }
     LETKF_HIP(hipMemcpyAsync(dy, y, bytes, hipMemcpyDeviceToDevice, s));
     return LETKF_OK;
   }
   if (!finite_all(y, h->P.p())) return fail(LETKF_ENUMERIC, "non-finite slopes");
   if (h->y_pending) LETKF_HIP(hipEventSynchronize(h->y_free));
+  h->y_pending = false;
   std::memcpy(h->h_y, y, bytes);
+  if (waits && h->P.p() <= kHostSlopes) {
+    *from = h->h_y;
+    return LETKF_OK;
+  }
   LETKF_HIP(hipMemcpyAsync(dy, h->h_y, bytes, hipMemcpyHostToDevice, s));
   LETKF_HIP(hipEventRecord(h->y_free, s));
   h->y_pending = true;
   return LETKF_OK;
 }
 
-static int read_means(letkf_handle* h, size_t off, double* out, hipStream_t s) {
-  LETKF_HIP(hipMemcpyAsync(h->h_out, h->ws + off, sizeof(double) * h->P.n_act, hipMemcpyDeviceToHost, s));
+// The means at `off` of the workspace, where a call wants them on the host.
+static HostMeans host_means(letkf_handle* h, size_t off, bool wanted) {
+  HostMeans o;
+  if (wanted) o = HostMeans{(const double*)(h->ws + off), h->h_out};
+  return o;
+}
+
+// The end of a call whose frame stored its means to h_out.
+static int wait_means(letkf_handle* h, double* out, hipStream_t s) {
   LETKF_HIP(hipStreamSynchronize(s));
   std::memcpy(out, h->h_out, sizeof(double) * h->P.n_act);
   return LETKF_OK;
+}
+
+// The launches of an analysis (mode 0) or a whole frame (mode 2), with the
+// timer's marks between its parts.
+static int launch_marked(letkf_handle* h, int mode, const double* from, const HostMeans& out, hipStream_t s) {
+  int rc;
+  if ((rc = mark(h, 0, s))) return rc;
+  launch_slopes(h->cls, h->P.p(), dev_desc(h), dev_hdr(h), s, from);
+  if ((rc = mark(h, 1, s))) return rc;
+  launch_domain_analysis(h, s);
+  if (h->P.flags & LETKF_FLAG_PISTONS) launch_pistons(h->cls, h->P.n_dom, dev_desc(h), dev_hdr(h), s);
+  if ((rc = mark(h, 2, s))) return rc;
+  launch_rows(h->cls, mode, h->P.n_act, dev_desc(h), dev_hdr(h), s, out);
+  if ((rc = mark(h, 3, s))) return rc;
+  LETKF_HIP(hipGetLastError());
+  return LETKF_OK;
+}
+
+static int run_frame(letkf_handle* h, const double* y, int y_on_device, int mode, double* out, hipStream_t s) {
+  const double* from = nullptr;
+  int rc = stage_y(h, y, y_on_device, out != nullptr, true, &from, s);
+  if (rc) return rc;
+  rc = launch_marked(h, mode, from, host_means(h, mode ? h->L.pmean : h->L.amean, out != nullptr), s);
+  if (!out) return rc;
+  if (rc) {
+    (void)hipStreamSynchronize(s);  // the launches made may still use the pinned buffers
+    return rc;
+  }
+  return wait_means(h, out, s);
 }
 
 int letkf_analyse(letkf_handle* h, const double* y, int y_on_device, double* mean_out, void* stream) {
   int rc = check_plain(h);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = stage_y(h, y, y_on_device, s))) return rc;
-  if ((rc = mark(h, 0, s))) return rc;
-  launch_slopes(h->cls, h->P.p(), dev_desc(h), dev_hdr(h), s);
-  if ((rc = mark(h, 1, s))) return rc;
-  launch_domain_analysis(h, s);
-  if (h->P.flags & LETKF_FLAG_PISTONS) launch_pistons(h->cls, h->P.n_dom, dev_desc(h), dev_hdr(h), s);
-  if ((rc = mark(h, 2, s))) return rc;
-  launch_rows(h->cls, 0, h->P.n_act, dev_desc(h), dev_hdr(h), s);
-  if ((rc = mark(h, 3, s))) return rc;
-  LETKF_HIP(hipGetLastError());
-  if (mean_out) return read_means(h, h->L.amean, mean_out, s);
-  return LETKF_OK;
+  return run_frame(h, y, y_on_device, 0, mean_out, s);
 }
 
 int letkf_forecast(letkf_handle* h, void* stream) {
@@ -911,29 +977,31 @@ int letkf_forecast(letkf_handle* h, void* stream) {
 
 // The kernels of one frame (slopes, analysis, pistons, merge + forecast,
 // state advance), all reading the frame's state from the device.
-static void launch_frame(letkf_handle* h, hipStream_t s) {
-  launch_slopes(h->cls, h->P.p(), dev_desc(h), dev_hdr(h), s);
+static void launch_frame(letkf_handle* h, const double* from, const HostMeans& out, hipStream_t s) {
+  launch_slopes(h->cls, h->P.p(), dev_desc(h), dev_hdr(h), s, from);
   launch_domain_analysis(h, s);
   if (h->P.flags & LETKF_FLAG_PISTONS) launch_pistons(h->cls, h->P.n_dom, dev_desc(h), dev_hdr(h), s);
-  launch_rows(h->cls, 2, h->P.n_act, dev_desc(h), dev_hdr(h), s);
+  launch_rows(h->cls, 2, h->P.n_act, dev_desc(h), dev_hdr(h), s, out);
 }
 
-// Captures launch_frame on the handle's private stream into a graph.
-static int capture_frame(letkf_handle* h) {
+// Captures launch_frame on the handle's private stream into a graph: one each
+// for frames nobody waits for, frames whose means go to the host, and those
+// whose slopes are read there as well (all its pointers are the handle's own).
+static int capture_frame(letkf_handle* h, const double* from, bool waits, hipGraphExec_t* exec) {
   if (!h->graph_stream) LETKF_HIP(hipStreamCreateWithFlags(&h->graph_stream, hipStreamNonBlocking));
   hipGraph_t g = nullptr;
   LETKF_HIP(hipStreamBeginCapture(h->graph_stream, hipStreamCaptureModeThreadLocal));
-  launch_frame(h, h->graph_stream);
+  launch_frame(h, from, host_means(h, h->L.pmean, waits), h->graph_stream);
   const hipError_t le = hipGetLastError();
   const hipError_t ee = hipStreamEndCapture(h->graph_stream, &g);
   if (le != hipSuccess || ee != hipSuccess || !g) {
     if (g) (void)hipGraphDestroy(g);
     return fail(LETKF_EDEVICE, "stream capture of the frame failed");
   }
-  const hipError_t ie = hipGraphInstantiate(&h->graph_exec, g, nullptr, nullptr, 0);
+  const hipError_t ie = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   if (ie != hipSuccess) {
-    h->graph_exec = nullptr;
+    *exec = nullptr;
     return fail(LETKF_EDEVICE, "hipGraphInstantiate");
   }
   return LETKF_OK;
@@ -943,23 +1011,13 @@ int letkf_step(letkf_handle* h, const double* y, int y_on_device, double* pred_o
   int rc = check_plain(h);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = stage_y(h, y, y_on_device, s))) return rc;
-  if ((h->P.flags & LETKF_FLAG_GRAPH) && !h->timing) {
-    if (!h->graph_exec && (rc = capture_frame(h))) return rc;
-    LETKF_HIP(hipGraphLaunch(h->graph_exec, s));
-    if (pred_out) return read_means(h, h->L.pmean, pred_out, s);
-    return LETKF_OK;
-  }
-  if ((rc = mark(h, 0, s))) return rc;
-  launch_slopes(h->cls, h->P.p(), dev_desc(h), dev_hdr(h), s);
-  if ((rc = mark(h, 1, s))) return rc;
-  launch_domain_analysis(h, s);
-  if (h->P.flags & LETKF_FLAG_PISTONS) launch_pistons(h->cls, h->P.n_dom, dev_desc(h), dev_hdr(h), s);
-  if ((rc = mark(h, 2, s))) return rc;
-  launch_rows(h->cls, 2, h->P.n_act, dev_desc(h), dev_hdr(h), s);
-  if ((rc = mark(h, 3, s))) return rc;
-  LETKF_HIP(hipGetLastError());
-  if (pred_out) return read_means(h, h->L.pmean, pred_out, s);
+  if (!(h->P.flags & LETKF_FLAG_GRAPH) || h->timing) return run_frame(h, y, y_on_device, 2, pred_out, s);
+  const double* from = nullptr;
+  if ((rc = stage_y(h, y, y_on_device, pred_out != nullptr, false, &from, s))) return rc;
+  hipGraphExec_t* exec = &h->graph_exec[!pred_out ? 0 : from ? 2 : 1];
+  if (!*exec && (rc = capture_frame(h, from, pred_out != nullptr, exec))) return rc;
+  LETKF_HIP(hipGraphLaunch(*exec, s));
+  if (pred_out) return wait_means(h, pred_out, s);
   return LETKF_OK;
 }
 
@@ -1188,10 +1246,7 @@ int letkf_autotune(letkf_handle* h, int32_t reps, letkf_tuning* out, void* strea
                        (hipStream_t)stream, out, &grid)))
     return rc;
   h->ana_grid = grid;
-  if (h->graph_exec) {  // the captured frame launches the old grid
-    (void)hipGraphExecDestroy(h->graph_exec);
-    h->graph_exec = nullptr;
-  }
+  drop_graphs(h);
   return LETKF_OK;
 }
 
@@ -1203,10 +1258,7 @@ int letkf_set_tuning(letkf_handle* h, const letkf_tuning* t, void* stream) {
     return fail(LETKF_EINVAL, "tuning: grid must be in [1, 65535] and order one of LETKF_ORDER_*");
   if ((rc = upload_order(h, t->order, (hipStream_t)stream))) return rc;
   h->ana_grid = std::min(t->grid, std::max(h->P.n_dom, 1));
-  if (h->graph_exec) {
-    (void)hipGraphExecDestroy(h->graph_exec);
-    h->graph_exec = nullptr;
-  }
+  drop_graphs(h);
   return LETKF_OK;
 }
 
