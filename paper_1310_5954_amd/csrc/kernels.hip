@@ -439,17 +439,28 @@ template <int M_, int NT_> struct StageCfg {
   static constexpr int KCB = 32;                   // BF16: observations per chunk (one k-step)
   static constexpr int LDKB = KCB + 8;             // row stride (bf16) of the transposed chunk
   static constexpr int KR = M <= 64 ? 32 : 16;     // update: state rows per chunk (16-row tiles)
+  // threads that hold partial sums of b, of norms and of products with a vector
+  static constexpr int RT = NT;
 };
 
-// k_analysis: 256 threads.
-template <int M> struct AnaCfg : StageCfg<M, 256> {
-  using StageCfg<M, 256>::NT;
-  using StageCfg<M, 256>::KCF;
-  using StageCfg<M, 256>::LDKF;
-  using StageCfg<M, 256>::LDKB;
-  using StageCfg<M, 256>::KR;
+// k_analysis: 256 threads, 512 at M = 128, where one workgroup fills the LDS of a
+// CU and 256 threads are one wavefront per SIMD: nothing overlaps a wavefront's
+// LDS traffic, and 32 rows a lane leave no registers to load the next column
+// ahead.  RT: sums over threads keep the order of 256 of them.
+// 128 x 128 map, m = 128, BF16: the analysis launch 4.70 -> 3.83 ms.
+template <int M> struct AnaCfg : StageCfg<M, M <= 64 ? 256 : 512> {
+  using B = StageCfg<M, M <= 64 ? 256 : 512>;
+  using B::NT;
+  using B::KCF;
+  using B::LDKF;
+  using B::LDKB;
+  using B::KR;
+  static constexpr int RT = 256;
   static constexpr int KC = 16;                    // FP64 path: rows per staged chunk (keeps m = 64 at 3 workgroups/CU)
-  static constexpr int TM = M / 16;                // FP64 path: TM x TM outputs per thread
+  // a thread's outputs where M x M entries are formed on vector FMA: TX x TM, rows
+  // row0 + 16 x and columns tid % 16 + 16 y
+  static constexpr int TM = M / 16, TX = TM * 256 / NT;
+  static constexpr __device__ int row0(int tid) { return NT == 256 ? tid / 16 : tid / 16 % 16 + 16 * TX * (tid / 256); }
   static constexpr int TPP = (2 * NT / M) < M ? (2 * NT / M) : M;  // threads per Jacobi pair
   // Column stride of the M x M matrix in LDS: shifting consecutive columns by
   // one pair-group span (min(TPP, 8) doubles) spreads the pair groups of a
@@ -471,10 +482,14 @@ template <int M> struct AnaSmem {
   static constexpr int LDA = C::LDB;                  // the gathers' stride of A
   static __device__ double pad(double) { return 1.0; }  // diagonal of A past m
   double Bm[M * C::LDB];                              // A, then U, then T (row-major)
-  alignas(16) unsigned char stage[C::STAGE_BYTES];    // chunk staging (phase-dependent type)
+  union {
+    alignas(16) unsigned char stage[C::STAGE_BYTES];  // chunk staging of the gather and the update (phase-dependent type)
+    struct {                                          // the transform's vectors, between the two
+      double lam[M], zv[M], pcol[2][M];
+    };
+  };
   double rc[32], dc[32];
-  double bvec[M], nrm[M], lam[M], zv[M], wbar[M];
-  double pcol[2][M];                                  // Cholesky pivot column (double buffer)
+  double bvec[M], nrm[M], wbar[M];
   int perm[M <= 64 ? M : 1];                          // FP64, M <= 64: A's symmetric permutation
   int s_rot;
   __device__ double* red() { return (double*)stage; }  // NT partial sums, aliases the staging area
@@ -676,7 +691,8 @@ template <typename SM>
 __device__ __forceinline__ void gather_C_fp32(SM& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
   using C = typename SM::C;
   constexpr int M = C::M;
-  constexpr int NT = C::NT;
+  constexpr int NT = C::NT, ST = C::RT;
+  const bool staging = ST == NT || phase_tid() < ST;
   constexpr int KCH = C::KCF;
   constexpr int TILES = C::TILES, TR = C::TR, TC = C::TC;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
@@ -692,11 +708,11 @@ __device__ __forceinline__ void gather_C_fp32(SM& sm, const InstDesc& I, int obs
   // observations carries ~sqrt(p_l / 4) 2^-24 of |C|, which the inverse square
   // root amplifies by up to kappa(A) / 2 (~1e4 on the ELT workloads).
   for (int idx = tid; idx < M * SM::LDA; idx += NT) sm.Bm[idx] = 0.0;
-  // Thread (kk0 = tid / M, j = tid % M) stages observations kk0 + e NT / M of
-  // every chunk for member j; the next chunk's rows are loaded into registers
+  // Thread (kk0 = tid / M, j = tid % M), of the first ST, stages observations
+  // kk0 + e ST / M of every chunk for member j; the next chunk's rows are loaded into registers
   // before the current chunk's MFMAs, so their latency overlaps the products.
-  constexpr int EPT = KCH * M / NT;
-  static_assert(KCH * M % NT == 0, "whole chunks per thread");
+  constexpr int EPT = KCH * M / ST;
+  static_assert(KCH * M % ST == 0, "whole chunks per thread");
   const int kk0 = M >= 64 ? __builtin_amdgcn_readfirstlane(tid / M) : tid / M, j = tid % M;
   float yv[EPT];
   double sv[EPT], dv[EPT];  // sqrt(r) (host-computed) and d; fetch() only issues loads
@@ -708,7 +724,7 @@ __device__ __forceinline__ void gather_C_fp32(SM& sm, const InstDesc& I, int obs
     int row[EPT];
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-      const int q = q0 + kk0 + e * (NT / M);
+      const int q = q0 + kk0 + e * (ST / M);
       row[e] = (q < nobs && j < m) ? gload(obs_row + q) : -1;
       sv[e] = q < nobs ? gload(obs_sr + q) : 0.0;
     }
@@ -722,18 +738,19 @@ __device__ __forceinline__ void gather_C_fp32(SM& sm, const InstDesc& I, int obs
       }
     }
   };
-  fetch(0);
+  if (staging) fetch(0);
   for (int q0 = 0; q0 < nobs; q0 += KCH) {
+    if (staging)
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-      const int kk = kk0 + e * (NT / M);
+      const int kk = kk0 + e * (ST / M);
       const double y = (double)yv[e];
       const double sy = sv[e] * y;
       bpart += (sv[e] * dv[e]) * sy;  // r d y with r = sqrt(r)^2
       ((float*)sm.stage)[j * C::LDKF + kk] = (float)sy;
     }
     __syncthreads();
-    if (q0 + KCH < nobs) fetch(q0 + KCH);
+    if (staging && q0 + KCH < nobs) fetch(q0 + KCH);
     if (wave_on) {
       const float* At = (const float*)sm.stage;
 #pragma unroll
@@ -772,11 +789,11 @@ __device__ __forceinline__ void gather_C_fp32(SM& sm, const InstDesc& I, int obs
         }
   }
   // b: threads sharing j = tid % M hold partial sums
-  sm.red()[tid] = bpart;
+  if (staging) sm.red()[tid] = bpart;
   __syncthreads();
   if (tid < M) {
     double t = 0.0;
-    for (int q = tid; q < NT; q += M) t += sm.red()[q];
+    for (int q = tid; q < ST; q += M) t += sm.red()[q];
     sm.bvec[tid] = tid < m ? t : 0.0;
   }
   __syncthreads();
@@ -793,7 +810,8 @@ template <typename SM>
 __device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
   using C = typename SM::C;
   constexpr int M = C::M;
-  constexpr int NT = C::NT, KCH = C::KCB, LDKB = C::LDKB;
+  constexpr int NT = C::NT, ST = C::RT, KCH = C::KCB, LDKB = C::LDKB;
+  const bool staging = ST == NT || phase_tid() < ST;
   constexpr int TILES = C::TILES, TR = C::TR, TC = C::TC;
   const int m = I.m, tid = phase_tid(), w = tid / 64, lane = tid % 64;
   const bool wave_on = TILES >= 2 || w == 0;
@@ -815,10 +833,10 @@ __device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs
   const int32_t* obs_row = I.obs_row + 2 * obs_off;
   const double* obs_sr = I.obs_sr + 2 * obs_off;
   const double* dvec = I.d;
-  // Thread (kk0 = tid / M, j = tid % M) stages observations kk0 + e NT / M of
-  // every chunk for member j.
-  constexpr int EPT = KCH * M / NT;
-  static_assert(KCH * M % NT == 0, "whole chunks per thread");
+  // Thread (kk0 = tid / M, j = tid % M), of the first ST, stages observations
+  // kk0 + e ST / M of every chunk for member j.
+  constexpr int EPT = KCH * M / ST;
+  static_assert(KCH * M % ST == 0, "whole chunks per thread");
   const int kk0 = M >= 64 ? __builtin_amdgcn_readfirstlane(tid / M) : tid / M, j = tid % M;
   __bf16* Ah = (__bf16*)sm.stage;
   __bf16* Al = Ah + M * LDKB;
@@ -842,16 +860,17 @@ __device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs
     auto fetch = [&](float (&y)[EPT], int q0) {  // Y' of chunk q0 (segment-relative)
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
-        const int q = q0 + kk0 + e * (NT / M);
+        const int q = q0 + kk0 + e * (ST / M);
         y[e] = 0.f;
         if (q < gn && j < m) y[e] = gload(Yp + (size_t)rowT[q] * m + j);
       }
     };
     auto chunk = [&](const float (&y)[EPT], float (&next)[EPT], int q0) {
+      if (staging)
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
-        const int q = q0 + kk0 + e * (NT / M);  // < gr: the table's tail is zero
-        const int kk = kk0 + e * (NT / M);
+        const int q = q0 + kk0 + e * (ST / M);  // < gr: the table's tail is zero
+        const int kk = kk0 + e * (ST / M);
         const double sy = sT[q] * (double)y[e];
         bpart += sdT[q] * sy;  // r d y with r = sqrt(r)^2
         // split BF16: x = hi + lo with hi = bf16(x), lo = bf16(x - hi)
@@ -861,7 +880,7 @@ __device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs
         Al[j * LDKB + kk] = (__bf16)(xf - (float)hi);
       }
       __syncthreads();
-      if (q0 + 2 * KCH < gn) fetch(next, q0 + 2 * KCH);
+      if (staging && q0 + 2 * KCH < gn) fetch(next, q0 + 2 * KCH);
       if (wave_on) {
         // C += hi hi^T + hi lo^T + lo hi^T (the lo lo^T term is below FP32 rounding)
         bf16x8 ah[TR], al[TR], bh[TC], bl[TC];
@@ -889,8 +908,8 @@ __device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs
       __syncthreads();
     };
     float ya[EPT], yb[EPT], yc[EPT];
-    fetch(ya, 0);
-    if (KCH < gn) fetch(yb, KCH);
+    if (staging) fetch(ya, 0);
+    if (staging && KCH < gn) fetch(yb, KCH);
     for (int q0 = 0; q0 < gn; q0 += 3 * KCH) {
       chunk(ya, yc, q0);
       if (q0 + KCH < gn) chunk(yb, ya, q0 + KCH);
@@ -909,27 +928,26 @@ __device__ __forceinline__ void gather_C_bf16(SM& sm, const InstDesc& I, int obs
         }
   }
   // b: threads sharing j = tid % M hold partial sums
-  sm.red()[tid] = bpart;
+  if (staging) sm.red()[tid] = bpart;
   __syncthreads();
   if (tid < M) {
     double t = 0.0;
-    for (int q = tid; q < NT; q += M) t += sm.red()[q];
+    for (int q = tid; q < ST; q += M) t += sm.red()[q];
     sm.bvec[tid] = tid < m ? t : 0.0;
   }
   __syncthreads();
 }
 
-// ---- the same on vector FMA, k_analysis at M = 128 (64 accumulators a lane of
-// 256 threads) ---------------------------------------------------------------
+// ---- the FP64 gather on vector FMA, k_analysis at M = 128 --------------------
 template <int M>
 __device__ __forceinline__ void gather_C_fp64(AnaSmem<M>& sm, const InstDesc& I, int obs_off, int s, double* dbg) {
   using C = AnaCfg<M>;
-  constexpr int NT = C::NT, KC = C::KC, TM = C::TM;
+  constexpr int NT = C::NT, KC = C::KC, TM = C::TM, TX = C::TX;
   double* Xc = (double*)sm.stage;
-  const int m = I.m, tid = phase_tid(), ti = tid / 16, tj = tid % 16;
-  double acc[TM][TM];
+  const int m = I.m, tid = phase_tid(), ti = C::row0(tid), tj = tid % 16;
+  double acc[TX][TM];
 #pragma unroll
-  for (int x = 0; x < TM; ++x)
+  for (int x = 0; x < TX; ++x)
 #pragma unroll
     for (int y = 0; y < TM; ++y) acc[x][y] = 0.0;
   double bacc = 0.0;
@@ -955,14 +973,13 @@ __device__ __forceinline__ void gather_C_fp64(AnaSmem<M>& sm, const InstDesc& I,
     __syncthreads();
     for (int qq = 0; qq < kc; ++qq) {
       const double r = sm.rc[qq];
-      double yi[TM], yj[TM];
+      double yi[TX], yj[TM];
 #pragma unroll
-      for (int x = 0; x < TM; ++x) {
-        yi[x] = r * Xc[qq * M + ti + 16 * x];
-        yj[x] = Xc[qq * M + tj + 16 * x];
-      }
+      for (int x = 0; x < TX; ++x) yi[x] = r * Xc[qq * M + ti + 16 * x];
 #pragma unroll
-      for (int x = 0; x < TM; ++x)
+      for (int y = 0; y < TM; ++y) yj[y] = Xc[qq * M + tj + 16 * y];
+#pragma unroll
+      for (int x = 0; x < TX; ++x)
 #pragma unroll
         for (int y = 0; y < TM; ++y) acc[x][y] += yi[x] * yj[y];
     }
@@ -971,7 +988,7 @@ __device__ __forceinline__ void gather_C_fp64(AnaSmem<M>& sm, const InstDesc& I,
     __syncthreads();
   }
 #pragma unroll
-  for (int x = 0; x < TM; ++x)
+  for (int x = 0; x < TX; ++x)
 #pragma unroll
     for (int y = 0; y < TM; ++y) put_A(sm, ti + 16 * x, tj + 16 * y, m, acc[x][y], I.a_diag, dbg);
   if (tid < M) sm.bvec[tid] = tid < m ? bacc : 0.0;
@@ -1048,7 +1065,7 @@ __device__ __forceinline__ void cholesky(AnaSmem<M>& sm) {
     int t = 0;
     for (int R = 0; R < nt; ++R)
       for (int Cc = 0; Cc <= R; ++Cc, ++t) {
-        if (t % 4 != w) continue;
+        if (t % (NT / 64) != w) continue;
         const int rb = c0 + 16 * (R + 1), cb = c0 + 16 * (Cc + 1);
         // the tile transposed, D[i][j] = B(rb + j, cb + i): a lane's accumulators
         // then lie along one column of the column-major B, consecutive across
@@ -1126,16 +1143,16 @@ __device__ __forceinline__ float group_sum(float v) {
 
 // True when every pair of columns of the current B satisfies
 // (b_i.b_j)^2 <= tol2 |b_i|^2 |b_j|^2, i.e. when a further sweep would not
-// rotate.  Each thread forms a TM x TM block of B^T B from LDS (the norms are
+// rotate.  Each thread forms a TX x TM block of B^T B from LDS (the norms are
 // the ones the sweep kept current).  Block-uniform result; ends with a barrier.
 // B: column c at B[c * LD], element type R.
 template <typename R, int M, int LD>
 __device__ __forceinline__ bool gram_converged(const R* B, const R* nrm, R tol2) {
-  constexpr int TM = AnaCfg<M>::TM;
-  const int tid = phase_tid(), ti = tid / 16, tj = tid % 16;
-  R g[TM][TM];
+  constexpr int TM = AnaCfg<M>::TM, TX = AnaCfg<M>::TX;
+  const int tid = phase_tid(), ti = AnaCfg<M>::row0(tid), tj = tid % 16;
+  R g[TX][TM];
 #pragma unroll
-  for (int x = 0; x < TM; ++x)
+  for (int x = 0; x < TX; ++x)
 #pragma unroll
     for (int y = 0; y < TM; ++y) g[x][y] = 0;
   // lane tj visits the rows from tj on (mod M): the 16 columns tj + 16 x that
@@ -1144,20 +1161,19 @@ __device__ __forceinline__ bool gram_converged(const R* B, const R* nrm, R tol2)
 #pragma unroll 2
   for (int r0 = 0; r0 < M; ++r0) {
     const int r = (r0 + tj) & (M - 1);
-    R u[TM], v[TM];
+    R u[TX], v[TM];
 #pragma unroll
-    for (int x = 0; x < TM; ++x) {
-      u[x] = B[(ti + 16 * x) * LD + r];
-      v[x] = B[(tj + 16 * x) * LD + r];
-    }
+    for (int x = 0; x < TX; ++x) u[x] = B[(ti + 16 * x) * LD + r];
 #pragma unroll
-    for (int x = 0; x < TM; ++x)
+    for (int y = 0; y < TM; ++y) v[y] = B[(tj + 16 * y) * LD + r];
+#pragma unroll
+    for (int x = 0; x < TX; ++x)
 #pragma unroll
       for (int y = 0; y < TM; ++y) g[x][y] = fma(u[x], v[y], g[x][y]);
   }
   bool bad = false;
 #pragma unroll
-  for (int x = 0; x < TM; ++x)
+  for (int x = 0; x < TX; ++x)
 #pragma unroll
     for (int y = 0; y < TM; ++y) {
       const int i = ti + 16 * x, j = tj + 16 * y;
@@ -1214,6 +1230,109 @@ __device__ __forceinline__ bool gram_converged_mfma64(const double* B, const dou
   return !__syncthreads_or(bad);
 }
 
+// One sweep at M = 128 (see jacobi_core): 64 pair slots of 8 lanes, 16 rows a
+// lane.  The same steps as below with the loops over groups and steps kept as
+// loops (unrolled, the 127 steps are four times the instruction cache), two
+// steps to a pass: after the even one the slots q and q ^ 1 exchange partners by
+// a lane swap, the odd one writes its partner back and loads the next pass's.  A
+// branch is taken by whole wavefronts, a lane whose pair does not rotate with
+// c = 1, sn = 0.
+// Lane e of a slot holds rows (e >> 1) + 4 (e & 1) + 8 u, so that a dot
+// product is summed as by four lanes of two partial sums each, and products are
+// fused where they are written so: the rotations, and with them the FP32 and
+// BF16 trajectories (which round X' every frame), do not depend on how many
+// threads share a column.
+template <typename R, int LD>
+__device__ __forceinline__ void sweep_128(__attribute__((address_space(3))) R* LB, __attribute__((address_space(3))) R* LN,
+                                          int* s_rot, R tol4, R trig4, int& big) {
+#pragma clang fp contract(off)
+  using LR = __attribute__((address_space(3))) R;
+  constexpr int RPT = 16;
+  const int tid = phase_tid(), q = tid / 8, e = tid % 8;
+  LR* const L0 = LB + (e >> 1) + 4 * (e & 1);
+  R xi[RPT], xa[RPT], xb[RPT], al = 0, ba = 0, bb = 0;
+  // A step of the pair (xi, xc), norms al and bc: put(u, v) takes the partner's
+  // values and end(n) its norm, on both sides of the branch, so that neither is
+  // a value the two sides have to agree on a register for.
+  auto step = [&](const R (&xc)[RPT], const R bc, auto&& put, auto&& end) {
+    R g = 0;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) g = fma(xi[u], xc[u], g);
+    const R gsum = group_sum<8>(g);
+    const R ab = al * bc, g2 = gsum + gsum, g4 = g2 * g2;
+    const bool rot = g4 > tol4 * ab;
+    if (__builtin_amdgcn_ballot_w64(rot) != 0) {
+      big = max(big, sign_word(fma(-trig4, ab, g4)));  // negative where no rotation
+      const R dd = bc - al;
+      const R q2 = fma(dd, dd, g4);
+      const R den = fma(q2, approx_rsq(q2), fabs(dd));
+      const R t = rot ? copysign((R)1, dd) * g2 * approx_rcp(den) : (R)0;
+      const R c = rot ? rsqrt_acc(fma(t, t, (R)1)) : (R)1;
+      const R sn = c * t;
+#pragma unroll
+      for (int u = 0; u < RPT; ++u) {
+        const R a = xi[u], b = xc[u];
+        const R sa = sn * a, sb = sn * b;
+        xi[u] = fma(c, a, -sb);
+        put(u, fma(c, b, sa));
+      }
+      al = fma(-t, gsum, al);
+      end(bc + t * gsum);
+      *s_rot = 1;
+    } else {
+#pragma unroll
+      for (int u = 0; u < RPT; ++u) put(u, xc[u]);
+      end(bc);
+    }
+  };
+  auto load = [&](int i, int j) {  // the pair slot's column and its first partner
+    const LR* bi = L0 + i * LD;
+    const LR* bj = L0 + j * LD;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+      xi[u] = bi[8 * u];
+      xa[u] = bj[8 * u];
+    }
+    al = LN[i];
+    ba = LN[j];
+  };
+  auto finish = [&](int i) {
+    LR* bi = L0 + i * LD;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) bi[8 * u] = xi[u];
+    if (e == 0) LN[i] = al;
+    __syncthreads();
+  };
+  {  // the first group's only step
+    LR* bj = L0 + (2 * q + 1) * LD;
+    load(2 * q, 2 * q + 1);
+    step(xa, ba, [&](int u, R v) { bj[8 * u] = v; }, [&](R n) { LN[2 * q + 1] = n; });
+    finish(2 * q);
+  }
+#pragma unroll 1
+  for (int h = 1; h < 7; ++h) {
+    const int low = 1 << h, i = ((q >> h) << (h + 1)) | (q & (low - 1)), kend = 2 << h;
+    load(i, i ^ low);
+#pragma unroll 1
+    for (int k = low; k < kend; k += 2) {
+      step(xa, ba, [&](int u, R v) { xb[u] = swap_lanes8(v); }, [&](R n) { bb = swap_lanes8(n); });
+      LR* bj = L0 + (i ^ (k + 1)) * LD;
+      step(xb, bb, [&](int u, R v) { bj[8 * u] = v; }, [&](R n) { LN[i ^ (k + 1)] = n; });
+      if (k + 2 < kend) {
+        // the next partner was written by a slot of this wavefront, except after
+        // every eighth step
+        if ((k + 2) % 8 == 0) __syncthreads();
+        else __asm__ volatile("" ::: "memory");
+        const LR* bn = L0 + (i ^ (k + 2)) * LD;
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) xa[u] = bn[8 * u];
+        ba = LN[i ^ (k + 2)];
+      }
+    }
+    finish(i);
+  }
+}
+
 // ---- a6 (second half): one-sided (Hestenes) Jacobi on the columns of L ------
 // L J = U Sigma with U the eigenvectors of A = L L^T and lambda = sigma^2, so
 // no rotation accumulator is needed; rounding scales with sqrt(lambda), and
@@ -1248,9 +1367,8 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
   const R trig = (R)0.2 * cbrt(tol);
   const R trig2 = trig * trig;
   const R tol4 = (R)4 * tol2, trig4 = (R)4 * trig2;
-  constexpr bool PREFETCH = C::RPT <= 16;
   // partners exchanged between slots q and q ^ 1 by a lane swap within 16-lane rows
-  constexpr bool SWAP = PREFETCH && TPP == 8;
+  constexpr bool SWAP = TPP == 8;
   // the step's column and norm accesses through LDS-typed pointers, so that
   // their addresses are 32-bit offsets (a generic pointer makes every partner
   // address a 64-bit multiply-add)
@@ -1263,7 +1381,8 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
     // progress-ordered issue (see k_analysis): the priority falls as the sweeps go by
     if (fair) set_issue_prio(sweeps < 3 ? 3 : sweeps < 5 ? 2 : sweeps < 6 ? 1 : 0);
     {
-      constexpr int TPC = NT / M;  // threads per column for the norms
+      constexpr int TPC = C::RT / M;  // threads per column for the norms
+      const bool on = C::RT == NT || tid < C::RT;
       const int c = tid / TPC, part = tid % TPC;
       // de Rijk's ordering: every sweep starts with the m columns sorted by
       // decreasing norm (the padded unit columns stay at m..M-1), which saves
@@ -1275,30 +1394,37 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
       R ss = 0;
       // column c's threads start at a row that shifts with c, so that the four
       // columns a pass of lanes reads fall in different banks
-      for (int j0 = 0; j0 < PER; ++j0) {
-        const R v = B[c * LD + part + TPC * ((j0 + c) & (PER - 1))];
-        ss = fma(v, v, ss);
-      }
+      // (M = 128: the addresses of its 64 loads formed anew, eight at a time; they
+      // would stay live over all sweeps)
+      int cn = c;
+      if constexpr (M == 128) __asm__ volatile("" : "+v"(cn));
+      if (on)
+#pragma unroll (M == 128 ? 8 : PER)
+        for (int j0 = 0; j0 < PER; ++j0) {
+          const R v = B[cn * LD + part + TPC * ((j0 + cn) & (PER - 1))];
+          ss = fma(v, v, ss);
+        }
       ss = group_sum<TPC>(ss);
-      if (part == 0) nrm[c] = ss;
+      if (on && part == 0) nrm[c] = ss;
       if (tid == 0) sm.s_rot = 0;  // last read before the previous sweep's closing barrier
       __syncthreads();
       R ahead = 0;  // columns ahead of c among this thread's share (exact small integers)
-      if (c < m)
+      if (on && c < m)
         for (int c2 = part; c2 < m; c2 += TPC) {
           const R n2 = nrm[c2];
           ahead += (n2 > ss || (n2 == ss && c2 < c)) ? (R)1 : (R)0;
         }
       ahead = group_sum<TPC>(ahead);
       const int rank = c < m ? (int)ahead : c;
-      if (__syncthreads_or(rank != c)) {
+      if (__syncthreads_or(on && rank != c)) {
         for (int k0 = 0; k0 < PER; k0 += CH) {
           // rows rotated by c within the pass, as in the norms: the reads then
           // avoid bank conflicts, and the writes (to the rank's column, same
           // rows) mostly do
           R v[CH];
+          if (on)
 #pragma unroll
-          for (int k = 0; k < CH; ++k) v[k] = B[c * LD + part + TPC * (k0 + ((k + c) & (CH - 1)))];
+            for (int k = 0; k < CH; ++k) v[k] = B[cn * LD + part + TPC * (k0 + ((k + cn) & (CH - 1)))];
           // every read of this pass's rows (rows TPC k0 .. TPC (k0 + CH) - 1, which no
           // other pass touches) is done before any column moves; the sweep reads
           // the moved columns after the barrier that follows
@@ -1308,14 +1434,18 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
           // across the barrier and raised the kernel's register count
           int cw = c;
           __asm__ volatile("" : "+v"(cw));
+          if (on)
 #pragma unroll
-          for (int k = 0; k < CH; ++k) B[rank * LD + part + TPC * (k0 + ((k + cw) & (CH - 1)))] = v[k];
+            for (int k = 0; k < CH; ++k) B[rank * LD + part + TPC * (k0 + ((k + cw) & (CH - 1)))] = v[k];
         }
-        if (part == 0) nrm[rank] = ss;
+        if (on && part == 0) nrm[rank] = ss;
         __syncthreads();  // the moved columns and norms before the sweep reads them
       }
     }
     int big = INT_MIN;
+    if constexpr (M == 128) {
+      sweep_128<R, LD>(LB, LN, &sm.s_rot, tol4, trig4, big);
+    } else
 #pragma unroll
     for (int h = 0; (1 << h) < M; ++h) {
       const int i = ((q >> h) << (h + 1)) | (q & ((1 << h) - 1));
@@ -1323,12 +1453,10 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
       R xi[C::RPT];
       R al = 0;
       // One step k: pair (i, i ^ k) with the partner column in xc (norm bc).
-      // With PREFETCH the next step's partner arrives in xn (norm bn) before
+      // The next step's partner arrives in xn (norm bn) before
       // this step rotates the lower column (registers only), so that its
       // latency overlaps that arithmetic instead of stalling the next dot
       // product; two register sets alternate between consecutive steps.
-      // (M = 128 holds 32 rows per lane: a second set would spill, so there
-      // each step loads its own partner.)
       // Between an even step k and k + 1 the slots exchange partners in pairs
       // (slot q takes the column slot q ^ 1 just rotated), so with SWAP the
       // rotated partner goes to its next slot by a lane swap and not through
@@ -1346,11 +1474,6 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
         const bool stale = SWAP && (k & 1) == 1 && k > (1 << h);
         R c = 1, sn = 0;
         bool rot = false;
-        if (!PREFETCH && active) {
-#pragma unroll
-          for (int t = 0; t < C::RPT; ++t) xc[t] = LB[jj * LD + sub + t * TPP];
-          bc = LN[jj];
-        }
         if (active) {
           R g0 = 0, g1 = 0;
 #pragma unroll
@@ -1443,7 +1566,7 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
         // the others only keep the compiler from moving LDS accesses across.
         if ((k + 1) % PSW == 0 && k + 1 < kend) __syncthreads();
         else __asm__ volatile("" ::: "memory");
-        if (PREFETCH && active && !swp && k + 1 < kend) {
+        if (active && !swp && k + 1 < kend) {
           const LR* bk = LB + (iv ^ (k + 1)) * LD;
 #pragma unroll
           for (int t = 0; t < C::RPT; ++t) xn[t] = bk[sub + t * TPP];
@@ -1454,26 +1577,22 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
           for (int u = 0; u < C::RPT; ++u) xi[u] = c * xi[u] - sn * xc[u];
         }
       };
-      R xa[C::RPT], xb[PREFETCH ? C::RPT : 1];
+      R xa[C::RPT], xb[C::RPT];
       R ba = 0, bb = 0;
       if (active) {
         const R* b0 = B + (i ^ (1 << h)) * LD;  // the group's first partner
 #pragma unroll
         for (int t = 0; t < C::RPT; ++t) {
           xi[t] = B[i * LD + sub + t * TPP];
-          if (PREFETCH) xa[t] = b0[sub + t * TPP];
+          xa[t] = b0[sub + t * TPP];
         }
         al = nrm[i];
-        if (PREFETCH) ba = nrm[i ^ (1 << h)];
+        ba = nrm[i ^ (1 << h)];
       }
-      if constexpr (PREFETCH) {
 #pragma unroll
-        for (int k = 1 << h; k < kend; k += 2) {
-          step(k, xa, ba, xb, bb);
-          if (k + 1 < kend) step(k + 1, xb, bb, xa, ba);
-        }
-      } else {
-        for (int k = 1 << h; k < kend; ++k) step(k, xa, ba, xa, ba);
+      for (int k = 1 << h; k < kend; k += 2) {
+        step(k, xa, ba, xb, bb);
+        if (k + 1 < kend) step(k + 1, xb, bb, xa, ba);
       }
       if (active) {
 #pragma unroll
@@ -1569,7 +1688,7 @@ __device__ __forceinline__ int jacobi(AnaSmem<M>& sm, int m, bool& converged, bo
 }
 
 // Product of the transposed M x M matrix in LDS (column c at Bm[c * LDB ..]) with a
-// vector, by TPC = NT / M lanes per output reduced by DPP: lane group o = tid / TPC,
+// vector, by TPC = RT / M lanes per output reduced by DPP: lane group o = tid / TPC,
 // lane part = tid % TPC takes every TPC-th term (two accumulators), and every
 // lane of the group gets the sum.  With the column stride LDB the lanes of a
 // wavefront read distinct banks in both forms.
@@ -1578,7 +1697,7 @@ template <typename SM>
 __device__ __forceinline__ double colsum(const SM& sm, const double* v, int o, int part) {
   using C = typename SM::C;
   constexpr int M = C::M;
-  constexpr int TPC = C::NT / M, PER = M / TPC, LDB = C::LDB;
+  constexpr int TPC = C::RT / M, PER = M / TPC, LDB = C::LDB;
   double t0 = 0.0, t1 = 0.0;
 #pragma unroll 8
   for (int k = 0; k < PER; k += 2) {
@@ -1591,7 +1710,7 @@ __device__ __forceinline__ double colsum(const SM& sm, const double* v, int o, i
 template <int M>
 __device__ __forceinline__ double rowsum(const AnaSmem<M>& sm, const double* z, int o, int part) {
   using C = AnaCfg<M>;
-  constexpr int TPC = C::NT / M, PER = M / TPC, LDB = C::LDB;
+  constexpr int TPC = C::RT / M, PER = M / TPC, LDB = C::LDB;
   double t0 = 0.0, t1 = 0.0;
 #pragma unroll 8
   for (int k = 0; k < PER; k += 2) {
@@ -1611,12 +1730,13 @@ __device__ __forceinline__ double rowsum(const AnaSmem<M>& sm, const double* z, 
 // and wbar += U Lambda^-1 U^T res.  Uses pcol[0] (residual) and pcol[1].
 template <int M>
 __device__ __forceinline__ void refine_wbar(AnaSmem<M>& sm, const double* __restrict__ Ag, int m) {
-  constexpr int TPC = AnaCfg<M>::NT / M, PER = M / TPC;
+  constexpr int TPC = AnaCfg<M>::RT / M, PER = M / TPC;
   const int tid = phase_tid(), o = tid / TPC, part = tid % TPC;
+  const bool on = AnaCfg<M>::RT == AnaCfg<M>::NT || tid < AnaCfg<M>::RT;
   double* res = sm.pcol[0];
   double* z = sm.pcol[1];
   __syncthreads();  // wbar complete
-  {
+  if (on) {
     // (A wbar)_o: row o of the symmetric A; entry (o, c) is packed at row
     // max(o, c), column min(o, c).  Padded rows and columns read entry 0 and
     // are masked by arithmetic (res is zero past m anyway).
@@ -1638,12 +1758,12 @@ __device__ __forceinline__ void refine_wbar(AnaSmem<M>& sm, const double* __rest
     if (part == 0) res[o] = o < m ? sm.bvec[o] - t : 0.0;
   }
   __syncthreads();
-  {
+  if (on) {
     const double t = colsum(sm, res, o, part);
     if (part == 0) z[o] = o < m ? t / sm.lam[o] : 0.0;
   }
   __syncthreads();
-  {
+  if (on) {
     const double w = rowsum<M>(sm, z, o, part);
     if (part == 0 && o < m) sm.wbar[o] += w;
   }
@@ -1661,27 +1781,28 @@ __device__ __forceinline__ void refine_wbar(AnaSmem<M>& sm, const double* __rest
 // wbar below 1e-8 and 2e-5 on the 15x15 (m = 100) and 84x84 workloads.
 template <int M>
 __device__ __forceinline__ void refine_wbar_lj(AnaSmem<M>& sm, int m) {
-  constexpr int TPC = AnaCfg<M>::NT / M;
+  constexpr int TPC = AnaCfg<M>::RT / M;
   const int tid = phase_tid(), o = tid / TPC, part = tid % TPC;
+  const bool on = AnaCfg<M>::RT == AnaCfg<M>::NT || tid < AnaCfg<M>::RT;
   double* z = sm.pcol[0];
   double* res = sm.pcol[1];
   __syncthreads();  // wbar complete
-  {
+  if (on) {
     const double t = colsum(sm, sm.wbar, o, part);
     if (part == 0) z[o] = o < m ? sm.lam[o] * t : 0.0;
   }
   __syncthreads();
-  {
+  if (on) {
     const double t = rowsum<M>(sm, z, o, part);
     if (part == 0) res[o] = o < m ? sm.bvec[o] - t : 0.0;
   }
   __syncthreads();
-  {
+  if (on) {
     const double t = colsum(sm, res, o, part);
     if (part == 0) z[o] = o < m ? t / sm.lam[o] : 0.0;
   }
   __syncthreads();
-  {
+  if (on) {
     const double w = rowsum<M>(sm, z, o, part);
     if (part == 0 && o < m) sm.wbar[o] += w;
   }
@@ -1695,14 +1816,15 @@ template <int P, int M>
 __device__ __forceinline__ void transform(AnaSmem<M>& sm, const InstDesc& I, int l, double* dbg) {
   const int m = I.m;
   using C = AnaCfg<M>;
-  constexpr int NT = C::NT, LDB = C::LDB, TM = C::TM;
-  const int tid = phase_tid(), ti = tid / 16, tj = tid % 16;
+  constexpr int NT = C::NT, LDB = C::LDB, TM = C::TM, TX = C::TX;
+  const int tid = phase_tid(), ti = C::row0(tid), tj = tid % 16;
+  const bool on = C::RT == NT || tid < C::RT;
   // debug: shader-clock stamps inside this phase (after U, after wbar, after its refinement)
   auto substamp = [&](int k) {
     if (dbg && threadIdx.x == 0) dbg[2 * m * m + m + 10 + k] = (double)clock64();
   };
-  {
-    constexpr int TPC = NT / M;
+  if (on) {
+    constexpr int TPC = C::RT / M;
     const int c = tid / TPC, part = tid % TPC;
     double ss = 0.0;
     for (int r = part; r < M; r += TPC) { const double v = sm.Bm[c * LDB + r]; ss += v * v; }
@@ -1721,16 +1843,16 @@ __device__ __forceinline__ void transform(AnaSmem<M>& sm, const InstDesc& I, int
   substamp(0);
   {
     // wbar = U Lambda^-1 U^T b
-    constexpr int TPC = NT / M;
+    constexpr int TPC = C::RT / M;
     const int o = tid / TPC, part = tid % TPC;
-    const double t = colsum(sm, sm.bvec, o, part);
-    if (part == 0) {
+    const double t = on ? colsum(sm, sm.bvec, o, part) : 0.0;
+    if (on && part == 0) {
       sm.zv[o] = o < m ? t / sm.lam[o] : 0.0;
       sm.nrm[o] = o < m ? sqrt((double)(m - 1) / sm.lam[o]) : 0.0;
     }
     __syncthreads();
-    const double w = rowsum<M>(sm, sm.zv, o, part);
-    if (part == 0) sm.wbar[o] = o < m ? w : 0.0;
+    const double w = on ? rowsum<M>(sm, sm.zv, o, part) : 0.0;
+    if (on && part == 0) sm.wbar[o] = o < m ? w : 0.0;
   }
   __syncthreads();
   substamp(1);
@@ -1793,27 +1915,26 @@ __device__ __forceinline__ void transform(AnaSmem<M>& sm, const InstDesc& I, int
           }
     }
   } else {
-    double tacc[TM][TM];
+    double tacc[TX][TM];
 #pragma unroll
-    for (int x = 0; x < TM; ++x)
+    for (int x = 0; x < TX; ++x)
 #pragma unroll
       for (int y = 0; y < TM; ++y) tacc[x][y] = 0.0;
     for (int c = 0; c < m; ++c) {
       const double sc = sm.nrm[c];
-      double ui[TM], uj[TM];
+      double ui[TX], uj[TM];
 #pragma unroll
-      for (int x = 0; x < TM; ++x) {
-        ui[x] = sm.Bm[c * LDB + ti + 16 * x] * sc;
-        uj[x] = sm.Bm[c * LDB + tj + 16 * x];
-      }
+      for (int x = 0; x < TX; ++x) ui[x] = sm.Bm[c * LDB + ti + 16 * x] * sc;
 #pragma unroll
-      for (int x = 0; x < TM; ++x)
+      for (int y = 0; y < TM; ++y) uj[y] = sm.Bm[c * LDB + tj + 16 * y];
+#pragma unroll
+      for (int x = 0; x < TX; ++x)
 #pragma unroll
         for (int y = 0; y < TM; ++y) tacc[x][y] += ui[x] * uj[y];
     }
     __syncthreads();
 #pragma unroll
-    for (int x = 0; x < TM; ++x)
+    for (int x = 0; x < TX; ++x)
 #pragma unroll
       for (int y = 0; y < TM; ++y) {
         const int i = ti + 16 * x, j = tj + 16 * y;
@@ -2187,7 +2308,7 @@ __device__ __forceinline__ void analyse_item(AnaSmem<M>& sm, const InstDesc* __r
 // priorities made the batches slower (serving -11 % with this one), so the
 // server launches with fair = 0.
 template <int P, int M>
-__global__ __launch_bounds__(256) void k_analysis(const InstDesc* __restrict__ tab,
+__global__ __launch_bounds__(AnaCfg<M>::NT) void k_analysis(const InstDesc* __restrict__ tab,
                                                   BatchHdr* __restrict__ hdr, int cls, int fair) {
   __shared__ AnaSmem<M> sm;
   __shared__ int s_next;
@@ -2707,7 +2828,7 @@ __global__ __launch_bounds__(PolyCfg<M>::NT, M <= 32 ? 4 : M <= 64 ? 3 : 2) void
 // (letkf_debug_domain).  No frame runs it.
 // ----------------------------------------------------------------------------
 template <int M>
-__global__ __launch_bounds__(256) void k_lambda(const InstDesc* __restrict__ inst, int l) {
+__global__ __launch_bounds__(AnaCfg<M>::NT) void k_lambda(const InstDesc* __restrict__ inst, int l) {
   using C = AnaCfg<M>;
   __shared__ AnaSmem<M> sm;
   const InstDesc& I = *inst;
@@ -3642,7 +3763,7 @@ void launch_analysis(int cls, int grid, int kinds, const InstDesc* tab, BatchHdr
 #undef LETKF_LAUNCH_POLY
   }
   if (!(kinds & kKindJacobi)) return;
-#define LETKF_LAUNCH_ANA(K) hipLaunchKernelGGL(K, dim3(grid), dim3(256), 0, s, tab, hdr, cls, fair)
+#define LETKF_LAUNCH_ANA(K) hipLaunchKernelGGL(K, dim3(grid), dim3(cls % 4 == 3 ? AnaCfg<128>::NT : 256), 0, s, tab, hdr, cls, fair)
   LETKF_ANA_KERNEL(cls, LETKF_LAUNCH_ANA);
 #undef LETKF_LAUNCH_ANA
 }
@@ -3652,14 +3773,14 @@ void launch_lambda(int cls, const InstDesc* inst, int domain, hipStream_t s) {
   if (sz == 0) hipLaunchKernelGGL(k_lambda<16>, dim3(1), dim3(256), 0, s, inst, domain);
   else if (sz == 1) hipLaunchKernelGGL(k_lambda<32>, dim3(1), dim3(256), 0, s, inst, domain);
   else if (sz == 2) hipLaunchKernelGGL(k_lambda<64>, dim3(1), dim3(256), 0, s, inst, domain);
-  else hipLaunchKernelGGL(k_lambda<128>, dim3(1), dim3(256), 0, s, inst, domain);
+  else hipLaunchKernelGGL(k_lambda<128>, dim3(1), dim3(AnaCfg<128>::NT), 0, s, inst, domain);
 }
 
 int analysis_blocks_per_cu(int cls) {
   if (cls == kBigClass) return 1;
   int n = 0;
   hipError_t e = hipSuccess;
-#define LETKF_OCC(K) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, 256, 0)
+#define LETKF_OCC(K) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, cls % 4 == 3 ? AnaCfg<128>::NT : 256, 0)
   LETKF_ANA_KERNEL(cls, LETKF_OCC);
 #undef LETKF_OCC
   return (e == hipSuccess && n > 0) ? n : 1;
