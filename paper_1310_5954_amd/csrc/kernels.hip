@@ -2924,14 +2924,14 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
   return t;
 }
 
-// grid (upper tiles ti <= tj, items), 8 wavefronts: one 16 x 16 tile of C per
+// grid (upper tiles ti <= tj, items), 16 wavefronts: one 16 x 16 tile of C per
 // workgroup, the observations in blocks of 16 dealt over the wavefronts (block
-// b to wavefront b mod 8), four k-steps of v_mfma_f64_16x16x4f64 each, and
+// b to wavefront b mod 16), four k-steps of v_mfma_f64_16x16x4f64 each, and
 // their partial tiles summed in LDS.  91 workgroups at m = 197, against the ten
 // 64 x 64 tiles of the former split, whose 51 chunks in sequence were a latency
-// chain (306 us on the global 32 x 32 domain).  A diagonal tile also forms its
+// chain (306 us on the global 32 x 32 domain; 8 wavefronts: 28.3 us, 16: 18.2).  A diagonal tile also forms its
 // 16 entries of b.
-constexpr int kGramWaves = 8, kGramObs = 1024;
+constexpr int kGramWaves = 16, kGramObs = 2048;
 __global__ __launch_bounds__(64 * kGramWaves) void k_big_gram(const InstDesc* __restrict__ tab,
                                                               const BatchHdr* __restrict__ hdr, int cls) {
   __shared__ int rowT[kGramObs];
@@ -3182,50 +3182,65 @@ __global__ __launch_bounds__(256) void k_big_slow(const InstDesc* __restrict__ t
 }
 
 // grid (items), 1024 threads: wbar = Z (Z b) and one refinement step with A; the
-// columns of Z (and of A) dealt over four thread groups, rows over a group.
+// columns of Z (and of A) dealt over eight thread groups, a thread two rows of
+// each.  One workgroup's reads of the matrix, five times, are what it takes:
+// 16 bytes a lane, sixteen columns in flight (eight bytes and eight columns over
+// four groups: 33.6 -> 24.1 us at m = 197).  Rows past m read the padded matrix; those past the padding
+// read entries that no sum uses.
 __global__ __launch_bounds__(1024) void k_big_wbar(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
                                                    int cls) {
-  __shared__ double x[kBigM], part[4][kBigM];
+  __shared__ double x[kBigM];
+  __shared__ alignas(16) double part[8][kBigM];
   const ClassBatch& cb = hdr->cls[cls];
   if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
   const BigDom D = big_dom(tab, cb, blockIdx.x);
   const InstDesc& I = *D.I;
-  const int m = I.m, mp = (m + 15) & ~15, tid = threadIdx.x, r = tid % kBigM, q = tid / kBigM;
+  const int m = I.m, mp = (m + 15) & ~15, tid = threadIdx.x, q = tid / 128, r2 = 2 * (tid % 128);
   const int n = kIsqrtPlan[D.f[3]].n;
   const double* Z = D.mat(3 + (n - 1) % 2);
-  auto product = [&](const double* B) {  // x <- B x; returns row r on every group
-    double t0 = 0.0, t1 = 0.0;
-    if (r < mp) {
-      const int c1 = (q + 1) * (mp / 4);
-      int c = q * (mp / 4);
-#pragma unroll 8
-      for (; c + 1 < c1; c += 2) {
-        t0 = fma(gload(B + (size_t)c * kBigM + r), x[c], t0);
-        t1 = fma(gload(B + (size_t)(c + 1) * kBigM + r), x[c + 1], t1);
+  auto product = [&](const double* B) {  // x <- B x; returns row tid (the first 256 threads)
+    f64x2 t0 = {0.0, 0.0}, t1 = {0.0, 0.0};
+    if (r2 < mp) {
+      const int c0 = q * (mp / 8), c1 = c0 + mp / 8;  // an even number of columns
+      for (int c = c0; c < c1; c += 16) {
+        f64x2 z[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) z[u] = gload((const f64x2*)(B + (size_t)(c + u < c1 ? c + u : c0) * kBigM + r2));
+#pragma unroll
+        for (int u = 0; u < 16; u += 2)
+          if (c + u < c1) {
+            t0 = x[c + u] * z[u] + t0;
+            t1 = x[c + u + 1] * z[u + 1] + t1;
+          }
       }
     }
-    part[q][r] = t0 + t1;
+    *(f64x2*)&part[q][r2] = t0 + t1;
     __syncthreads();
-    const double t = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
-    if (q == 0) x[r] = t;
+    double t = 0.0;
+    if (tid < kBigM) {
+      t = ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])) +
+          ((part[4][tid] + part[5][tid]) + (part[6][tid] + part[7][tid]));
+      x[tid] = t;
+    }
     __syncthreads();
     return t;
   };
-  if (q == 0) x[r] = r < mp ? D.v[r] : 0.0;
+  if (tid < kBigM) x[tid] = tid < mp ? D.v[tid] : 0.0;
   __syncthreads();
   product(Z);
   const double w0 = product(Z);
   const double aw = product(D.A);
-  if (q == 0) x[r] = r < m ? D.v[r] - aw : 0.0;
+  if (tid < kBigM) x[tid] = tid < m ? D.v[tid] - aw : 0.0;
   __syncthreads();
   product(Z);
   const double w1 = product(Z);
-  if (q == 0) D.v[kBigM + r] = r < m ? w0 + w1 : 0.0;
+  if (tid < kBigM) D.v[kBigM + tid] = tid < m ? w0 + w1 : 0.0;
   if (double* dbg = big_dbg(D)) {
-    if (q == 0) x[r] = r < m ? w0 + w1 : 0.0;
+    if (tid < kBigM) x[tid] = tid < m ? w0 + w1 : 0.0;
     __syncthreads();
     const double sc = sqrt((double)(m - 1));
-    for (int k = q; k < m; k += 4)
+    const int r = tid % kBigM;
+    for (int k = tid / kBigM; k < m; k += 4)
       if (r < m) dbg[(size_t)m * m + m + (size_t)k * m + r] = fma(sc, Z[(size_t)r * kBigM + k], x[k]);
   }
   if (tid == 0) {
