@@ -86,7 +86,7 @@ def analysis_flops(m: int, dmap, sweeps_total: int, solves: int, frames: int, po
       Jacobi per sweep: column norms 2m^2 + one dot per pair 2m * m(m-1)/2,
       rotations 6m per pair * m(m-1)/2 in every sweep but the last (check) one,
       lambda/U 3m^2, wbar 4m^2, W 2m^3, update 2 n_l m^2 + 2 n_l m.
-    poly: the FP64 and FP32 paths, whose A^(-1/2) takes sweeps_total matrix
+    poly: the paths on polynomial stages, whose A^(-1/2) takes sweeps_total matrix
     products of 2m^3 instead."""
     e = np.diff(dmap.est_ptr).astype(float)
     s = np.diff(dmap.obs_ptr).astype(float)

@@ -121,13 +121,20 @@ inline int variant_of(int prec, bool fp32_rot) { return fp32_rot ? 3 : prec; }
 // whose trajectory a change of rounding leaves alone.  Three kinds do not.  The
 // BF16 paths round X' to BF16 every frame, so that two solvers agreeing to 1e-7
 // flip different roundings and stand 1e-3 apart after four to eight frames.  On
-// the FP32 path the rounding of C, amplified by kappa(A), does the same at a
-// smaller scale: 1e-6 to 1e-5 after 16 frames for m <= 64, but 4e-5 after two for
-// m > 64.  A filter that observes the previous instant (H = [0 D]) is unstable
-// on window maps (a CPU replay of 33 x 33 grows a perturbation 7 times a frame).
-// Those keep the solver, and so the trajectories, they have had.
-inline bool uses_poly(int prec, int m, int obs_instant) {
-  return obs_instant == 0 && (prec == 0 || (prec == 1 && m <= 64));
+// the FP32 path the rounding of C and of the state, amplified by kappa(A) and by
+// the filter, does the same at a smaller scale, the more the fewer slopes a
+// domain has.  After 7 to 16 frames two solvers stood 1.3e-5 or less apart on all
+// of 65 maps whose observations are tapered and whose domains average at least two
+// slopes per member and per state row (n_sub >= m n_dom and >= 2 n_est, the sums
+// over the domains of the subapertures and of the estimated actuators); with
+// fewer slopes 2e-5 to 1e-4 on one map in three, without a taper up to 5e-5, and
+// for m > 64 4e-5 after two frames.  A filter that observes the previous instant
+// (H = [0 D]) is unstable on window maps (a CPU replay of 33 x 33 grows a
+// perturbation 7 times a frame).  Those keep the solver, and so the
+// trajectories, they have had.
+inline bool uses_poly(int prec, int m, int obs_instant, int64_t n_dom, int64_t n_sub, int64_t n_est, bool tapered) {
+  if (obs_instant != 0) return false;
+  return prec == 0 || (prec == 1 && m <= 64 && tapered && n_sub >= m * n_dom && n_sub >= 2 * n_est);
 }
 constexpr int kKindJacobi = 1, kKindPoly = 2;  // kinds of instances in a launch
 

@@ -394,7 +394,8 @@ __global__ __launch_bounds__(1024) void k_finish(const InstDesc* __restrict__ ta
 }
 
 // ----------------------------------------------------------------------------
-// a4-a8: per-domain analysis, one 256-thread workgroup (4 wavefronts) per domain.
+// a4-a8: per-domain analysis, one workgroup per domain (256 threads; 512 where
+// its matrices fill the LDS of a CU, M = 128).
 //
 // P selects the contraction path: 0 = FP64, 1 = FP32 MFMA
 // (v_mfma_f32_16x16x4f32), 2 = BF16 MFMA (v_mfma_f32_16x16x32_bf16) with FP32

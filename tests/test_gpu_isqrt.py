@@ -45,12 +45,13 @@ def test_T_over_condition_numbers(m, scale):
     check_T(m, scale)
 
 
-@pytest.mark.parametrize("precision", [FP64, FP32])
-@pytest.mark.parametrize("m", [16, 64, 128])
-def test_batch_of_both_solvers_equals_the_plain_path(m, precision):
+# config 2, FP32: enough slopes a member and a state row for the stages up to m = 48 or so
+@pytest.mark.parametrize("m,precision,config", [(16, FP64, 1), (64, FP64, 1), (128, FP64, 1), (16, FP32, 1), (128, FP32, 1),
+                                                 (16, FP32, 2), (32, FP32, 2), (33, FP32, 2), (64, FP32, 2)])
+def test_batch_of_both_solvers_equals_the_plain_path(m, precision, config):
     """Instances that observe phi_k and phi_{k-1} share a class but not an
     analysis kernel; served together they give the plain path's states."""
-    case = build_case(1, m=m)
+    case = build_case(config, m=m)
     problems = [Problem.from_case(case, obs_instant=o) for o in (0, 1, 0)]
     plain = []
     for p in problems:
