@@ -828,7 +828,7 @@ def main() -> int:
         """Algorithmic FP64-dominated work of one analysis launch over its
         HIP-event duration; HBM traffic from the committed counter summary."""
         ana_ms = run["kernel_ms"][1]
-        flops = analysis_flops(case.m, case.dmap, run["sweeps"], run["solves"], K, path_name != "bf16") / K
+        flops = analysis_flops(case.m, case.dmap, run["sweeps"], run["solves"], K, path_name == "fp64") / K
         achieved = flops / (ana_ms * 1e-3) / 1e12
         es = 8 if path_name == "fp64" else 4
         traffic = measured_traffic(TRAFFIC_FILES[path_name], kernel_hash(), run["tuning"]) if args.workload == 84 else None

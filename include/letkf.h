@@ -79,11 +79,9 @@ extern "C" {
  * W = [(m-1) A^-1]^(1/2) and wbar are FP64 on every path; the paths differ in
  * the storage of the ensemble and slopes and in the two dense contractions,
  * C = Y'^T diag(r) Y' and X' T.
- * On LETKF_FP64, and on LETKF_FP32 with m <= 64 where the observations are
- * tapered and the domains average at least two slopes per member and per state
- * row, A^(-1/2) comes from minimax
+ * On LETKF_FP64 A^(-1/2) comes from minimax
  * polynomial stages (matrix products on FP64 MFMA) chosen by a bound of A's
- * condition number, exact to rounding.  LETKF_BF16, the other LETKF_FP32 and
+ * condition number, exact to rounding.  LETKF_BF16, LETKF_FP32 and
  * instances with m <= 128 and obs_instant 1 solve the eigenproblem (Cholesky,
  * one-sided Jacobi rotations in FP64 unless LETKF_FLAG_FP32_ROTATIONS is given)
  * to a path's tolerance.

@@ -116,26 +116,20 @@ inline int variant_of(int prec, bool fp32_rot) { return fp32_rot ? 3 : prec; }
 
 // Which analysis kernel serves an instance (m <= 128): A^(-1/2) by polynomial
 // stages (k_analysis_poly) or through the Jacobi eigensolver (k_analysis).  The
-// stages agree with the eigensolver to rounding and take 0.47 of its launch time
-// in FP64 at 84 x 84, m = 64 (134 against 286 us), so they serve every instance
+// stages agree with the eigensolver to rounding and take 0.43 of its launch time
+// in FP64 at 84 x 84, m = 64 (123 against 286 us), so they serve every instance
 // whose trajectory a change of rounding leaves alone.  Three kinds do not.  The
 // BF16 paths round X' to BF16 every frame, so that two solvers agreeing to 1e-7
 // flip different roundings and stand 1e-3 apart after four to eight frames.  On
 // the FP32 path the rounding of C and of the state, amplified by kappa(A) and by
-// the filter, does the same at a smaller scale, the more the fewer slopes a
-// domain has.  After 7 to 16 frames two solvers stood 1.3e-5 or less apart on all
-// of 65 maps whose observations are tapered and whose domains average at least two
-// slopes per member and per state row (n_sub >= m n_dom and >= 2 n_est, the sums
-// over the domains of the subapertures and of the estimated actuators); with
-// fewer slopes 2e-5 to 1e-4 on one map in three, without a taper up to 5e-5, and
-// for m > 64 4e-5 after two frames.  A filter that observes the previous instant
-// (H = [0 D]) is unstable on window maps (a CPU replay of 33 x 33 grows a
+// the filter, does the same at a smaller scale: 3e-7 to 1e-5 after 16 frames on
+// most maps with m <= 64, but up to 1e-4 with few slopes per domain or hard
+// window edges, 4e-5 after two frames for m > 64, and by instance the error
+// against 64 bits moves by half either way.  A filter that observes the previous
+// instant (H = [0 D]) is unstable on window maps (a CPU replay of 33 x 33 grows a
 // perturbation 7 times a frame).  Those keep the solver, and so the
 // trajectories, they have had.
-inline bool uses_poly(int prec, int m, int obs_instant, int64_t n_dom, int64_t n_sub, int64_t n_est, bool tapered) {
-  if (obs_instant != 0) return false;
-  return prec == 0 || (prec == 1 && m <= 64 && tapered && n_sub >= m * n_dom && n_sub >= 2 * n_est);
-}
+inline bool uses_poly(int prec, int obs_instant) { return prec == 0 && obs_instant == 0; }
 constexpr int kKindJacobi = 1, kKindPoly = 2;  // kinds of instances in a launch
 
 inline int class_of(int padded_m, int prec, bool fp32_rot) {

@@ -48,12 +48,6 @@ struct Problem {  // validated, host-side copy of the create arguments
   int sum_e() const { return est_ptr.back(); }
   int sum_s() const { return obs_ptr.back(); }
   int zrows() const { return 2 * sum_e(); }
-  // whether k_analysis_poly analyses it (m <= 128)
-  bool poly() const {
-    bool tapered = false;
-    for (double t : obs_taper) tapered |= t < 1.0;
-    return uses_poly(prec, m, obs_instant, n_dom, sum_s(), sum_e(), tapered);
-  }
   size_t piston_terms() const {  // sum over actuators of (covering domains)^2
     std::vector<int> k(n_act, 0);
     for (int a : est_act) ++k[a];

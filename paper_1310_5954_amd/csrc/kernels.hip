@@ -478,17 +478,27 @@ template <int M> struct AnaCfg : StageCfg<M, M <= 64 ? 256 : 512> {
   }();
 };
 
-template <int M> struct AnaSmem {
+// The chunk staging of the gather and the update (phase-dependent type), and the
+// vectors of the transform between the two: in one place at M = 128, where LDS
+// has no room for both.
+template <int M> struct AnaStage {
+  alignas(16) unsigned char stage[AnaCfg<M>::STAGE_BYTES];
+  double lam[M], zv[M], pcol[2][M];
+};
+template <> struct AnaStage<128> {
+  union {
+    alignas(16) unsigned char stage[AnaCfg<128>::STAGE_BYTES];
+    struct {
+      double lam[128], zv[128], pcol[2][128];
+    };
+  };
+};
+template <int M> struct AnaSmem : AnaStage<M> {
   using C = AnaCfg<M>;
+  using AnaStage<M>::stage;
   static constexpr int LDA = C::LDB;                  // the gathers' stride of A
   static __device__ double pad(double) { return 1.0; }  // diagonal of A past m
   double Bm[M * C::LDB];                              // A, then U, then T (row-major)
-  union {
-    alignas(16) unsigned char stage[C::STAGE_BYTES];  // chunk staging of the gather and the update (phase-dependent type)
-    struct {                                          // the transform's vectors, between the two
-      double lam[M], zv[M], pcol[2][M];
-    };
-  };
   double rc[32], dc[32];
   double bvec[M], nrm[M], wbar[M];
   int perm[M <= 64 ? M : 1];                          // FP64, M <= 64: A's symmetric permutation
@@ -505,7 +515,7 @@ template <int M> struct PolyCfg : StageCfg<M, M <= 64 ? 256 : 512> {
   static constexpr int keep(int T) { return T <= 3 ? T : T == 4 ? 2 : T == 5 ? 4 : T == 6 ? 3 : T == 7 ? 0 : 1; }
   static constexpr size_t STAGE_BYTES = [] {
     size_t x = 0;
-    for (size_t v : {(size_t)M * B::LDKD * 8, (size_t)M * B::LDKF * 4, (size_t)16 * (M + 1) * 8, (size_t)B::KR * (M + 1) * 4,
+    for (size_t v : {(size_t)M * B::LDKD * 8, (size_t)16 * (M + 1) * 8,
                      (size_t)B::NT * 8, M == 64 ? (size_t)B::NT * 8 * 4 * 2 - (size_t)M * (LDB - LDA) * 8 : 0})  // parked Z, behind A
       x = v > x ? v : x;
     return (x + 15) & ~size_t(15);
@@ -1399,12 +1409,16 @@ __device__ __forceinline__ int jacobi_core(AnaSmem<M>& sm, int m, R* B, R* nrm, 
       // would stay live over all sweeps)
       int cn = c;
       if constexpr (M == 128) __asm__ volatile("" : "+v"(cn));
-      if (on)
-#pragma unroll (M == 128 ? 8 : PER)
-        for (int j0 = 0; j0 < PER; ++j0) {
-          const R v = B[cn * LD + part + TPC * ((j0 + cn) & (PER - 1))];
-          ss = fma(v, v, ss);
-        }
+      auto term = [&](int j0) {
+        const R v = B[cn * LD + part + TPC * ((j0 + cn) & (PER - 1))];
+        ss = fma(v, v, ss);
+      };
+      if constexpr (M < 128) {
+        for (int j0 = 0; j0 < PER; ++j0) term(j0);
+      } else if (on) {
+#pragma unroll 8
+        for (int j0 = 0; j0 < PER; ++j0) term(j0);
+      }
       ss = group_sum<TPC>(ss);
       if (on && part == 0) nrm[c] = ss;
       if (tid == 0) sm.s_rot = 0;  // last read before the previous sweep's closing barrier
@@ -2230,14 +2244,16 @@ __device__ __forceinline__ void sort_diag(AnaSmem<M>& sm, int m) {
 template <int P, int M>
 __device__ __forceinline__ void analyse_item(AnaSmem<M>& sm, const InstDesc* __restrict__ tab, const ClassBatch& cb, int item, bool fair) {
   using C = AnaCfg<M>;
-  const int eb = __builtin_amdgcn_readfirstlane(find_entry(cb.dom_off, cb.n, item));
+  // uniform values, in scalar registers where vector ones are short (M = 128); at
+  // M = 32 that took 7 % longer in the Jacobi steps
+  auto uni = [](int x) { return M == 128 ? __builtin_amdgcn_readfirstlane(x) : x; };
+  const int eb = uni(find_entry(cb.dom_off, cb.n, item));
   const InstDesc& I = tab[cb.inst[eb]];
-  // uniform values, kept in scalar registers
-  const int l = __builtin_amdgcn_readfirstlane(I.order[item - cb.dom_off[eb]]);
-  const int est_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l]), e = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 1]);
-  const int obs_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 2]), s = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 3]);
+  const int l = uni(I.order[item - cb.dom_off[eb]]);
+  const int est_off = uni(I.dom[4 * l]), e = uni(I.dom[4 * l + 1]);
+  const int obs_off = uni(I.dom[4 * l + 2]), s = uni(I.dom[4 * l + 3]);
   const int m = I.m;
-  const int cur = __builtin_amdgcn_readfirstlane(I.st->cur);
+  const int cur = uni(I.st->cur);
   double* dbg = I.dbg ? I.dbg + (size_t)l * (2 * m * m + m + kDbgTail) : nullptr;
   // debug: shader-clock stamps at the phase boundaries (after each phase's barrier)
   auto stamp = [&](int k) {
@@ -2317,11 +2333,11 @@ __global__ __launch_bounds__(AnaCfg<M>::NT) void k_analysis(const InstDesc* __re
   const int total = cb.dom_off[cb.n];
   int item = blockIdx.x;
   while (item < total) {
-    // FP64 and FP32 batches may hold instances of the other kernel
-    if (P >= 2 || !tab[cb.inst[find_entry(cb.dom_off, cb.n, item)]].poly) analyse_item<P, M>(sm, tab, cb, item, fair != 0);
+    // FP64 batches may hold instances of the other kernel
+    if (P != 0 || !tab[cb.inst[find_entry(cb.dom_off, cb.n, item)]].poly) analyse_item<P, M>(sm, tab, cb, item, fair != 0);
     if (threadIdx.x == 0) s_next = (int)gridDim.x + (int)atomicAdd(&cb.next, 1u);
     __syncthreads();
-    item = __builtin_amdgcn_readfirstlane(s_next);
+    item = M == 128 ? __builtin_amdgcn_readfirstlane(s_next) : s_next;
     __syncthreads();
   }
 }
@@ -2674,7 +2690,7 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
 // wbar = A^-1 b = Z (Z b) (with one refinement step through A itself on the
 // FP64 path) and T = sqrt(m-1) Z + wbar 1^T, row-major in Bm (T[k][j] at
 // Bm[k LDB + j], zero outside m x m), from the wavefronts' columns of Z.
-template <int P, int M, int T>
+template <int M, int T>
 __device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int l, const f64x4 (&Z)[T], double* dbg) {
   using B = IsqrtBlock<M, T>;
   using C = PolyCfg<M>;
@@ -2707,7 +2723,7 @@ __device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int
     __syncthreads();
   }
   substamp(1);
-  if constexpr (P == 0) {
+  {
     residual_wbar<M>(sm, I.Ascr + (size_t)l * tri_size(m), m);
     const double x = solve(sm.pcol);
     if (part == 0) sm.wbar[o] += x;
@@ -2730,7 +2746,7 @@ __device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int
   __syncthreads();
 }
 
-template <int P, int M>
+template <int M>
 __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __restrict__ tab, const ClassBatch& cb, int item) {
   const int eb = __builtin_amdgcn_readfirstlane(find_entry(cb.dom_off, cb.n, item));
   const InstDesc& I = tab[cb.inst[eb]];
@@ -2753,9 +2769,8 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
   }
 
   constexpr int ld = PolySmem<M>::LDA;
-  if constexpr (P == 0) gather_C_fp64_mfma(sm, I, obs_off, s, dbg);
-  else gather_C_fp32(sm, I, obs_off, s, dbg);
-  if constexpr (P == 0) {
+  gather_C_fp64_mfma(sm, I, obs_off, s, dbg);
+  {
     // the domain's A, kept for the refinement of wbar (the stages overwrite
     // it): the lower triangle of the m x m matrix, packed by rows (row i at
     // i (i + 1) / 2), rows spread over the wavefronts and coalesced over lanes
@@ -2782,7 +2797,7 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
         gatomic_add(&I.st->sweeps, (unsigned long long)products);
         gatomic_add(&I.st->solves, 1ull);
       }
-      finish_T<P, M, T>(sm, I, l, Z, dbg);
+      finish_T<M, T>(sm, I, l, Z, dbg);
     };
     const int t = (m + 15) / 16;
     if constexpr (M == 64) {
@@ -2798,14 +2813,13 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
     }
   }
   stamp(4);
-  if constexpr (P == 0) update_fp64(sm, I, est_off, e, cur);
-  else update_mfma<P>(sm, I, est_off, e, cur);
+  update_fp64(sm, I, est_off, e, cur);
   stamp(5);
 }
 
 // Persistent like k_analysis, with a work counter of its own (a batch may hold
 // instances of both kernels).
-template <int P, int M>
+template <int M>
 __global__ __launch_bounds__(PolyCfg<M>::NT, M <= 32 ? 4 : M <= 64 ? 3 : 2) void k_analysis_poly(const InstDesc* __restrict__ tab,
                                                   BatchHdr* __restrict__ hdr, int cls) {
   __shared__ PolySmem<M> sm;
@@ -2814,7 +2828,7 @@ __global__ __launch_bounds__(PolyCfg<M>::NT, M <= 32 ? 4 : M <= 64 ? 3 : 2) void
   const int total = cb.dom_off[cb.n];
   int item = blockIdx.x;
   while (item < total) {
-    if (tab[cb.inst[find_entry(cb.dom_off, cb.n, item)]].poly) analyse_poly<P, M>(sm, tab, cb, item);
+    if (tab[cb.inst[find_entry(cb.dom_off, cb.n, item)]].poly) analyse_poly<M>(sm, tab, cb, item);
     if (threadIdx.x == 0) s_next = (int)gridDim.x + (int)atomicAdd(&cb.next_poly, 1u);
     __syncthreads();
     item = __builtin_amdgcn_readfirstlane(s_next);
@@ -3754,19 +3768,13 @@ void launch_big_lambda(int items, int m_max, const InstDesc* tab, BatchHdr* hdr,
   hipLaunchKernelGGL(k_big_lambda, dim3(items), dim3(256), 0, s, tab, hdr, cls);
 }
 
-#define LETKF_POLY_KERNEL(cls, FN)                                  \
-  do {                                                              \
-    const int prec_ = (cls) / 4, sz_ = (cls) % 4;                   \
-    if (prec_ == 0) {                                               \
-      if (sz_ == 0) FN((k_analysis_poly<0, 16>));                   \
-      else if (sz_ == 1) FN((k_analysis_poly<0, 32>));              \
-      else if (sz_ == 2) FN((k_analysis_poly<0, 64>));              \
-      else FN((k_analysis_poly<0, 128>));                           \
-    } else {                                                        \
-      if (sz_ == 0) FN((k_analysis_poly<1, 16>));                   \
-      else if (sz_ == 1) FN((k_analysis_poly<1, 32>));              \
-      else FN((k_analysis_poly<1, 64>));                            \
-    }                                                               \
+#define LETKF_POLY_KERNEL(cls, FN)             \
+  do {                                         \
+    const int sz_ = (cls) % 4;                 \
+    if (sz_ == 0) FN(k_analysis_poly<16>);     \
+    else if (sz_ == 1) FN(k_analysis_poly<32>); \
+    else if (sz_ == 2) FN(k_analysis_poly<64>); \
+    else FN(k_analysis_poly<128>);             \
   } while (0)
 
 void launch_analysis(int cls, int grid, int kinds, const InstDesc* tab, BatchHdr* hdr, hipStream_t s, int fair) {

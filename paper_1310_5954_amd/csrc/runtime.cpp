@@ -185,7 +185,7 @@ Layout make_layout(const Problem& P) {
   {
     const size_t M = padded_members(P.m);
     L.Ascr = (P.prec == LETKF_FP64 && M <= 128) ? take((size_t)P.n_dom * tri_size(P.m) * 8) : 0;
-    L.park = M == 128 && P.poly() ? take((size_t)std::min(P.n_dom, kParkSlots) * kParkDoubles * 8) : 0;
+    L.park = M == 128 && uses_poly(P.prec, P.obs_instant) ? take((size_t)std::min(P.n_dom, kParkSlots) * kParkDoubles * 8) : 0;
   }
   if (P.flags & LETKF_FLAG_DEBUG) {
     L.dbg = take((size_t)P.n_dom * (2 * m * m + m + kDbgTail) * 8);
@@ -444,7 +444,7 @@ int upload_instance(const Problem& P, const Layout& L, char* ws, const double* X
   D.dom_sweeps = (uint32_t*)(ws + L.dom_sweeps);
   D.Ascr = L.Ascr ? (double*)(ws + L.Ascr) : nullptr;
   D.park = L.park ? (double*)(ws + L.park) : nullptr;
-  D.poly = P.poly() ? 1 : 0;
+  D.poly = uses_poly(P.prec, P.obs_instant) ? 1 : 0;
   D.dbg = L.dbg ? (double*)(ws + L.dbg) : nullptr;
   D.dbg_sweeps = L.dbg_sweeps ? (int32_t*)(ws + L.dbg_sweeps) : nullptr;
   D.st = (InstState*)(ws + L.state);
