@@ -80,8 +80,8 @@ extern "C" {
  * the storage of the ensemble and slopes and in the two dense contractions,
  * C = Y'^T diag(r) Y' and X' T.
  * On LETKF_FP64 A^(-1/2) comes from minimax
- * polynomial stages (matrix products on FP64 MFMA) chosen by a bound of A's
- * condition number, exact to rounding.  LETKF_BF16, LETKF_FP32 and
+ * polynomial stages (matrix products on FP64 MFMA) that end when a norm of
+ * what is left certifies them, X' W as accurate as by Cholesky and SVD.  LETKF_BF16, LETKF_FP32 and
  * instances with m <= 128 and obs_instant 1 solve the eigenproblem (Cholesky,
  * one-sided Jacobi rotations in FP64 unless LETKF_FLAG_FP32_ROTATIONS is given)
  * to a path's tolerance.
@@ -258,8 +258,8 @@ int letkf_debug_placement(letkf_handle* h, int32_t domain, uint32_t* hw_id_out, 
 int letkf_debug_substeps(letkf_handle* h, int32_t domain, double* cycles_out, void* stream);
 
 /* Number of domains of the last analysis whose eigensolver hit the sweep cap, or
- * whose condition number passed the polynomial stages' range (4e15, 1e14 for
- * m > 128; 0 when all converged); waits for the stream. */
+ * whose A the polynomial stages found not finite or numerically indefinite (0 when
+ * all converged); waits for the stream. */
 int letkf_unconverged_domains(letkf_handle* h, int32_t* count, void* stream);
 
 /* The means the last plain-path frame wrote (host [n_act] each, either may

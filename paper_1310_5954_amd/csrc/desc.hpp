@@ -8,6 +8,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 
 namespace letkf {
@@ -25,7 +26,7 @@ constexpr int kBigClass = 4 * kVariants;
 
 struct InstState {           // mutated on the device by the forecast kernel
   int32_t cur;               // ring slot holding phi_k (the other holds phi_{k-1})
-  int32_t unconverged;       // domains of the last analysis that hit the Jacobi sweep cap or passed the stages' condition range
+  int32_t unconverged;       // domains of the last analysis that hit the Jacobi sweep cap or whose stages did not get there
   uint64_t frame;            // forecasts done so far (Philox counter word 2..3)
   unsigned long long sweeps; // Jacobi sweeps (poly: matrix products of the stages) summed over every domain solve
   unsigned long long solves; // domain solves
@@ -38,6 +39,7 @@ struct InstDesc {
   int32_t poly;              // 1: k_analysis_poly analyses the instance, 0: k_analysis (uses_poly)
   double sigma_v;
   double a_diag;             // (m-1)/rho
+  double sqrt_m1;            // (m-1)^(1/2)
   uint64_t seed;
   void* ens;                 // [2][n_act][m]   storage type (double for FP64, float otherwise)
   void* Yp;                  // [p][m]          slope perturbations D X'_phi
@@ -52,7 +54,7 @@ struct InstDesc {
   const int32_t* order;      // [n_dom] domains by decreasing estimated cost
   const int32_t* est_act;    // [sum e]
   const int32_t* obs_row;    // [2 sum s]: slope row of each observation (x rows then y rows per domain)
-  const double* obs_r;       // [2 sum s]: taper * R^-1 of each observation
+  const double* obs_r;       // [2 sum s]: taper * R^-1 of each observation (null where no kernel reads it: reads_weights)
   const double* obs_sr;      // [2 sum s]: its square root (the weight of the staged rows of C)
   const int32_t* mptr;       // [n_act+1] merge CSR: covering (domain, position) entries per actuator
   const int32_t* mrow;       // [2*entries]: Z row of the phi_k copy and of the phi_{k-1} copy
@@ -67,6 +69,7 @@ struct InstDesc {
   double* bigA;              // m > 128: [n_dom][256][256] A
   double* bigW;              // m > 128: [n_dom][5][256][256] M, M^2, P and two Z of the stages (column-major)
   double* bigv;              // m > 128: [n_dom][5][256] b, wbar, spare, partial sums of |A^2|_F^2, spare
+  const uint8_t* guess;      // poly: [n_dom] first entry of the stages (stage_guess)
   int32_t* bigf;             // m > 128: [n_dom][4] debug Jacobi: converged, rounds that rotated, sweeps; table row of the stages
   uint32_t* dom_sweeps;      // [n_dom] Jacobi sweeps (poly: products) of each domain, summed over every analysis
   double* Ascr;              // FP64, m <= 128: [n_dom][m(m+1)/2] each domain's A (lower triangle packed by rows), for refining wbar
@@ -116,9 +119,10 @@ inline int variant_of(int prec, bool fp32_rot) { return fp32_rot ? 3 : prec; }
 
 // Which analysis kernel serves an instance (m <= 128): A^(-1/2) by polynomial
 // stages (k_analysis_poly) or through the Jacobi eigensolver (k_analysis).  The
-// stages agree with the eigensolver to rounding and take 0.43 of its launch time
-// in FP64 at 84 x 84, m = 64 (123 against 286 us), so they serve every instance
-// whose trajectory a change of rounding leaves alone.  Three kinds do not.  The
+// stages are as accurate as the eigensolver on X' W (isqrt_stages) and take 0.47
+// of its launch time in FP64 at 84 x 84, m = 64 (135 against 286 us), so they
+// serve every instance whose trajectory a change of rounding leaves alone.
+// Three kinds do not.  The
 // BF16 paths round X' to BF16 every frame, so that two solvers agreeing to 1e-7
 // flip different roundings and stand 1e-3 apart after four to eight frames.  On
 // the FP32 path the rounding of C and of the state, amplified by kappa(A) and by
@@ -131,6 +135,44 @@ inline int variant_of(int prec, bool fp32_rot) { return fp32_rot ? 3 : prec; }
 // trajectories, they have had.
 inline bool uses_poly(int prec, int obs_instant) { return prec == 0 && obs_instant == 0; }
 constexpr int kKindJacobi = 1, kKindPoly = 2;  // kinds of instances in a launch
+
+// Whether a kernel reads the observations' weights themselves and not only their
+// square roots: the FP64 gathers of m > 64, but for k_analysis_poly's.
+inline bool reads_weights(int prec, int padded_m, int obs_instant) {
+  return prec == 0 && (padded_m > 128 || (padded_m == 128 && !uses_poly(prec, obs_instant)));
+}
+
+// Entry of the polynomial stages (kappa <= 2^(entry / 4)) for what A's condition
+// number may be off the vector of ones, from the domain's observation weights r
+// and the number of actuators that its slopes touch.  With n slopes against m - 1
+// directions the smallest eigenvalue of C off the ones goes as
+// (1 - sqrt((m-1) / n))^2 (the lower edge of a sample covariance); with fewer
+// slopes than directions nothing better than the bound of (m-1)/rho is to be had
+// (the last entry stands for that).  Slopes of small weight count too, at that
+// weight (taken at 1, 1/8, 1/64 and 1/512 of the largest, fractions below).  The
+// actuators touched, less one (piston), bound the rank in the same way.  The
+// factors 96 and 16 are what the slopes' own spectrum adds: their quotient was
+// 30 to 100 over the von Karman domains of 8 to 128 subapertures, 20 to 60 in
+// the frames after the first.  A guess only (a certificate decides when the
+// stages end), but one within a factor 10 of the truth keeps the rounding to
+// that condition number's, below that of Cholesky + SVD, where the bound's
+// stages cost one to three digits.
+constexpr int kStageEntries = 208;
+inline int stage_guess(int m, const double* r, int count, int touched) {
+  auto edge = [&](double n) {  // 0: no more than the directions
+    const double u = 1.0 - std::sqrt((m - 1) / n);
+    return n > m - 1 ? u * u : 0.0;
+  };
+  double most = 0.0, kappa = HUGE_VAL, scale = 1.0;
+  for (int q = 0; q < count; ++q) most = std::fmax(most, r[q]);
+  for (int k = 0; k < 4 && most > 0.0; ++k, scale *= 8.0) {
+    double n = 0.0;
+    for (int q = 0; q < count; ++q) n += std::fmin(r[q] / most * scale, 1.0);
+    kappa = std::fmin(kappa, 96.0 * scale / edge(n));
+  }
+  kappa = std::fmax(kappa, 16.0 / edge(touched - 1));
+  return (int)std::fmin(kStageEntries, std::ceil(4.0 * std::log2(kappa)));
+}
 
 inline int class_of(int padded_m, int prec, bool fp32_rot) {
   if (padded_m > 128) return kBigClass;  // validated to be FP64

@@ -5,14 +5,29 @@
 A is scaled so that its eigenvalues lie in [1/kappa, 1].  With M_0 = A and
 Z_0 = I, a stage takes P = q(M), Z <- P Z, M <- P P M; x = sqrt(eigenvalue of
 M) maps to x q(x^2).  A stage's q is the minimax polynomial of that map to 1 on
-the interval [l, 1] the previous stages left (Remez exchange), divided by
-1 + E (E its error) so that the next interval is again [l', 1]; the last stage
-is not divided and ends with E below TOL, so Z = A^(-1/2) to TOL.  The degrees
-(in M) are the non-decreasing sequence over {2, 4, 6} (1 too for the last) of
-fewest matrix products, after degree 4 while l < 2^-13:
-a stage forms its powers and q (0, 1, 2 or 3 products), P Z (none in the first
-stage) and, unless it is the last, P (P M) (2).  The last stage's coefficients
-are in powers of R = M - I, whose norm is small there.
+the interval [l, 1] the stages before it left (Remez exchange), divided by
+1 + E (E its error), so that the next interval is again [l', 1], less TOP, so
+that no rounding takes an eigenvalue past 1, where the next stages' slopes (50
+and more) would carry it away.  An eigenvalue below l^2 stays in (0, 1) and
+gains at least as much as one at l^2, so a stage for too small a kappa costs
+further stages and nothing else.
+
+The last stage maps to 1 within TOL without the division.  Its polynomials are
+in powers of R = M - I, of degree 2, 4 or 6, for ||R|| <= kIsqrtRho; the
+kernels choose by the bound ||R^2||_F^(1/2) >= ||R||, up to m^(1/4) times the
+norm, so the stages before it aim at a MARGIN-th of that.
+
+kIsqrtPlan: row r serves kappa <= 2^(r/2) (row 0: 1.05) by stages of degree 4,
+one at least, and the last.  A stage forms M^2 and q (2 products in all; 1 and 3
+for degrees 2 and 6), P Z (not in the first stage) and, unless it is the last,
+P (P M) (2).  Degree 4 gains most per product until little is left to gain;
+stages of degree 2 or 6 before the last would save a product here and there,
+at a branch per stage whose registers the kernel does not have, and degree 6
+at a digit (its coefficients sum to 3e4 in size, those of degree 4 to 1e3).
+
+kIsqrtStage4: the same stages singly, entry i - 1 for kappa <= 2^(i/4); `next` is
+the entry number of the interval it leaves, 0 where that is near enough to 1
+for a last stage of degree 4.
 """
 import sys
 from functools import lru_cache
@@ -21,9 +36,10 @@ import mpmath as mp
 import numpy as np
 
 mp.mp.dps = 50
-TOL = mp.mpf("1e-15")
-ROWS, MAX_STAGES, MAX_DEG = 105, 11, 6   # row r serves kappa <= 2^(r/2)
-POWERS = {1: 0, 2: 1, 4: 2, 6: 3}
+TOL, TOP = mp.mpf("2e-16"), mp.mpf("1e-10")
+ROWS, MAX_STAGES, MAX_DEG, ENTRIES, MARGIN = 105, 12, 6, 208, 3
+PRODUCTS = {2: 1, 4: 2, 6: 3}  # to form q(M)
+RHO = {2: mp.mpf("2.7e-5"), 4: mp.mpf("3.3e-3"), 6: mp.mpf("2.5e-2")}
 
 
 @lru_cache(maxsize=None)
@@ -58,72 +74,66 @@ def minimax(l, k):
     return c, max(abs(1 - sum(c[i] * t ** (2 * i + 1) for i in range(n))) for t in x)
 
 
-def last_stage(l, k):
-    """Coefficients in R = M - 1, or None when degree k leaves more than TOL."""
-    if 1 - l < mp.mpf("1e-12"):  # the binomial series of (1 + R)^(-1/2)
-        c = [mp.binomial(mp.mpf(-1) / 2, j) for j in range(k + 1)]
-        return c if (1 - l * l) ** (k + 1) < TOL else None
-    c, e = minimax(l, k)
-    if e > TOL:
-        return None
+@lru_cache(maxsize=None)
+def last_stage(k):
+    """Coefficients in R = M - 1 for eigenvalues of R in [-rho, 0]."""
+    c, e = minimax(mp.sqrt(1 - RHO[k]), k)
+    assert e <= TOL, (k, e)
     return [sum(c[i] * mp.binomial(i, j) for i in range(j, k + 1)) for j in range(k + 1)]
 
 
-def sequences(cost, first=True, least=2, depth=MAX_STAGES):
-    """Non-decreasing degree sequences of that many products, the last stage's after a comma."""
-    for k in POWERS:
-        if POWERS[k] + (0 if first else 1) == cost:
-            yield (k,)
-    if depth > 1:
-        for k in (2, 4, 6):
-            spent = POWERS[k] + (0 if first else 1) + 2
-            if k >= least and spent < cost:
-                for rest in sequences(cost - spent, False, k, depth - 1):
-                    yield (k,) + rest
+def stage(l, k):
+    """Coefficients of a stage from [l, 1], and the l it leaves."""
+    c, e = minimax(l, k)
+    f = (1 - TOP) / (1 + e)
+    return [v * f for v in c], (1 - e) * f
 
 
-def stages(l, degrees):
-    """The stages of that sequence from the interval [l, 1], or None when it leaves more than TOL."""
-    got = []
-    for k in degrees[:-1]:
-        c, e = minimax(l, k)
-        if e < mp.mpf("1e-13"):
-            return None
-        got.append((k, [v / (1 + e) for v in c]))
-        l = (1 - e) / (1 + e)
-    c = last_stage(l, degrees[-1])
-    return None if c is None else got + [(degrees[-1], c)]
+def last_degree(l, degrees=(2, 4, 6)):
+    return next((k for k in degrees if 1 - l * l <= RHO[k] / MARGIN), None)
+
+
+def sequence(l):
+    """The stages from [l, 1] as (degree, coefficients), and their products."""
+    got, x = [], l
+    while True:
+        c, x = stage(x, 4)
+        got.append((4, c))
+        end = last_degree(x)
+        if end:
+            return got + [(end, last_stage(end))], 5 * len(got) - 1 + PRODUCTS[end] + 1
 
 
 def main():
     out = ["// Polynomial stages of A^(-1/2) by condition number: written by isqrt_plan.py, which says how",
-           "// they are found.  Row r serves kappa <= 2^(r/2); deg[] ends at the first 0; the last stage's",
-           "// coefficients are in powers of M - I, the others' in powers of M.",
+           "// they are found.  Row r of kIsqrtPlan serves kappa <= 2^(r/2); deg[] ends at the first 0; the last",
+           "// stage's coefficients are in powers of M - I, the others' in powers of M.  Entry i - 1 of",
+           "// kIsqrtStage4 serves kappa <= 2^(i/4) and leaves the interval of entry `next` (0: the last stage's).",
            "#pragma once", "", "namespace letkf {", "", f"constexpr int kIsqrtRows = {ROWS};",
-           f"constexpr int kIsqrtStages = {MAX_STAGES};", "",
+           f"constexpr int kIsqrtStages = {MAX_STAGES};", f"constexpr int kIsqrtEntries = {ENTRIES};", "",
            "struct IsqrtRow {", "  int n, products;", f"  int deg[{MAX_STAGES}];",
-           f"  double c[{MAX_STAGES}][{MAX_DEG + 2}];", "};", "",
+           f"  double c[{MAX_STAGES}][{MAX_DEG + 2}];", "};", "struct IsqrtStage {", "  int next;", "  double c[5];", "};", "",
            "static __device__ const IsqrtRow kIsqrtPlan[kIsqrtRows] = {"]
-    prods = 1
     for r in range(ROWS):
-        l = mp.mpf(2) ** (mp.mpf(-r) / 4) if r else mp.mpf(2) ** mp.mpf("-0.0001")
-        head, got = [], None
-        while l < mp.mpf(2) ** -13:  # far from 1 degree 4 gains most per product
-            c, e = minimax(l, 4)
-            head.append((4, [v / (1 + e) for v in c]))
-            l = (1 - e) / (1 + e)
-        tail = 1 if head else max(prods, 1)
-        while got is None:  # the count does not fall as kappa grows
-            got = next((g for g in (stages(l, d) for d in sequences(tail, not head, 4 if head else 2)) if g), None)
-            tail += got is None
-        prods = tail + (5 * len(head) - 1 if head else 0)
-        got = head + got
+        l = mp.mpf(2) ** (mp.mpf(-r) / 4) if r else 1 / mp.sqrt(mp.mpf("1.05"))
+        got, products = sequence(l)
         deg = [k for k, _ in got] + [0] * (MAX_STAGES - len(got))
-        out.append(f"    {{{len(got)}, {prods}, {{{', '.join(map(str, deg))}}}, {{")
+        out.append(f"    {{{len(got)}, {products}, {{{', '.join(map(str, deg))}}}, {{")
         for k, c in got:
             out.append("        {" + ", ".join(mp.nstr(v, 20) for v in c) + "},")
         out.append("    }},")
-        print(r, "kappa %.3g" % 2 ** (r / 2), deg, prods, file=sys.stderr, flush=True)
+        print(r, "kappa %.3g" % 2 ** (r / 2), deg, products, file=sys.stderr, flush=True)
+    out += ["};", "", "static __device__ const IsqrtStage kIsqrtStage4[kIsqrtEntries] = {"]
+    for i in range(1, ENTRIES + 1):
+        c, low = stage(mp.mpf(2) ** (mp.mpf(-i) / 8), 4)
+        nxt = 0 if last_degree(low, (4,)) else int(mp.ceil(-8 * mp.log(low, 2)))
+        assert nxt < i
+        out.append(f"    {{{nxt}, {{" + ", ".join(mp.nstr(v, 20) for v in c) + "}},")
+    out += ["};", "", "// the last stage: degree 2, 4, 6 for ||M - I|| <= kIsqrtRho",
+            "constexpr double kIsqrtRho[3] = {" + ", ".join(mp.nstr(RHO[k], 6) for k in (2, 4, 6)) + "};",
+            "static __device__ const double kIsqrtLast[3][7] = {"]
+    for k in (2, 4, 6):
+        out.append("    {" + ", ".join(mp.nstr(v, 20) for v in last_stage(k)) + "},")
     out += ["};", "", "}  // namespace letkf"]
     print("\n".join(out))
 

@@ -23,6 +23,8 @@
 
 namespace letkf {
 
+static_assert(kIsqrtEntries == kStageEntries, "stage_guess's range is the table's");
+
 // ----------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11) and one Box-Muller normal per counter.
 // ----------------------------------------------------------------------------
@@ -524,11 +526,11 @@ template <int M> struct PolyCfg : StageCfg<M, M <= 64 ? 256 : 512> {
 template <int M> struct PolySmem {
   using C = PolyCfg<M>;
   static constexpr int LDA = C::LDA;
-  // past m the diagonal of A is its smallest eigenvalue, which leaves the spectrum's bounds alone
+  // diagonal of A past m (the stages put the mean eigenvalue there)
   static __device__ double pad(double a_diag) { return a_diag; }
   alignas(16) double Bm[M * C::LDB];                  // A, the stages' left factors, Z, then T (row-major)
   alignas(16) unsigned char stage[C::STAGE_BYTES];    // chunk staging (phase-dependent type)
-  double rc[32], dc[32];
+  double rc[32];
   double bvec[M], zv[M], wbar[M], pcol[M];
   __device__ double* red() { return (double*)stage; }  // NT partial sums, aliases the staging area
 };
@@ -1104,7 +1106,7 @@ __device__ __forceinline__ void cholesky(AnaSmem<M>& sm) {
   __syncthreads();
 }
 
-// 1/sqrt(x) for x in [1, 2] (no zero, infinity or denormal input): the
+// 1/sqrt(x) for x in [1, 2] (or any x but zero, infinity and denormals): the
 // hardware estimate e0 (relative error ~2^-23) refined by one third-order step
 // c = c0 (1 + e/2 + 3e^2/8), e = 1 - x c0^2, which leaves a relative error of
 // order e^3, below the rounding of the result.
@@ -2373,15 +2375,14 @@ __device__ __forceinline__ void residual_wbar(PolySmem<M>& sm, const double* __r
 }
 
 // ---- a6/a7: A^(-1/2) by polynomial stages on the FP64 matrix cores ----------
-// W = [(m-1) A^-1]^(1/2) needs no eigenvectors.  A = (m-1)/rho I + C has its
-// smallest eigenvalue bounded below by (m-1)/rho, so with an upper bound beta
-// the spectrum's interval is known, and Z = A^(-1/2) comes from a few minimax
-// polynomial stages (isqrt_plan.hpp: 17-20 matrix products at the condition
-// numbers 1e4-6e4 of the ELT maps):
+// W = [(m-1) A^-1]^(1/2) needs no eigenvectors: Z = A^(-1/2) comes from a few
+// minimax polynomial stages (isqrt_plan.hpp: 16 matrix products at the condition
+// numbers 1e2-1e3 that the 15 x 15 map has off the vector of ones, 17-18 and
+// 20-22 at the 84 x 84 and 100 x 100 maps' 4e3 and 6e4):
 //   P = q(M),  Z <- P Z,  M <- P (P M),   M_0 = A, Z_0 = I.
-// beta = |A^2|_F^(1/2), from the A^2 that the first stage needs anyway (1.05 to
-// 1.4 times the largest eigenvalue there); the first stage's coefficients
-// carry the scaling, so A itself is never rounded again.
+// A's upper bound is beta = |A^2|_F^(1/2), from the A^2 that the first stage needs
+// anyway (1.05 to 1.4 times the largest eigenvalue there); the first stage's
+// coefficients carry the scaling by it (isqrt_scale).
 //
 // Layout: wavefront w owns the columns 16 w .. 16 w + 15 of every matrix, in
 // the accumulator registers of v_mfma_f64_16x16x4f64.  Register v of lane l
@@ -2393,13 +2394,11 @@ __device__ __forceinline__ void residual_wbar(PolySmem<M>& sm, const double* __r
 // LD = M + 2: the 8 lanes of a 16-byte column write then fall in 32 banks.
 // Every factor is used as computed, never mirrored: the products are
 // polynomials in A taken from the left, and their rounding stays commuting with
-// A to first order (forcing symmetry cost a factor 10 in a CPU replay, where
-// this form matches Cholesky + SVD at every condition number of the table:
-// 1e-13 at 1e4, 6e-12 at 1e6, 4e-10 at 6e7).
+// A to first order (forcing symmetry cost a factor 10 in a CPU replay).
 // T = ceil(m / 16) tiles take part: at m = 48 a product is 36 MFMAs a wavefront
 // instead of the 64 of the padded M = 64 (an odd last tile has its rows in
 // plain order and loads of its own), at m = 100 seven tiles instead of eight.
-// 40 x 40, m = 48: analysis 82 -> 69 us; 100 x 100, m = 100: 1004 -> 840 us.
+// 100 x 100, m = 100: analysis 1004 -> 840 us (stages of the time).
 template <int M, int T_>
 struct IsqrtBlock {
   static constexpr int T = T_, LD = M + 2, Q = T / 2, ODD = T % 2;
@@ -2408,6 +2407,14 @@ struct IsqrtBlock {
   static constexpr __device__ __forceinline__ int row(int t, int v, int g) {
     if (ODD && t == T - 1) return 16 * t + g + 4 * v;
     return 32 * (t / 2) + 2 * (g + 4 * v) + (t & 1);
+  }
+  // which of its 4 T elements (4 t + v) a thread holds on the diagonal, -1 for none
+  static constexpr __device__ __forceinline__ int diagonal(int tid) {
+    const int c = column(tid), g = (tid & 63) >> 4;
+    if (c >= 16 * T) return -1;  // the wavefront that runs along (isqrt_stages)
+    if (ODD && c >= 16 * (T - 1)) return g == (c & 3) ? 4 * (T - 1) + ((c & 15) >> 2) : -1;
+    const int y = (c & 31) >> 1;
+    return g == (y & 3) ? 4 * (2 * (c >> 5) + (c & 1)) + (y >> 2) : -1;
   }
   // acc = S X (ADD: acc += S X) for the wavefront's columns; S: column c at S[c * LD]
   template <bool ADD = false>
@@ -2507,18 +2514,94 @@ struct IsqrtBlock {
   }
 };
 
-// Z = A^(-1/2) from A in Bm (stride M + 2): each wavefront ends with its
-// columns of Z in Z.  Returns the matrix products done; in_table: A's condition bound was
-// within the table (past it, or with a NaN in A, the last row runs all the same
-// and the domain counts as unconverged).
+// Sum and maximum over a wavefront, in scalar registers (shuffles would keep a
+// register of lane addresses each).
+__device__ __forceinline__ double wave_sum(double v) {
+  v = group_sum<16>(v);
+  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, dpp_f64<0xB1>(v));
+  v = fmax(v, dpp_f64<0x4E>(v));
+  v = fmax(v, dpp_f64<0x141>(v));
+  v = fmax(v, dpp_f64<0x140>(v));
+  return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
+}
+
+// A uniform value in a scalar register, where the compiler, knowing it uniform,
+// would keep it in a vector one across the stages.  (The compiler does not look
+// into the block: the first nop is for a vector register written just before,
+// the second for a vector memory access by the scalar right after.)
+__device__ __forceinline__ int to_scalar(int x) {
+  int s;
+  __asm__("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 4" : "=s"(s) : "v"(x));
+  return s;
+}
+
+// Entry (from 1) of the stages for eigenvalues in [1/kappa, 1].
+__device__ __forceinline__ int isqrt_entry(float kappa) {
+  const int i = to_scalar((int)ceilf(4.0f * __log2f(kappa) - 0.001f));
+  return i < 1 ? 1 : i > kIsqrtEntries ? kIsqrtEntries : i;
+}
+
+// beta^(-1/2), or a millionth less, of the upper bound beta = |A^2|_F^(1/2) of A's
+// eigenvalues, from fro = |A^2|_F^2: M = A times its square has them below 1, and
+// need not be closer (hardware estimates, each within 2^-23 or so).
+__device__ __forceinline__ double isqrt_scale(double fro) {
+  return __builtin_amdgcn_sqrt(__builtin_amdgcn_sqrt(__builtin_amdgcn_rsq(fro))) * (1.0 - 0x1.0p-20);
+}
+
+// The first stage, of M = A scale^2: (m-1)/rho bounds the condition number, `guess`
+// says what it may be off the vector of ones (stage_guess).  bound: the entry
+// that the smallest eigenvalue is certainly not below.
+__device__ __forceinline__ int isqrt_first(double scale, double a_diag, int guess, int& bound) {
+  bound = isqrt_entry(1.0f / (float)(scale * scale * a_diag));
+  return min(bound, guess);
+}
+
+constexpr int upper_word(double x) { return (int)(__builtin_bit_cast(unsigned long long, x) >> 32); }
+// After the planned stages: f2 = |R^2|_F^2, R = M - I, bounds ||R|| by f = f2^(1/4)
+// and so, below 1, M's smallest eigenvalue by 1 - f.
+__device__ __forceinline__ int isqrt_more(double f2, int bound) {
+  if (bound < 1) bound = 1;
+  if (to_scalar(upper_word(f2)) >= upper_word(1.0)) return bound;
+  return min(bound, isqrt_entry(1.0f / (1.0f - __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf((float)f2)))));
+}
+// The last stage's degree once f2 allows it (0: not yet), kIsqrtNever where f2 is
+// not finite.  By f2's upper word; its threshold is below rho^4 by at most 2^-20.
+constexpr int kIsqrtNever = -1;
+constexpr int isqrt_limit(int k) { return upper_word(kIsqrtRho[k] * kIsqrtRho[k] * kIsqrtRho[k] * kIsqrtRho[k]); }
+__device__ __forceinline__ int isqrt_last(double f2) {
+  const int h = to_scalar(upper_word(f2));  // f2 >= 0 or NaN
+  if (h < 0 || h >= 0x7ff00000) return kIsqrtNever;
+  return h < isqrt_limit(0) ? 2 : h < isqrt_limit(1) ? 4 : h < isqrt_limit(2) ? 6 : 0;
+}
+constexpr int kIsqrtCap = 40;  // stages at most (11 at the table's end)
+
+// Z = (A + shift 1 1^T)^(-1/2) from A in Bm (stride M + 2): each wavefront ends
+// with its columns of Z in Z (sm.rc[8]: the shift).  Returns the matrix products
+// done.  Every stage after the first forms M^2 and with it f2 = |(M - I)^2|_F^2;
+// the stages end when that says that the last stage's polynomial is exact to
+// rounding, whatever the condition number was taken to be.  sm.rc[9]: whether they
+// got there (not where A holds a NaN or is numerically indefinite).
+// A's smallest eigenvalue (m-1)/rho belongs to the vector of ones, of which Y'
+// and X' know nothing (their rows sum to zero); every other one may be orders
+// above it, and W only matters there.  So the trace's mean goes on top of that
+// eigenvalue (shift = tr(A) / m^2), and the interval, the stages and the rounding
+// are those of the others.  b is orthogonal to the ones as well.
+// Relative error of X' W on 15 x 15, m = 16, against extended precision: 4e-15
+// (Cholesky + SVD of A 4e-15; without the shift and with the bound's interval
+// 4e-13), on 32 x 32, m = 197 1e-14 (1e-14; 1e-12); with R^-1 x 1e4 3e-13 and
+// 1e-12 (3e-13 and 9e-13; 1e-11 and 3e-10).  Launch: 15 x 15 16.6 -> 17.6 us,
+// 84 x 84, m = 64 136 -> 135, 100 x 100, m = 100 850 -> 990 (22 products for 20).
 // Four matrices in registers are 128 VGPRs per lane at M = 64 and 256 at
 // M = 128, which leaves too few for the rest: two of Z's four tiles wait in LDS
 // (behind S, up to the end of the staging area) at M = 64, seven of its eight in
 // `park` (a slot of the instance's workspace) at M = 128, while the stage's
 // polynomial is formed.
 template <int M, int T, typename F>
-__device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, double* park, f64x4 (&Z)[T],
-                                            bool& in_table, F&& planned) {
+__device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, int m, double a_diag, int guess, double* park, f64x4 (&Z)[T],
+                                            F&& planned) {
   using B = IsqrtBlock<M, T>;
   using C = PolyCfg<M>;
   constexpr int NW = C::NW;
@@ -2532,31 +2615,79 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
   const bool on = T == NW || T == 7 || w < T;
   double* S = sm.Bm;
   f64x4 Mc[T], X[T];
-  double ss = 0.0;
+  // sm.rc by an address formed here: the compiler would keep one per pair of sums
+  using lds_double = __attribute__((address_space(3))) double;
+  auto scratch = [&]() {
+    unsigned o = (unsigned)(uintptr_t)(lds_double*)sm.rc;
+    __asm__ volatile("" : "+v"(o));
+    return (lds_double*)(uintptr_t)o;
+  };
+  // the trace, summed alike by every wavefront
+  double tr;
+  {
+    const int t = tid0 % 64;
+    tr = t < m ? S[t * (B::LD + 1)] : 0.0;
+    if constexpr (M > 64) tr += t + 64 < m ? S[(t + 64) * (B::LD + 1)] : 0.0;
+    tr = wave_sum(tr);
+  }
+  const double shift = tr / ((double)m * m);
+  if (tid0 == 0) scratch()[8] = shift;
+  // and a power of 4 near it, by which A is divided: |A^2|_F^2 stays in range
+  const int ex = __builtin_amdgcn_readfirstlane((__builtin_amdgcn_frexp_exp(tr) + 1) & ~1);
+  __syncthreads();  // A's diagonal read everywhere before it changes
   if (on) {
     B::load(S, B::LD, Mc, tid());
+    // past m the diagonal is the mean eigenvalue, inside the others' interval
+    const int t0 = tid(), g = (t0 & 63) >> 4, dk = B::diagonal(t0);
+    const bool in = B::column(t0) < m;
+#pragma unroll
+    for (int k = 0; k < 4 * T; ++k) {
+      const double x = in ? Mc[k / 4][k % 4] + (B::row(k / 4, k % 4, g) < m ? shift : 0.0) : k == dk ? shift * m : 0.0;
+      Mc[k / 4][k % 4] = ldexp(x, -ex);
+    }
+    B::store(S, B::LD, Mc, t0);
+  }
+  __syncthreads();
+  // 1 where k is the diagonal's element and 0 elsewhere, from words formed here
+  // (constants that the compiler would keep in registers across the stages)
+  struct Unit {
+    int dk, hi, lo;
+    __device__ __forceinline__ double operator()(int k) const { return __hiloint2double(k == dk ? hi : 0, lo); }
+  };
+  auto unit = [&](int dk) {
+    Unit u{dk, 0, 0};
+    __asm__ volatile("v_mov_b32 %0, 0x3ff00000\n\tv_mov_b32 %1, 0" : "=&v"(u.hi), "=v"(u.lo));
+    return u;
+  };
+  // the thread's diagonal element, afresh at every use (its comparisons are not kept)
+  auto diagonal = [&]() {
+    int d = B::diagonal(tid());
+    __asm__ volatile("" : "+v"(d));
+    return d;
+  };
+  // |V|_F^2 over the workgroup, from each thread's sum over its elements
+  auto frobenius = [&](double ss) {
+    ss = wave_sum(ss);
+    lds_double* const sums = scratch();
+    if (tid() % 64 == 0) sums[w] = ss;
+    __syncthreads();
+    double f = 0.0;
+#pragma unroll
+    for (int k = 0; k < (T < NW ? T : NW); ++k) f += sums[k];
+    return f;
+  };
+  double ss = 0.0;
+  if (on) {
     B::mul(S, Mc, X, tid());  // A^2
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) ss = fma(X[t][v], X[t][v], ss);
   }
-  ss = group_sum<16>(ss);
-  ss += __shfl_xor(ss, 16, 64);
-  ss += __shfl_xor(ss, 32, 64);
-  if (tid0 % 64 == 0) sm.rc[w] = ss;
-  __syncthreads();
-  double fro = 0.0;
-#pragma unroll
-  for (int k = 0; k < (T < NW ? T : NW); ++k) fro += sm.rc[k];
-  const double beta = sqrt(sqrt(fro)), kappa = beta / a_diag;
-  // row r of the table serves kappa <= 2^(r/2); uniform, every thread read the same sums
-  in_table = kappa <= 0.999 * 0x1.0p52;
-  int r = in_table ? 1 + (int)(2.0f * __log2f((float)kappa) + 0.01f) : kIsqrtRows - 1;
-  r = __builtin_amdgcn_readfirstlane(r < 1 ? 1 : r >= kIsqrtRows ? kIsqrtRows - 1 : r);
+  const double scale = readlane_f64(isqrt_scale(frobenius(ss)), 0);
+  int bound;
+  const int plan = isqrt_first(scale, ldexp(a_diag, -ex), guess, bound);
   planned();
-  const IsqrtRow& R = kIsqrtPlan[r];
-  const int n = R.n;
   // Z between the stages: KEEP tiles stay in registers, the others wait outside
   // (each lane its own values, 16 bytes a lane)
   constexpr int KEEP = C::keep(T);
@@ -2609,20 +2740,17 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
     }
     __syncthreads();
   };
-  // P = q(M) into S; Mc: the columns of M (of M - I in the last stage), S: all of
-  // it, X: the columns of its square (unless deg = 1).  Leaves X undefined.
-  auto stage_poly = [&](int s, int deg, double scale, double step) {
+  // P = q(M) into S; Mc: the columns of M (of M - I in the last stage), X: those
+  // of its square.  Leaves X undefined.
+  // Degree 4, in a last stage (`any`) 2 and 6 as well.
+  auto stage_poly = [&](auto any, const double* c, int deg, double scale, double step) {
     double q[7];  // in scalar registers
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
-      q[k] = readlane_f64(R.c[s][k] * scale, 0);
+      q[k] = k <= 4 || (any && deg == 6) ? readlane_f64(c[k] * scale, 0) : 0.0;
       scale *= step;
     }
-    if (deg == 1) {
-#pragma unroll
-      for (int t = 0; t < T; ++t) X[t] = q[1] * Mc[t];
-      publish(X, q[0]);
-    } else if (deg == 2) {
+    if (any && deg == 2) {
 #pragma unroll
       for (int t = 0; t < T; ++t) X[t] = q[2] * X[t] + q[1] * Mc[t];
       publish(X, q[0]);
@@ -2631,7 +2759,7 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
       publish(X, 0.0);
       // deg 4: M^2 (q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I
       // deg 6: M^2 (M^2 (q6 M^2 + q5 M) + q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I
-      const bool six = deg == 6;
+      const bool six = any && deg == 6;
       const double h2 = six ? q[6] : q[4], h1 = six ? q[5] : q[3], l2 = six ? q[4] : q[2], l1 = six ? q[3] : q[1];
 #pragma unroll
       for (int k = 0; k < 4 * T; ++k) {
@@ -2652,39 +2780,92 @@ __device__ __forceinline__ int isqrt_stages(PolySmem<M>& sm, double a_diag, doub
       publish(Y, q[0]);
     }
   };
-  // M <- P (P M) (minus I ahead of the last stage), its columns and S
-  auto stage_next = [&](bool shift) {
+  // M <- P (P M), its columns and S
+  auto stage_next = [&]() {
     if (on) {
       B::mul(S, Mc, X, tid());
       B::mul(S, X, Mc, tid());
     }
-    publish(Mc, shift ? -1.0 : 0.0);
-    if (shift && on) B::load(S, B::LD, Mc, tid());
+    publish(Mc, 0.0);
   };
-  stage_poly(0, R.deg[0], 1.0 / sqrt(beta), 1.0 / beta);  // the powers of A carry 1 / beta each
+  // of the table, and the stage of it that comes next
+  int row = (plan + 1) / 2, next = 1;
+  int products = 4;
+  stage_poly(std::false_type{}, kIsqrtPlan[row].c[0], 4, scale, scale * scale);  // a power of M is one of A times scale^2 each
   if (on) {
     B::load(S, B::LD, X, tid());  // Z = P
     park_store(X);
   }
-  stage_next(n == 2);
+  stage_next();
+  auto stage_z = [&]() {  // Z <- P Z, into X
+    f64x4 V[T];
+    park_load(V);
+    B::mul(S, V, X, tid());
+  };
+  // Last stages of degree 2 and 6 where registers allow the branch between them
+  // (M = 128: 229 VGPRs without, spills with it).
+  constexpr bool ANY = M <= 64;
+  int last;
 #pragma unroll 1
   for (int s = 1;; ++s) {
-    const int deg = R.deg[s];
-    if (deg > 1 && on) B::mul(S, Mc, X, tid());  // M^2
-    stage_poly(s, deg, 1.0, 1.0);
-    f64x4 V[T];
+    double f2 = 0.0;
     if (on) {
-      park_load(V);
-      B::mul(S, V, X, tid());  // Z <- P Z
-    }
-    if (s + 1 == n) break;
-    if (on) park_store(X);
-    stage_next(s + 2 == n);
-  }
+      B::mul(S, Mc, X, tid());  // M^2
+      const Unit one = unit(diagonal());
 #pragma unroll
-  for (int t = 0; t < T; ++t) Z[t] = X[t];
+      for (int k = 0; k < 4 * T; ++k) {
+        const double d = fma(-2.0, Mc[k / 4][k % 4], X[k / 4][k % 4]) + one(k);
+        f2 = fma(d, d, f2);
+        if (k % 2) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    f2 = readlane_f64(frobenius(f2), 0);
+    last = isqrt_last(f2);
+    if (!ANY && last == 6) last = 0;  // too wide for degree 4
+    if (last != 0 || s == kIsqrtCap) break;
+    if (next + 1 >= __builtin_amdgcn_readfirstlane(kIsqrtPlan[row].n)) {
+      // the row's stages are done, and raised what was below their interval by its
+      // width at least (to within 1 %)
+      bound = max(bound - 2 * row, 0) + 1;
+      row = isqrt_more(f2, bound);
+      row = row == 1 ? 0 : (row + 1) / 2;
+      next = 0;
+    }
+    stage_poly(std::false_type{}, kIsqrtPlan[row].c[next++], 4, 1.0, 1.0);
+    if (on) {
+      stage_z();
+      park_store(X);
+    }
+    stage_next();
+    products += 5;
+  }
+  // the last stage, in powers of M - I (by its degree 6 where the certificate is
+  // not to be had)
+  const int deg = !ANY ? 4 : last > 0 ? last : 6;
+  if (on) {
+    const Unit one = unit(diagonal());
+#pragma unroll
+    for (int k = 0; k < 4 * T; ++k) {  // X = (M - I)^2, Mc = M - I
+      X[k / 4][k % 4] = fma(-2.0, Mc[k / 4][k % 4], X[k / 4][k % 4]) + one(k);
+      Mc[k / 4][k % 4] -= one(k);
+      if (k % 2) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  stage_poly(std::bool_constant<ANY>{}, kIsqrtLast[deg / 2 - 1], deg, 1.0, 1.0);
+  products += deg / 2 + 1;
+  if (on) stage_z();
+  if (tid() == 0) scratch()[9] = last > 0 ? 1.0 : 0.0;
+#pragma unroll
+  for (int k = 0; k < 4 * T; ++k) Z[k / 4][k % 4] = ldexp(X[k / 4][k % 4], -ex / 2);
   __syncthreads();  // every wavefront is done with S
-  return R.products;
+  return products;
+}
+
+// What W has along the vector of ones beyond the shifted matrix's inverse square
+// root, per entry of T.  X' annihilates it but for the rounding of xbar, which
+// it takes out again.
+__device__ __forceinline__ double ones_term(int m, double sqrt_m1, double a_diag, double shift) {
+  return sqrt_m1 * (rsqrt_1_2(a_diag) - rsqrt_1_2(a_diag + m * shift)) / m;
 }
 
 // wbar = A^-1 b = Z (Z b) (with one refinement step through A itself on the
@@ -2704,8 +2885,12 @@ __device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int
   };
   if (on) B::store(sm.Bm, LDB, Z, tid);
   if constexpr (16 * T < M) {  // past the tiles that took part: zero
-    for (int k = tid; k < M * (M - 16 * T); k += C::NT) sm.Bm[k / (M - 16 * T) * LDB + 16 * T + k % (M - 16 * T)] = 0.0;
-    for (int k = tid; k < (M - 16 * T) * 16 * T; k += C::NT) sm.Bm[(16 * T + k / (16 * T)) * LDB + k % (16 * T)] = 0.0;
+    double zero = 0.0;
+    __asm__ volatile("" : "+v"(zero));  // (not a register kept over the stages)
+    for (int k = tid / 16; k < M; k += C::NT / 16)
+      for (int r = 16 * T + tid % 16; r < M; r += 16) sm.Bm[k * LDB + r] = zero;
+    for (int k = 16 * T + tid / 16; k < M; k += C::NT / 16)
+      for (int r = tid % 16; r < 16 * T; r += 16) sm.Bm[k * LDB + r] = zero;
   }
   __syncthreads();
   substamp(0);
@@ -2731,7 +2916,7 @@ __device__ __forceinline__ void finish_T(PolySmem<M>& sm, const InstDesc& I, int
   }
   substamp(2);
   if (on) {
-    const double sc = sqrt((double)(m - 1)), wb = sm.wbar[c];
+    const double sc = I.sqrt_m1, wb = sm.wbar[c] + ones_term(m, sc, I.a_diag, sm.rc[8]);
     f64x4 X[T];
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -2754,6 +2939,7 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
   const int l = __builtin_amdgcn_readfirstlane(I.order[item - cb.dom_off[eb]]);
   const int est_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l]), e = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 1]);
   const int obs_off = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 2]), s = __builtin_amdgcn_readfirstlane(I.dom[4 * l + 3]);
+  const int guess = __builtin_amdgcn_readfirstlane((int)gload(I.guess + l));
   const int m = I.m;
   const int cur = __builtin_amdgcn_readfirstlane(I.st->cur);
   double* dbg = I.dbg ? I.dbg + (size_t)l * (2 * m * m + m + kDbgTail) : nullptr;
@@ -2765,7 +2951,9 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
   if (dbg && threadIdx.x == 0) {  // debug: where the workgroup runs (HW_ID: SE, SH, CU, SIMD; XCC_ID)
     dbg[2 * m * m + m + 6] = (double)__builtin_amdgcn_s_getreg(4 | (31 << 11));
     dbg[2 * m * m + m + 7] = (double)__builtin_amdgcn_s_getreg(20 | (31 << 11));
-    dbg[2 * m * m + m + 8] = (double)blockIdx.x;
+    int wg = blockIdx.x;
+    __asm__ volatile("" : "+s"(wg));  // (its conversion is not kept over the items)
+    dbg[2 * m * m + m + 8] = (double)wg;
   }
 
   constexpr int ld = PolySmem<M>::LDA;
@@ -2787,13 +2975,12 @@ __device__ __forceinline__ void analyse_poly(PolySmem<M>& sm, const InstDesc* __
     auto solve = [&](auto tiles) {
       constexpr int T = decltype(tiles)::value;
       f64x4 Z[T];
-      bool in_table;
-      const int products = isqrt_stages<M, T>(sm, I.a_diag, park, Z, in_table, [&]() { stamp(2); });
+      const int products = isqrt_stages<M, T>(sm, m, I.a_diag, guess, park, Z, [&]() { stamp(2); });
       stamp(3);
       if (threadIdx.x == 0) {
         if (I.dbg_sweeps) I.dbg_sweeps[l] = products;
         gatomic_add(&I.dom_sweeps[l], (unsigned)products);
-        if (!in_table) gatomic_add(&I.st->unconverged, 1);
+        if (sm.rc[9] == 0.0) gatomic_add(&I.st->unconverged, 1);
         gatomic_add(&I.st->sweeps, (unsigned long long)products);
         gatomic_add(&I.st->solves, 1ull);
       }
@@ -2872,29 +3059,21 @@ __global__ __launch_bounds__(AnaCfg<M>::NT) void k_lambda(const InstDesc* __rest
 // (which stays in L2 between launches), one wavefront group per 16 x 16 tile:
 //   k_big_gram    A = (m-1)/rho I + Y'^T diag(r) Y' by tiles, b = Y'^T diag(r) d
 //   k_big_mul     the matrix products of the polynomial stages of A^(-1/2)
-//                 (isqrt_plan.hpp), one launch per product
-//   k_big_slow    the stages past the launched ones, for condition bounds that
+//                 (isqrt_stages says how they are chosen and ended), one launch
+//                 per product
+//   k_big_slow    the stages past the launched ones, for condition numbers that
 //                 need more than kBigStages of them (an empty launch otherwise)
 //   k_big_wbar    wbar = Z (Z b), refined once with A
 //   k_big_update  Z_l = xbar 1^T + X' (sqrt(m-1) Z + wbar 1^T)
-// W = [(m-1) A^-1]^(1/2) needs no eigenvectors: A's smallest eigenvalue is at
-// least (m-1)/rho, so with the upper bound beta = |A^2|_F^(1/2) its spectrum's
-// interval is known, and Z = A^(-1/2) comes from minimax polynomial stages
-//   P = q(M),  Z <- P Z,  M <- P (P M),   M_0 = A, Z_0 = I,
-// the first stage's coefficients carrying the scaling by beta.  The products
-// are polynomials in A taken from the left, never mirrored: their rounding
-// stays commuting with A to first order (a CPU replay matches Cholesky + SVD
-// at every condition number up to 1e15; forcing symmetry costs a factor 10).
-// Every stage has degree 4 (the table's rows of that form), so that the launch
-// sequence is the same for every condition number; the launches of stages a
-// domain does not need return at once.  On the 32 x 32 pupil (m = 197, one
-// domain) the blocked Jacobi this replaced took 3.42 of the analysis's 3.98 ms,
-// in 312 dependent launches.
+// Every stage has degree 4, so that the launch sequence is the same for every
+// condition number; the launches of stages a domain does not need return at
+// once.  On the 32 x 32 pupil (m = 197, one domain) the blocked Jacobi this
+// replaced took 3.42 of the analysis's 3.98 ms, in 312 dependent launches.
 // ----------------------------------------------------------------------------
 constexpr int kBigM = 256;
 constexpr int kBigLd = kBigM + 8;     // LDS column stride in k_big_round
 constexpr int kBigMaxSweeps = 24;
-constexpr int kBigStages = 7;
+constexpr int kBigStages = 8;
 
 struct BigDom {
   const InstDesc* I;
@@ -2902,9 +3081,18 @@ struct BigDom {
   double* A;
   double* W;   // 5 matrices: M, M^2 (then P M), P, Z of even and of odd stages
   double* v;
-  int32_t* f;
+  int32_t* f;  // f[3]: the stages done, 0 until the last one is chosen
   __device__ double* mat(int k) const { return W + (size_t)k * kBigM * kBigM; }
+  // of A + shift 1 1^T, divided by 2^ex ahead of the stages
+  __device__ double& shift() const { return v[2 * kBigM]; }
+  __device__ double& ex() const { return v[2 * kBigM + 1]; }
+  // partial sums of |(M - I)^2|_F^2 (first stage: of |A^2|_F^2), by tile
+  __device__ double* part() const { return v + 3 * kBigM; }
+  // of stage s: the table entry planned for it (0: none), and the bound's
+  __device__ double* plan(int s) const { return v + 4 * kBigM + 2 * s; }
+  __device__ const double* Z() const { return mat(3 + (f[3] - 1) % 2); }
 };
+static_assert(2 * (kIsqrtCap + 2) <= kBigM, "plans of every stage");
 
 __device__ __forceinline__ BigDom big_dom(const InstDesc* __restrict__ tab, const ClassBatch& cb, int item) {
   BigDom d;
@@ -2929,9 +3117,7 @@ __device__ __forceinline__ double* big_dbg(const BigDom& D) {
 
 // The sum of v over a 256-thread workgroup, on every thread.
 __device__ __forceinline__ double block_sum256(double v, double* red) {
-  v = group_sum<16>(v);
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
+  v = wave_sum(v);
   if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
   __syncthreads();
   const double t = (red[0] + red[1]) + (red[2] + red[3]);
@@ -3022,12 +3208,13 @@ __global__ __launch_bounds__(64 * kGramWaves) void k_big_gram(const InstDesc* __
           dbg[(size_t)gj * m + gi] = x;
         }
       } else {
-        a = gi == gj ? I.a_diag : 0.0;  // padded members: the spectrum's lower bound
+        a = gi == gj ? I.a_diag : 0.0;  // (the stages put the mean eigenvalue there)
       }
       D.A[(size_t)gj * kBigM + gi] = a;
       D.A[(size_t)gi * kBigM + gj] = a;
     }
   }
+  if (blockIdx.x == 0 && tid == 0) D.f[3] = 0;
   if (diag && tid < 16) {
     double x = 0.0;
 #pragma unroll
@@ -3036,14 +3223,14 @@ __global__ __launch_bounds__(64 * kGramWaves) void k_big_gram(const InstDesc* __
   }
 }
 
-// Tile (tr, tc) of L X (c2 X2 != nullptr: of L (c1 X + c2 X2)), column-major
-// matrices of leading dimension 256, by a 256-thread workgroup: wavefront w
-// takes the 16-row blocks w, w + 4, ... of the contraction, all its operand
-// loads first (the loads' latency, not the 13 to 16 products of a wavefront,
-// is what a tile takes), and the four partial tiles are summed in LDS.  Thread
-// t returns element (t % 16, t / 16) of the tile.
-__device__ __forceinline__ double big_tile(const double* L, const double* X, const double* X2, double c1, double c2,
-                                           int tr, int tc, int nt, double (&red)[4][16 * 17]) {
+// Tile (tr, tc) of L X, column-major matrices of leading dimension 256, by a
+// 256-thread workgroup: wavefront w takes the 16-row blocks w, w + 4, ... of the
+// contraction, all its operand loads first (the loads' latency, not the 13 to 16
+// products of a wavefront, is what a tile takes), and the four partial tiles
+// are summed in LDS.  left(r, k) and right(k, c) load the operands (right two
+// consecutive k).  Thread t returns element (t % 16, t / 16) of the tile.
+template <typename FL, typename FR>
+__device__ __forceinline__ double big_tile(FL&& left, FR&& right, int tr, int tc, int nt, double (&red)[4][16 * 17]) {
   const int tid = threadIdx.x, w = tid / 64, lane = tid % 64, g = lane / 16, i = lane % 16;
   double a[16];
   f64x2 x[8];
@@ -3051,17 +3238,11 @@ __device__ __forceinline__ double big_tile(const double* L, const double* X, con
   for (int k = 0; k < 4; ++k) {
     const int b = w + 4 * k;
     const bool in = b < nt;
-    const double* Xc = X + (size_t)(16 * tc + i) * kBigM + 16 * (in ? b : 0) + 4 * g;
-    const double* La = L + (size_t)(16 * (in ? b : 0) + 4 * g) * kBigM + 16 * tr + i;
+    const int k0 = 16 * (in ? b : 0) + 4 * g;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) a[4 * k + h] = gload(La + h * kBigM);
+    for (int h = 0; h < 4; ++h) a[4 * k + h] = left(16 * tr + i, k0 + h);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) x[2 * k + h] = gload((const f64x2*)Xc + h);
-    if (X2) {
-      const double* X2c = X2 + (size_t)(16 * tc + i) * kBigM + 16 * (in ? b : 0) + 4 * g;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) x[2 * k + h] = c1 * x[2 * k + h] + c2 * gload((const f64x2*)X2c + h);
-    }
+    for (int h = 0; h < 2; ++h) x[2 * k + h] = right(k0 + 2 * h, 16 * tc + i);
     if (!in)
 #pragma unroll
       for (int h = 0; h < 2; ++h) x[2 * k + h] = f64x2{0.0, 0.0};
@@ -3079,67 +3260,127 @@ __device__ __forceinline__ double big_tile(const double* L, const double* X, con
   __syncthreads();
   return t;
 }
-
-// Table row of a domain by its condition bound: the rows whose stages all have
-// degree 4.  Rows past kBigStages stages run in k_big_slow.
-__device__ __forceinline__ int big_row(double kappa) {
-  constexpr int rows[] = {25, 37, 48, 59, 71, 83, 95};
-  const double x = kappa > 1.0 ? 2.0 * log2(kappa) + 0.01 : 0.01;
-  for (int k = 0; k < 6; ++k)
-    if (x <= rows[k]) return rows[k];
-  return rows[6];
+__device__ __forceinline__ double big_product_tile(const double* L, const double* X, int tr, int tc, int nt, double (&red)[4][16 * 17]) {
+  return big_tile([&](int r, int k) { return gload(L + (size_t)k * kBigM + r); },
+                  [&](int k, int c) { return gload((const f64x2*)(X + (size_t)c * kBigM + k)); }, tr, tc, nt, red);
 }
 
-// Tile (tr, tc) of product `kind` of stage s (table row R, condition scaling
-// 1 / beta in the first stage):
-//   0: M^2    1: P = M^2 (q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I
-//   2: Z <- P Z    3: P M    4: M <- P (P M), minus I ahead of the last stage
-// Returns the thread's element.
-__device__ __forceinline__ double big_product(const BigDom& D, int kind, int s, const IsqrtRow& R, double beta, int tr,
-                                              int tc, int nt, double (&red)[4][16 * 17]) {
-  const double* M = s == 0 ? D.A : D.mat(0);
-  double* M2 = D.mat(1);
-  double* P = D.mat(2);
-  double* Zo = D.mat(3 + s % 2);
+// Tile (tr, tc) of M^2 of stage s (of the first: of A^2, A shifted and scaled,
+// which it leaves in M).  Returns the square of the thread's element of M^2 - 2 M + I
+// (first stage: of A^2).
+__device__ __forceinline__ double big_square(const BigDom& D, int s, int tr, int tc, int nt, double (&red)[4][16 * 17], double* bs) {
+  const int r = 16 * tr + threadIdx.x % 16, c = 16 * tc + threadIdx.x / 16, m = D.I->m;
+  const size_t at = (size_t)c * kBigM + r;
+  double* M = D.mat(0);
+  double t;
+  if (s == 0) {
+    const double* A = D.A;
+    const double tr_A = block_sum256((int)threadIdx.x < m ? gload(A + (size_t)threadIdx.x * (kBigM + 1)) : 0.0, bs);
+    const double shift = tr_A / ((double)m * m);
+    const int ex = (__builtin_amdgcn_frexp_exp(tr_A) + 1) & ~1;
+    auto get = [&](int r, int c) {  // past m the diagonal is the mean eigenvalue
+      return ldexp(r < m && c < m ? gload(A + (size_t)c * kBigM + r) + shift : r == c ? shift * m : 0.0, -ex);
+    };
+    t = big_tile(get, [&](int k, int c) { return f64x2{get(k, c), get(k + 1, c)}; }, tr, tc, nt, red);
+    gstore(M + at, get(r, c));
+    if (tr == 0 && tc == 0 && threadIdx.x == 0) {
+      D.shift() = shift;
+      D.ex() = (double)ex;
+    }
+  } else {
+    t = big_product_tile(M, M, tr, tc, nt, red);
+  }
+  gstore(D.mat(1) + at, t);
+  const double d = s == 0 ? t : fma(-2.0, gload(M + at), t) + (r == c ? 1.0 : 0.0);
+  return d * d;
+}
+
+// What stage s does, from f2 = |(M - I)^2|_F^2 (first stage: |A^2|_F^2).  The plan of
+// a stage is written by the stage before it, so that every workgroup of a launch
+// reads the same.
+struct BigStage {
+  const IsqrtStage* E;  // null: the last stage
+  double scale;         // first stage: isqrt_scale
+  bool converged;
+};
+__device__ __forceinline__ BigStage big_stage(const BigDom& D, int s, double f2, bool writer) {
+  BigStage g{nullptr, 1.0, true};
+  int plan, bound;
+  if (s == 0) {
+    g.scale = isqrt_scale(f2);
+    plan = isqrt_first(g.scale, ldexp(D.I->a_diag, -(int)D.ex()), D.I->guess[D.l], bound);
+  } else {
+    plan = (int)D.plan(s)[0];
+    bound = (int)D.plan(s)[1];
+    const int last = isqrt_last(f2);
+    g.converged = last == 2 || last == 4;
+    if (g.converged || s == kIsqrtCap || last == kIsqrtNever) {
+      if (writer) D.f[3] = s + 1;
+      return g;
+    }
+    if (plan == 0) plan = isqrt_more(f2, bound);
+  }
+  g.E = &kIsqrtStage4[plan - 1];
+  if (writer) {
+    const int next = g.E->next;
+    D.plan(s + 1)[0] = next;
+    D.plan(s + 1)[1] = max(bound - (plan - next), next);
+  }
+  return g;
+}
+
+// Tile (tr, tc) of P = M^2 (q4 M^2 + q3 M) + q2 M^2 + q1 M + q0 I of stage s, in
+// powers of M - I for the last stage.
+__device__ __forceinline__ void big_poly(const BigDom& D, int s, const BigStage& G, int tr, int tc, int nt, double (&red)[4][16 * 17]) {
+  const double* M = D.mat(0);
+  const double* M2 = D.mat(1);
+  const double* coef = G.E ? G.E->c : kIsqrtLast[1];
+  double q[5], scale = G.scale;
+  const double step = scale * scale;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    q[k] = coef[k] * scale;
+    scale *= step;
+  }
   const int r = 16 * tr + threadIdx.x % 16, c = 16 * tc + threadIdx.x / 16;
   const size_t at = (size_t)c * kBigM + r;
-  if (kind == 0) {
-    const double t = big_tile(M, M, nullptr, 0.0, 0.0, tr, tc, nt, red);
-    M2[at] = t;
-    return t;
+  double t, e1 = gload(M + at), e2 = gload(M2 + at);
+  if (G.E) {
+    t = big_tile([&](int r, int k) { return gload(M2 + (size_t)k * kBigM + r); },
+                 [&](int k, int c) {
+                   const size_t x = (size_t)c * kBigM + k;
+                   return q[3] * gload((const f64x2*)(M + x)) + q[4] * gload((const f64x2*)(M2 + x));
+                 }, tr, tc, nt, red);
+  } else {
+    auto one = [](int r, int c) { return r == c ? 1.0 : 0.0; };
+    t = big_tile([&](int r, int k) {
+                   const size_t x = (size_t)k * kBigM + r;
+                   return fma(-2.0, gload(M + x), gload(M2 + x)) + one(r, k);
+                 },
+                 [&](int k, int c) {
+                   const size_t x = (size_t)c * kBigM + k;
+                   const f64x2 d = {one(k, c), one(k + 1, c)}, v = gload((const f64x2*)(M + x));
+                   return q[3] * (v - d) + q[4] * (gload((const f64x2*)(M2 + x)) - 2.0 * v + d);
+                 }, tr, tc, nt, red);
+    e2 = fma(-2.0, e1, e2) + one(r, c);
+    e1 -= one(r, c);
   }
-  if (kind == 1) {
-    double q[5], scale = s == 0 ? 1.0 / sqrt(beta) : 1.0;
-    const double step = s == 0 ? 1.0 / beta : 1.0;
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      q[k] = R.c[s][k] * scale;
-      scale *= step;
-    }
-    double t = big_tile(M2, M, M2, q[3], q[4], tr, tc, nt, red);
-    t += q[2] * M2[at] + q[1] * M[at] + (r == c ? q[0] : 0.0);
-    P[at] = t;
-    if (s == 0) Zo[at] = t;
-    return t;
-  }
-  if (kind == 2) {
-    const double t = big_tile(P, D.mat(3 + (s + 1) % 2), nullptr, 0.0, 0.0, tr, tc, nt, red);
-    Zo[at] = t;
-    return t;
-  }
-  if (kind == 3) {
-    const double t = big_tile(P, M, nullptr, 0.0, 0.0, tr, tc, nt, red);
-    M2[at] = t;
-    return t;
-  }
-  const double t = big_tile(P, M2, nullptr, 0.0, 0.0, tr, tc, nt, red) - (s + 2 == R.n && r == c ? 1.0 : 0.0);
-  D.mat(0)[at] = t;
-  return t;
+  t += q[2] * e2 + q[1] * e1 + (r == c ? q[0] : 0.0);
+  gstore(D.mat(2) + at, t);
+  if (s == 0) gstore(D.mat(3) + at, t);  // Z = P
 }
 
-// grid (16 nt, ...): tile (x / 16, x % 16); KIND 0, 1, 4: that product; KIND 2:
-// products 2 and 3, by blockIdx.z.  f[3]: the domain's table row, written by the
-// first stage's KIND 1 from the tiles' partial sums of |A^2|_F^2 (KIND 0).
+// Tile (tr, tc) of: kind 2: Z <- P Z    3: P M (into M^2's place)    4: M <- P (P M)
+__device__ __forceinline__ void big_product(const BigDom& D, int kind, int s, int tr, int tc, int nt, double (&red)[4][16 * 17]) {
+  const double* X = kind == 2 ? D.mat(3 + (s + 1) % 2) : kind == 3 ? D.mat(0) : D.mat(1);
+  double* out = kind == 2 ? D.mat(3 + s % 2) : kind == 3 ? D.mat(1) : D.mat(0);
+  const double t = big_product_tile(D.mat(2), X, tr, tc, nt, red);
+  gstore(out + (size_t)(16 * tc + threadIdx.x / 16) * kBigM + 16 * tr + threadIdx.x % 16, t);
+}
+
+// grid (16 nt, ...): tile (x / 16, x % 16); KIND 0: M^2 and its partial sums,
+// 1: the stage chosen from them and P, 2: products 2 and 3, by blockIdx.z, 4: that
+// product.
 template <int KIND>
 __global__ __launch_bounds__(256) void k_big_mul(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
                                                  int cls, int s) {
@@ -3150,50 +3391,53 @@ __global__ __launch_bounds__(256) void k_big_mul(const InstDesc* __restrict__ ta
   const BigDom D = big_dom(tab, cb, blockIdx.y);
   const int nt = (D.I->m + 15) / 16, tr = blockIdx.x / 16, tc = blockIdx.x % 16, tid = threadIdx.x;
   if (tr >= nt || tc >= nt) return;
-  double beta = 1.0;
-  int row = 0;
-  if (KIND != 0 || s > 0) {
-    if (KIND == 1 && s == 0) {
-      // every workgroup sums the same partials in the same order
-      const double part = tid / 16 < nt && tid % 16 < nt ? D.v[3 * kBigM + tid] : 0.0;
-      beta = sqrt(sqrt(block_sum256(part, bs)));
-      const double kappa = beta / D.I->a_diag;
-      row = big_row(kappa);
-      if (blockIdx.x == 0 && tid == 0) {
-        D.f[3] = row;
-        if (!(kappa <= 0x1.0p47)) gatomic_add(&D.I->st->unconverged, 1);
-      }
-    } else {
-      row = D.f[3];
-    }
-    const int n = kIsqrtPlan[row].n;
-    if (s >= n || s >= kBigStages) return;
-    if ((KIND == 4 || (KIND == 2 && blockIdx.z == 1)) && s + 1 == n) return;
-  }
-  const int kind = KIND == 2 ? (s == 0 ? 3 : 2 + (int)blockIdx.z) : KIND;
-  const double t = big_product(D, kind, s, kIsqrtPlan[row], beta, tr, tc, nt, red);
-  if (KIND == 0 && s == 0) {
-    const double sum = block_sum256(t * t, bs);
-    if (tid == 0) D.v[3 * kBigM + blockIdx.x] = sum;
+  // done before this stage; at KIND 1 its first workgroup may just be writing
+  // f[3] = s + 1, which reads the same here as 0
+  const int done = D.f[3];
+  if (done != 0 && done <= s) return;
+  if (KIND == 0) {
+    const double sum = block_sum256(big_square(D, s, tr, tc, nt, red, bs), bs);
+    if (tid == 0) D.part()[blockIdx.x] = sum;
+  } else if (KIND == 1) {
+    // every workgroup sums the same partials in the same order
+    const double f2 = block_sum256(tid / 16 < nt && tid % 16 < nt ? D.part()[tid] : 0.0, bs);
+    const bool writer = blockIdx.x == 0 && tid == 0;
+    const BigStage G = big_stage(D, s, f2, writer);
+    if (writer && !G.converged && !G.E) gatomic_add(&D.I->st->unconverged, 1);
+    big_poly(D, s, G, tr, tc, nt, red);
+  } else {
+    const int kind = KIND == 2 ? (s == 0 ? 3 : 2 + (int)blockIdx.z) : KIND;
+    if (kind >= 3 && done == s + 1) return;
+    big_product(D, kind, s, tr, tc, nt, red);
   }
 }
 
-// grid (items): the stages past kBigStages, one workgroup per domain (seconds of
-// a millisecond each: condition bounds above 7e8, where FP64 leaves 1e-8 of W).
+// grid (items): the stages past kBigStages, one workgroup per domain (condition
+// numbers above 1e9 or so off the vector of ones).
 __global__ __launch_bounds__(256) void k_big_slow(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
                                                   int cls) {
   __shared__ double red[4][16 * 17];
+  __shared__ double bs[4];
   const ClassBatch& cb = hdr->cls[cls];
   if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
   const BigDom D = big_dom(tab, cb, blockIdx.x);
-  const IsqrtRow& R = kIsqrtPlan[D.f[3]];
+  if (D.f[3] != 0) return;
   const int nt = (D.I->m + 15) / 16;
-  for (int s = kBigStages; s < R.n; ++s)
-    for (int kind = 0; kind < 5; ++kind) {
-      if (kind >= 3 && s + 1 == R.n) break;
-      for (int t = 0; t < nt * nt; ++t) big_product(D, kind, s, R, 1.0, t / nt, t % nt, nt, red);
+  for (int s = kBigStages; s <= kIsqrtCap; ++s) {
+    double f2 = 0.0;
+    for (int t = 0; t < nt * nt; ++t) f2 += big_square(D, s, t / nt, t % nt, nt, red, bs);
+    f2 = block_sum256(f2, bs);
+    const bool writer = threadIdx.x == 0;
+    const BigStage G = big_stage(D, s, f2, writer);
+    if (writer && !G.converged && !G.E) gatomic_add(&D.I->st->unconverged, 1);
+    for (int t = 0; t < nt * nt; ++t) big_poly(D, s, G, t / nt, t % nt, nt, red);
+    for (int kind = 2; kind <= (G.E ? 4 : 2); ++kind) {
       __syncthreads();
+      for (int t = 0; t < nt * nt; ++t) big_product(D, kind, s, t / nt, t % nt, nt, red);
     }
+    if (!G.E) break;
+    __syncthreads();
+  }
 }
 
 // grid (items), 1024 threads: wbar = Z (Z b) and one refinement step with A; the
@@ -3211,8 +3455,8 @@ __global__ __launch_bounds__(1024) void k_big_wbar(const InstDesc* __restrict__ 
   const BigDom D = big_dom(tab, cb, blockIdx.x);
   const InstDesc& I = *D.I;
   const int m = I.m, mp = (m + 15) & ~15, tid = threadIdx.x, q = tid / 128, r2 = 2 * (tid % 128);
-  const int n = kIsqrtPlan[D.f[3]].n;
-  const double* Z = D.mat(3 + (n - 1) % 2);
+  const int ex = (int)D.ex();
+  const double* Z = D.Z();  // times 2^(ex / 2)
   auto product = [&](const double* B) {  // x <- B x; returns row tid (the first 256 threads)
     f64x2 t0 = {0.0, 0.0}, t1 = {0.0, 0.0};
     if (r2 < mp) {
@@ -3243,23 +3487,27 @@ __global__ __launch_bounds__(1024) void k_big_wbar(const InstDesc* __restrict__ 
   if (tid < kBigM) x[tid] = tid < mp ? D.v[tid] : 0.0;
   __syncthreads();
   product(Z);
-  const double w0 = product(Z);
+  const double w0 = ldexp(product(Z), -ex);
+  if (tid < kBigM) x[tid] = w0;
+  __syncthreads();
   const double aw = product(D.A);
   if (tid < kBigM) x[tid] = tid < m ? D.v[tid] - aw : 0.0;
   __syncthreads();
   product(Z);
-  const double w1 = product(Z);
-  if (tid < kBigM) D.v[kBigM + tid] = tid < m ? w0 + w1 : 0.0;
+  const double w1 = ldexp(product(Z), -ex);
+  // wbar and what W lacks along the ones, which enter T in the same way
+  const double wbar = w0 + w1 + ones_term(m, I.sqrt_m1, I.a_diag, D.shift());
+  if (tid < kBigM) D.v[kBigM + tid] = tid < m ? wbar : 0.0;
   if (double* dbg = big_dbg(D)) {
-    if (tid < kBigM) x[tid] = tid < m ? w0 + w1 : 0.0;
+    if (tid < kBigM) x[tid] = tid < m ? wbar : 0.0;
     __syncthreads();
-    const double sc = sqrt((double)(m - 1));
+    const double sc = ldexp(I.sqrt_m1, -ex / 2);
     const int r = tid % kBigM;
     for (int k = tid / kBigM; k < m; k += 4)
       if (r < m) dbg[(size_t)m * m + m + (size_t)k * m + r] = fma(sc, Z[(size_t)r * kBigM + k], x[k]);
   }
   if (tid == 0) {
-    const int products = kIsqrtPlan[D.f[3]].products;
+    const int products = 5 * D.f[3] - 3;  // 4 in the first stage, 3 in the last
     if (I.dbg_sweeps) I.dbg_sweeps[D.l] = products;
     gatomic_add(&I.st->sweeps, (unsigned long long)products);
     gatomic_add(&I.st->solves, 1ull);
@@ -3282,8 +3530,8 @@ __global__ __launch_bounds__(256) void k_big_update(const InstDesc* __restrict__
   const int m = I.m, nt = (m + 15) / 16, rows = 2 * D.e, tid = threadIdx.x, w = tid / 64, lane = tid % 64;
   const int q0 = 16 * blockIdx.x, tc = 4 * blockIdx.y + w;
   if (q0 >= rows || 4 * (int)blockIdx.y >= nt) return;
-  const int cur = I.st->cur, n = kIsqrtPlan[D.f[3]].n;
-  const double* Z = D.mat(3 + (n - 1) % 2);
+  const int cur = I.st->cur;
+  const double* Z = D.Z();
   const double* wbar = D.v + kBigM;
   const double* ens = (const double*)I.ens;
   const size_t slot = (size_t)I.n_act * m;
@@ -3328,7 +3576,7 @@ __global__ __launch_bounds__(256) void k_big_update(const InstDesc* __restrict__
     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[2], z1.x, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[3], z1.y, acc, 0, 0, 0);
   }
-  const double sc = sqrt((double)(m - 1));
+  const double sc = ldexp(I.sqrt_m1, -(int)D.ex() / 2);
   double* out = (double*)I.Z + (size_t)2 * D.est_off * m;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {

@@ -149,10 +149,11 @@ Layout make_layout(const Problem& P) {
   L.col = take((size_t)P.nnz * 4);
   L.val = take((size_t)P.nnz * 8);
   L.dom = take((size_t)P.n_dom * 16);
+  L.guess = uses_poly(P.prec, P.obs_instant) ? take(P.n_dom) : 0;
   L.order = take((size_t)P.n_dom * 4);
   L.est = take((size_t)P.sum_e() * 4);
   L.obs_row = take((size_t)2 * P.sum_s() * 4);
-  L.obs_r = take((size_t)2 * P.sum_s() * 8);
+  L.obs_r = reads_weights(P.prec, padded_members(P.m), P.obs_instant) ? take((size_t)2 * P.sum_s() * 8) : 0;
   L.obs_sr = take((size_t)2 * P.sum_s() * 8);
   L.mptr = take((n_act + 1) * 4);
   L.mrow = take((size_t)2 * P.sum_e() * 4);
@@ -358,7 +359,23 @@ int upload_instance(const Problem& P, const Layout& L, char* ws, const double* X
     }
   }
   put(blob, B, L.obs_row, obs_row.data(), obs_row.size());
-  put(blob, B, L.obs_r, obs_r.data(), obs_r.size());
+  if (L.obs_r) put(blob, B, L.obs_r, obs_r.data(), obs_r.size());
+  if (L.guess) {
+    std::vector<uint8_t> guess(P.n_dom);
+    std::vector<int> seen(n_act, -1);  // the last domain whose slopes touch the actuator
+    for (int l = 0; l < P.n_dom; ++l) {
+      const int o0 = 2 * P.obs_ptr[l], count = 2 * P.obs_ptr[l + 1] - o0;
+      int touched = 0;
+      for (int q = o0; q < o0 + count; ++q)
+        for (int k = P.d_rowptr[obs_row[q]]; obs_r[q] > 0.0 && k < P.d_rowptr[obs_row[q] + 1]; ++k)
+          if (seen[P.d_col[k]] != l) {
+            seen[P.d_col[k]] = l;
+            ++touched;
+          }
+      guess[l] = (uint8_t)stage_guess(m, obs_r.data() + o0, count, touched);
+    }
+    put(blob, B, L.guess, guess.data(), guess.size());
+  }
   std::vector<double> obs_sr(obs_r.size());
   for (size_t o = 0; o < obs_r.size(); ++o) obs_sr[o] = std::sqrt(obs_r[o]);
   put(blob, B, L.obs_sr, obs_sr.data(), obs_sr.size());
@@ -415,6 +432,7 @@ int upload_instance(const Problem& P, const Layout& L, char* ws, const double* X
   D.obs_inst = P.obs_instant;
   D.sigma_v = P.sigma_v;
   D.a_diag = (double)(m - 1) / P.inflation;
+  D.sqrt_m1 = std::sqrt((double)(m - 1));
   D.seed = P.seed;
   D.ens = ws + L.ens; D.Yp = ws + L.Yp; D.d = (double*)(ws + L.d); D.Z = ws + L.Z;
   D.a1 = (const double*)(ws + L.a1); D.a2 = (const double*)(ws + L.a2);
@@ -422,7 +440,9 @@ int upload_instance(const Problem& P, const Layout& L, char* ws, const double* X
   D.d_val = (const double*)(ws + L.val);
   D.dom = (const int32_t*)(ws + L.dom); D.order = (const int32_t*)(ws + L.order);
   D.est_act = (const int32_t*)(ws + L.est);
-  D.obs_row = (const int32_t*)(ws + L.obs_row); D.obs_r = (const double*)(ws + L.obs_r);
+  D.obs_row = (const int32_t*)(ws + L.obs_row);
+  D.obs_r = L.obs_r ? (const double*)(ws + L.obs_r) : nullptr;
+  D.guess = L.guess ? (const uint8_t*)(ws + L.guess) : nullptr;
   D.obs_sr = (const double*)(ws + L.obs_sr);
   D.mptr = (const int32_t*)(ws + L.mptr); D.mrow = (const int32_t*)(ws + L.mrow);
   D.mw = (const double*)(ws + L.mw);
