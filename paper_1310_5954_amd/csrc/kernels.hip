@@ -192,6 +192,8 @@ __global__ __launch_bounds__(256) void k_slopes(const InstDesc* __restrict__ tab
         if (j < m) gstore((T*)I.Yp + (size_t)o * m + j, (T)(v - ybar));
         if (j == 0) {
           gstore(I.d + o, yo - ybar);
+          // read elsewhere: kept where a later launch of this frame's slopes (autotune) looks
+          if (y) gstore((double*)hdr->yptr[cb.ent[b]] + o, yo);
           if (hdr->check_y && !isfinite(yo)) hdr->bad[cb.ent[b]] = 1;  // every writer stores the same value
         }
       }

@@ -11,7 +11,7 @@
 namespace letkf {
 
 // y (may be null): the slopes of a batch of one entry, in place of the header's
-// (a device pointer, or pinned host memory)
+// (a device pointer, or pinned host memory), which get a copy
 void launch_slopes(int cls, int slope_rows, const InstDesc* tab, BatchHdr* hdr, hipStream_t s,
                    const double* y = nullptr);
 // The means a frame of one instance leaves, `mean` (device, the one the mode
