@@ -889,16 +889,19 @@ int letkf_destroy(letkf_handle* h) {
 // copy cost a frame 4 to 6 us; by 4096 the two are even.
 constexpr int kHostSlopes = 4096;
 
-// Whether the slope kernel can read the caller's device slopes in place:
-// memory of the handle's GPU (anything else a copy command accepts is copied).
-static bool readable_y(const letkf_handle* h, const double* y) {
+// Whether the slope kernel can read the caller's device slopes in place: memory
+// of the handle's GPU, all of it within one allocation (anything else is left
+// to a copy command, which takes or refuses it).
+static bool readable_y(const letkf_handle* h, const double* y, size_t bytes) {
   if ((uintptr_t)y % alignof(double)) return false;
   hipPointerAttribute_t a{};
-  if (hipPointerGetAttributes(&a, y) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&a, y) != hipSuccess || hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)y) != hipSuccess) {
     (void)hipGetLastError();  // not memory HIP knows
     return false;
   }
-  return a.type == hipMemoryTypeDevice && a.device == h->device;
+  return a.type == hipMemoryTypeDevice && a.device == h->device && (size_t)((const char*)y - (const char*)base) + bytes <= size;
 }
 
 // The slopes of a frame (plain path).  *from: where the slope kernel reads
@@ -912,7 +915,7 @@ static int stage_y(letkf_handle* h, const double* y, int y_on_device, bool waits
   *from = nullptr;
   if (!y) return fail(LETKF_EINVAL, "null y");
   if (y_on_device) {
-    if (inplace && readable_y(h, y)) {
+    if (inplace && readable_y(h, y, bytes)) {
       *from = y;
       return LETKF_OK;
     }
