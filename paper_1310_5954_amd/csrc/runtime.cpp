@@ -23,6 +23,7 @@ int fail(int code, const std::string& msg) {
   return code;
 }
 int hip_fail(hipError_t e, const char* what) {
+  (void)hipGetLastError();  // reported here, and not by the next call's check of its launches
   g_last_error = std::string(what) + ": " + hipGetErrorString(e);
   return LETKF_EDEVICE;
 }

@@ -70,3 +70,17 @@ def test_device_slopes_that_end_before_their_count_are_refused():
     assert np.array_equal(f.get_state()[0], before)
     assert hip.hipFree(short) == 0
     f.close()
+
+
+def test_a_refused_call_leaves_no_error_for_the_next():
+    case = build_case(1)
+    p = Problem.from_case(case)
+    f = Filter(p, case.X0, precision=FP64)
+    loaded = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = C.CDLL(loaded)
+    short = C.c_void_p()
+    assert hip.hipMalloc(C.byref(short), C.c_size_t(8 * (p.p - 1))) == 0
+    assert _step(f, short.value, None) == L.EDEVICE
+    assert np.isfinite(f.step(case.slopes(0))).all()
+    assert hip.hipFree(short) == 0
+    f.close()
