@@ -497,12 +497,18 @@ template <> struct AnaStage<128> {
     };
   };
 };
-template <int M> struct AnaSmem : AnaStage<M> {
+// The matrix ahead of them: at LDS address 0 a column's or a partner's offset is
+// its address (behind the staging the Jacobi steps spent an add on every other
+// one: m = 32 FP32 launches of 8 instances 85.8 -> 88.2 us).
+template <int M> struct AnaMatrix {
+  double Bm[M * AnaCfg<M>::LDB];                      // A, then U, then T (row-major)
+};
+template <int M> struct AnaSmem : AnaMatrix<M>, AnaStage<M> {
   using C = AnaCfg<M>;
+  using AnaMatrix<M>::Bm;
   using AnaStage<M>::stage;
   static constexpr int LDA = C::LDB;                  // the gathers' stride of A
   static __device__ double pad(double) { return 1.0; }  // diagonal of A past m
-  double Bm[M * C::LDB];                              // A, then U, then T (row-major)
   double rc[32], dc[32];
   double bvec[M], nrm[M], wbar[M];
   int perm[M <= 64 ? M : 1];                          // FP64, M <= 64: A's symmetric permutation
