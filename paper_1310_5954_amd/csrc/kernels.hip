@@ -4037,7 +4037,7 @@ void launch_analysis(int cls, int grid, int kinds, const InstDesc* tab, BatchHdr
   if (grid <= 0 || cls == kBigClass) return;  // the m > 128 class runs launch_big_analysis
   if (kinds & kKindPoly) {
     const bool m128 = cls % 4 == 3;
-    const int pgrid = m128 ? min(grid, kParkSlots) : grid;  // a workgroup per parking slot (and one fits a CU)
+    const int pgrid = min(grid, analysis_max_grid(cls, kKindPoly));
 #define LETKF_LAUNCH_POLY(K) hipLaunchKernelGGL(K, dim3(pgrid), dim3(m128 ? 512 : 256), 0, s, tab, hdr, cls)
     LETKF_POLY_KERNEL(cls, LETKF_LAUNCH_POLY);
 #undef LETKF_LAUNCH_POLY
@@ -4056,14 +4056,25 @@ void launch_lambda(int cls, const InstDesc* inst, int domain, hipStream_t s) {
   else hipLaunchKernelGGL(k_lambda<128>, dim3(1), dim3(AnaCfg<128>::NT), 0, s, inst, domain);
 }
 
-int analysis_blocks_per_cu(int cls) {
+int analysis_blocks_per_cu(int cls, int kinds) {
   if (cls == kBigClass) return 1;
-  int n = 0;
+  int n = 0, least = 0;
   hipError_t e = hipSuccess;
-#define LETKF_OCC(K) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, cls % 4 == 3 ? AnaCfg<128>::NT : 256, 0)
-  LETKF_ANA_KERNEL(cls, LETKF_OCC);
+#define LETKF_OCC(K) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, cls % 4 == 3 ? 512 : 256, 0)
+  static_assert(AnaCfg<128>::NT == 512 && PolyCfg<128>::NT == 512, "workgroups of M = 128");
+  if (kinds & kKindPoly) {
+    LETKF_POLY_KERNEL(cls, LETKF_OCC);
+    least = (e == hipSuccess && n > 0) ? n : 1;
+  }
+  if (kinds & kKindJacobi) {
+    LETKF_ANA_KERNEL(cls, LETKF_OCC);
+    if (e != hipSuccess || n < 1) n = 1;
+int analysis_max_grid(int cls, int kinds) { return cls % 4 == 3 && kinds == kKindPoly ? kParkSlots : 65535; }
+
+    least = least ? min(least, n) : n;
+  }
 #undef LETKF_OCC
-  return (e == hipSuccess && n > 0) ? n : 1;
+  return least ? least : 1;
 }
 
 }  // namespace letkf

@@ -41,7 +41,10 @@ void launch_lambda(int cls, const InstDesc* inst, int domain, hipStream_t s);
 // progress-ordered priorities: at most two of its workgroups share a CU.
 inline int analysis_fair_grid(int grid, int num_cu) { return grid <= 2 * num_cu ? 1 : 0; }
 // Analysis workgroups of the class one CU holds at once (LDS and registers).
-int analysis_blocks_per_cu(int cls);
+int analysis_blocks_per_cu(int cls, int kinds);
+// The largest grid an analysis launch of these kinds takes: at M = 128 the
+// polynomial stages have a workgroup per parking slot (and one fits a CU).
+int analysis_max_grid(int cls, int kinds);
 
 // ---- the allocation-free frame (letkf_step_noalloc) ----
 // Byte offsets, inside the library's static device array, of the scratch of

@@ -661,7 +661,7 @@ int upload_order(letkf_handle* h, int policy, hipStream_t s, std::vector<int32_t
     for (int l = 0; l < n; ++l) cost[l] = sw[l] + (h->desc.poly ? 13.0 : 3.5) * analyses;
     int num_cu = 0;
     LETKF_HIP(hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, h->device));
-    order = balanced_order(h->P, cost, num_cu, analysis_blocks_per_cu(h->cls) * num_cu);
+    order = balanced_order(h->P, cost, num_cu, analysis_blocks_per_cu(h->cls, h->kinds()) * num_cu);
   } else {
     order = domain_order(h->P, policy);
   }
@@ -709,17 +709,17 @@ int tune_class(int cls, const InstDesc* tab, BatchHdr* hdr, int slope_rows, int 
                hipStream_t s, letkf_tuning* res, int* grid_out) {
   if (items <= 0 || insts.empty()) return fail(LETKF_EINVAL, "nothing to tune");
   reps = std::max(1, std::min(reps, 100));
-  const int bpc = analysis_blocks_per_cu(cls);
   int kinds = 0;
   for (const letkf_handle* h : insts) kinds |= h->kinds();
+  const int bpc = analysis_blocks_per_cu(cls, kinds), most = analysis_max_grid(cls, kinds);
+  max_grid = max_grid > 0 ? std::min(max_grid, most) : most;
   std::vector<int> grids;
   for (int k = 1; k <= 2 * bpc; ++k) grids.push_back(std::min(items, (k * num_cu + 1) / 2));
-  grids.push_back(std::min(items, 65535));  // one workgroup per item: the hardware dispatcher balances
-  if (max_grid > 0)
-    for (int& g : grids) g = std::min(g, max_grid);
+  grids.push_back(items);  // one workgroup per item: the hardware dispatcher balances
+  for (int& g : grids) g = std::min(g, max_grid);
   std::sort(grids.begin(), grids.end());
   grids.erase(std::unique(grids.begin(), grids.end()), grids.end());
-  const int def_grid = std::min(items, max_grid > 0 ? std::min(bpc * num_cu, max_grid) : bpc * num_cu);
+  const int def_grid = std::min({items, bpc * num_cu, max_grid});
 
   std::vector<InstState> saved(insts.size());
   std::vector<std::vector<uint32_t>> saved_sw(insts.size());
@@ -849,7 +849,8 @@ int letkf_create(const letkf_dims* dims, const letkf_model* model, const letkf_d
     if (hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || num_cu < 1)
       rc = fail(LETKF_EDEVICE, "hipDeviceGetAttribute");
     h->num_cu = num_cu;
-    h->ana_grid = std::min(h->P.n_dom, analysis_blocks_per_cu(h->cls) * num_cu);
+    h->ana_grid = std::min({h->P.n_dom, analysis_blocks_per_cu(h->cls, h->kinds()) * num_cu,
+                            analysis_max_grid(h->cls, h->kinds())});
     for (int l = 0; l < h->P.n_dom; ++l)
       h->max_rows = std::max(h->max_rows, 2 * (h->P.est_ptr[l + 1] - h->P.est_ptr[l]));
   }
@@ -1297,7 +1298,7 @@ int letkf_set_tuning(letkf_handle* h, const letkf_tuning* t, void* stream) {
   if (!t || t->grid < 1 || t->grid > 65535 || t->order < LETKF_ORDER_MAP || t->order > LETKF_ORDER_BALANCED)
     return fail(LETKF_EINVAL, "tuning: grid must be in [1, 65535] and order one of LETKF_ORDER_*");
   if ((rc = upload_order(h, t->order, (hipStream_t)stream))) return rc;
-  h->ana_grid = std::min(t->grid, std::max(h->P.n_dom, 1));
+  h->ana_grid = std::min({t->grid, std::max(h->P.n_dom, 1), analysis_max_grid(h->cls, h->kinds())});
   drop_graphs(h);
   return LETKF_OK;
 }

@@ -483,7 +483,8 @@ int letkf_server_create(void* arena, size_t arena_bytes, int32_t max_batch, uint
     if (hipStreamCreateWithFlags(&s->stream[k], hipStreamNonBlocking) != hipSuccess) rc = fail(LETKF_EDEVICE, "stream");
   if (!rc && hipStreamCreateWithFlags(&s->upload, hipStreamNonBlocking) != hipSuccess) rc = fail(LETKF_EDEVICE, "stream");
   if (!rc && hipStreamCreateWithFlags(&s->capture, hipStreamNonBlocking) != hipSuccess) rc = fail(LETKF_EDEVICE, "stream");
-  for (int c = 0; c < kNumClasses && !rc; ++c) s->bpc[c] = analysis_blocks_per_cu(c);
+  for (int c = 0; c < kNumClasses && !rc; ++c)  // classes 0..3 are FP64: a batch may hold both kinds
+    s->bpc[c] = analysis_blocks_per_cu(c, c < 4 ? kKindJacobi | kKindPoly : kKindJacobi);
   for (int k = 0; k < kSlots && !rc; ++k) {
     if (hipHostMalloc((void**)&s->h_hdr[k], sizeof(BatchHdr)) != hipSuccess ||
         hipHostMalloc((void**)&s->h_y[k], sizeof(double) * kStageDoubles) != hipSuccess ||
