@@ -3593,8 +3593,8 @@ __global__ __launch_bounds__(256) void k_big_update(const InstDesc* __restrict__
   }
 }
 
-// ---- debug instances, m > 128: the eigenvalues of each domain's A ------------
-// As for m <= 128, when a debug record is read: Cholesky, then the one-sided
+// ---- debug instances, m > 128: the eigenvalues of one domain's A -------------
+// As for m <= 128, when that domain's record is read: Cholesky, then the one-sided
 // Jacobi by blocks (L J = U Sigma).  The columns form NB blocks of 16 (NB even;
 // columns past m are unit vectors that never rotate).  A sweep is NB - 1 rounds
 // of a round-robin tournament between the blocks (circle method, block 0
@@ -3612,11 +3612,10 @@ __global__ __launch_bounds__(256) void k_big_update(const InstDesc* __restrict__
 // wavefronts hide; the panel's columns from LDS).
 constexpr int kBigCholWaves = 8;
 __global__ __launch_bounds__(64 * kBigCholWaves) void k_big_chol(const InstDesc* __restrict__ tab,
-                                                                 const BatchHdr* __restrict__ hdr, int cls) {
+                                                                 const BatchHdr* __restrict__ hdr, int cls, int item) {
   __shared__ double pnl[16][kBigM];
   const ClassBatch& cb = hdr->cls[cls];
-  if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
-  const BigDom D = big_dom(tab, cb, blockIdx.x);
+  const BigDom D = big_dom(tab, cb, item);
   const int m = D.I->m, mp = (m + 15) & ~15, tid = threadIdx.x, w = tid / 64, lane = tid % 64;
   for (int idx = tid; idx < kBigM * kBigM; idx += 64 * kBigCholWaves) {
     const int c = idx / kBigM, r = idx % kBigM;
@@ -3689,12 +3688,11 @@ __global__ __launch_bounds__(64 * kBigCholWaves) void k_big_chol(const InstDesc*
 
 // grid (nb / 2, items): the workgroup of block pair blockIdx.x in round `round`.
 __global__ __launch_bounds__(256) void k_big_round(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                                   int cls, int nb, int round) {
+                                                   int cls, int item, int nb, int round) {
   __shared__ double col[32 * kBigLd];
   __shared__ double nrm[32];
   const ClassBatch& cb = hdr->cls[cls];
-  if ((int)blockIdx.y >= cb.dom_off[cb.n]) return;
-  const BigDom D = big_dom(tab, cb, blockIdx.y);
+  const BigDom D = big_dom(tab, cb, item);
   if (D.f[0]) return;  // converged: uniform over the workgroup
   const int m = D.I->m, tid = threadIdx.x, w = blockIdx.x, n1 = nb - 1;
   const int a = w == 0 ? 0 : 1 + (round + w) % n1;
@@ -3822,11 +3820,8 @@ __global__ __launch_bounds__(256) void k_big_round(const InstDesc* __restrict__ 
   }
 }
 
-__global__ __launch_bounds__(64) void k_big_sweep(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                                  int cls) {
+__global__ void k_big_sweep(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr, int cls, int item) {
   const ClassBatch& cb = hdr->cls[cls];
-  const int item = blockIdx.x * 64 + threadIdx.x;
-  if (item >= cb.dom_off[cb.n]) return;
   const BigDom D = big_dom(tab, cb, item);
   if (D.f[0]) return;
   D.f[2] += 1;
@@ -3840,10 +3835,9 @@ __global__ __launch_bounds__(64) void k_big_sweep(const InstDesc* __restrict__ t
 
 // Thread c: lambda_c, the squared norm of column c of L J.
 __global__ __launch_bounds__(256) void k_big_lambda(const InstDesc* __restrict__ tab, const BatchHdr* __restrict__ hdr,
-                                                    int cls) {
+                                                    int cls, int item) {
   const ClassBatch& cb = hdr->cls[cls];
-  if ((int)blockIdx.x >= cb.dom_off[cb.n]) return;
-  const BigDom D = big_dom(tab, cb, blockIdx.x);
+  const BigDom D = big_dom(tab, cb, item);
   const int m = D.I->m, c = threadIdx.x;
   double* dbg = big_dbg(D);
   if (!dbg || c >= m) return;
@@ -4013,15 +4007,15 @@ void launch_big_analysis(int items, int rows_max, int m_max, const InstDesc* tab
   hipLaunchKernelGGL(k_big_update, dim3((rows_max + 15) / 16, (nt + 3) / 4, items), dim3(256), 0, s, tab, hdr, cls);
 }
 
-void launch_big_lambda(int items, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s) {
+void launch_big_lambda(int domain, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s) {
   const int cls = kBigClass, nb = 2 * ((m_max + 31) / 32);
-  hipLaunchKernelGGL(k_big_chol, dim3(items), dim3(64 * kBigCholWaves), 0, s, tab, hdr, cls);
+  hipLaunchKernelGGL(k_big_chol, dim3(1), dim3(64 * kBigCholWaves), 0, s, tab, hdr, cls, domain);
   for (int sw = 0; sw < kBigMaxSweeps; ++sw) {
     for (int r = 0; r < nb - 1; ++r)
-      hipLaunchKernelGGL(k_big_round, dim3(nb / 2, items), dim3(256), 0, s, tab, hdr, cls, nb, r);
-    hipLaunchKernelGGL(k_big_sweep, dim3((items + 63) / 64), dim3(64), 0, s, tab, hdr, cls);
+      hipLaunchKernelGGL(k_big_round, dim3(nb / 2), dim3(256), 0, s, tab, hdr, cls, domain, nb, r);
+    hipLaunchKernelGGL(k_big_sweep, dim3(1), dim3(1), 0, s, tab, hdr, cls, domain);
   }
-  hipLaunchKernelGGL(k_big_lambda, dim3(items), dim3(256), 0, s, tab, hdr, cls);
+  hipLaunchKernelGGL(k_big_lambda, dim3(1), dim3(256), 0, s, tab, hdr, cls, domain);
 }
 
 #define LETKF_POLY_KERNEL(cls, FN)             \

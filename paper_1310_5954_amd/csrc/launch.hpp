@@ -71,6 +71,6 @@ void launch_noalloc_setup(const InstDesc* src, const BatchHdr* src_hdr, unsigned
 void launch_big_analysis(int items, int rows_max, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
 // Eigenvalues of every domain of a debug instance of that class, from the A its
 // last analysis left (over the scratch of the stages).
-void launch_big_lambda(int items, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
+void launch_big_lambda(int domain, int m_max, const InstDesc* tab, BatchHdr* hdr, hipStream_t s);
 
 }  // namespace letkf

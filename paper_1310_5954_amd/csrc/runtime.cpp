@@ -1169,12 +1169,15 @@ int letkf_debug_domain(letkf_handle* h, int32_t domain, double* C_out, double* l
   if (domain < 0 || domain >= h->P.n_dom) return fail(LETKF_EINVAL, "domain out of range");
   const size_t m = h->P.m, per = 2 * m * m + m + kDbgTail;
   std::vector<double> buf(per);
-  int32_t sw = 0;
-  if (lam_out && h->cls == letkf::kBigClass) letkf::launch_big_lambda(h->P.n_dom, h->P.m, dev_desc(h), dev_hdr(h), s);
+  int32_t sw = 0, big = 0;
+  const bool big_lam = lam_out && h->cls == letkf::kBigClass;
+  if (big_lam) letkf::launch_big_lambda(domain, h->P.m, dev_desc(h), dev_hdr(h), s);
   else if (lam_out && h->desc.poly) letkf::launch_lambda(h->cls, dev_desc(h), domain, s);
   LETKF_HIP(hipMemcpyAsync(buf.data(), h->ws + h->L.dbg + domain * per * 8, per * 8, hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipMemcpyAsync(&sw, h->ws + h->L.dbg_sweeps + domain * 4, 4, hipMemcpyDeviceToHost, s));
+  if (big_lam) LETKF_HIP(hipMemcpyAsync(&big, h->ws + h->L.bigf + domain * 16, 4, hipMemcpyDeviceToHost, s));
   LETKF_HIP(hipStreamSynchronize(s));
+  if (big_lam && big != 1) return fail(LETKF_ENUMERIC, "the eigenvalues did not converge");
   if (C_out) std::memcpy(C_out, buf.data(), m * m * 8);
   if (lam_out) {
     std::vector<double> lam(buf.begin() + m * m, buf.begin() + m * m + m);
