@@ -4063,12 +4063,12 @@ int analysis_blocks_per_cu(int cls, int kinds) {
   if (kinds & kKindJacobi) {
     LETKF_ANA_KERNEL(cls, LETKF_OCC);
     if (e != hipSuccess || n < 1) n = 1;
-int analysis_max_grid(int cls, int kinds) { return cls % 4 == 3 && kinds == kKindPoly ? kParkSlots : 65535; }
-
     least = least ? min(least, n) : n;
   }
 #undef LETKF_OCC
   return least ? least : 1;
 }
+
+int analysis_max_grid(int cls, int kinds) { return cls % 4 == 3 && kinds == kKindPoly ? kParkSlots : 65535; }
 
 }  // namespace letkf
