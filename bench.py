@@ -865,7 +865,7 @@ def main() -> int:
                      p99_us=round(plain["p99_us"], 1), latency_frames=NL,
                      kernel_ms=dict(slopes=round(plain["kernel_ms"][0], 4), analysis=round(plain["kernel_ms"][1], 4),
                                     merge_forecast=round(plain["kernel_ms"][2], 4)),
-                     jacobi_sweeps_mean=round(plain["sweeps"] / max(plain["solves"], 1), 3),
+                     stage_products_mean=round(plain["sweeps"] / max(plain["solves"], 1), 3),
                      graph_replay=dict(frames_per_s=round(graph["fps"], 2), p50_us=round(graph["p50_us"], 1),
                                        p99_us=round(graph["p99_us"], 1)),
                      tuning=plain["tuning"], roofline=rf64)

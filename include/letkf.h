@@ -167,7 +167,10 @@ typedef struct letkf_domain_map {
 
 /* ---- single instance -------------------------------------------------- */
 
-/* Bytes of device workspace letkf_create needs for this problem. */
+/* Bytes of device workspace letkf_create needs for this problem.  Beyond the
+ * data's own size: above 128 members about 3 MB a domain (six 256 x 256 FP64
+ * matrices); LETKF_FP64 with 65..128 members and obs_instant 0 a slot of 115 KB
+ * for each of its first 256 domains (at most 29 MB). */
 int letkf_workspace_size(const letkf_dims* dims, const letkf_model* model,
                          const letkf_domain_map* map, int precision, uint32_t flags,
                          size_t* bytes);

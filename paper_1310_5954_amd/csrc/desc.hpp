@@ -68,9 +68,9 @@ struct InstDesc {
   double* pist_c;            // [n_dom][2][m] pistons added before the merge
   double* bigA;              // m > 128: [n_dom][256][256] A
   double* bigW;              // m > 128: [n_dom][5][256][256] M, M^2, P and two Z of the stages (column-major)
-  double* bigv;              // m > 128: [n_dom][5][256] b, wbar, spare, partial sums of |A^2|_F^2, spare
+  double* bigv;              // m > 128: [n_dom][5][256] b, wbar, shift and exponent, partial sums of norms, the stages' plan
   const uint8_t* guess;      // poly: [n_dom] first entry of the stages (stage_guess)
-  int32_t* bigf;             // m > 128: [n_dom][4] debug Jacobi: converged, rounds that rotated, sweeps; table row of the stages
+  int32_t* bigf;             // m > 128: [n_dom][4] debug Jacobi: converged, rounds that rotated, sweeps; stages done
   uint32_t* dom_sweeps;      // [n_dom] Jacobi sweeps (poly: products) of each domain, summed over every analysis
   double* Ascr;              // FP64, m <= 128: [n_dom][m(m+1)/2] each domain's A (lower triangle packed by rows), for refining wbar
   double* park;              // poly, 64 < m <= 128: [min(n_dom, kParkSlots)][kParkDoubles] a workgroup's Z between its stages
